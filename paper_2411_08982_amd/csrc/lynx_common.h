@@ -184,13 +184,15 @@ constexpr int kWsOrder = 16;                               // LYNX_MAX_N words
 constexpr int kWsActive = kWsOrder + LYNX_MAX_N;           // LYNX_MAX_N words
 constexpr int kWsMember = kWsActive + LYNX_MAX_N;          // LYNX_MAX_N * LYNX_MAX_T/32 words
 constexpr int kWsDone = kWsMember + LYNX_MAX_N * (LYNX_MAX_T / 32);   // FFN: gate/up completion counters
-constexpr int kWsDoneWords = 1024;                         // LYNX_MAX_N routed + (shared expert, token block) pairs
+constexpr int kWsDoneWords = 1024;                         // routed experts (LYNX_MAX_N; the rest is a limit: see moe_ffn_validate)
 constexpr int kWsFlags = kWsDone + kWsDoneWords;           // FFN: bit 0 = a bounded wait ran out
 constexpr int kWsPlanHdr = kWsFlags + 16;                  // FFN work plan (lynx_plan.h): header, 16 words
 constexpr int kPlanMaxBlocks = 512;                        // most (expert, token block) pairs: LYNX_MAX_N + LYNX_MAX_T * LYNX_MAX_K / 128, rounded up
 constexpr int kWsPlanBlk = kWsPlanHdr + 16;                // one record of four words per (expert, token block) pair
 constexpr int kWsPlanPairs = kWsPlanBlk + 4 * kPlanMaxBlocks;   // 16 pair ids of 16 bits per block: 8 words each
-constexpr int kWsRoutingWords = kWsPlanPairs + 8 * kPlanMaxBlocks;
+constexpr int kWsDoneShared = kWsPlanPairs + 8 * kPlanMaxBlocks;  // FFN: the same per (shared expert, token block) pair
+constexpr int kWsDoneSharedWords = 2048;
+constexpr int kWsRoutingWords = kWsDoneShared + kWsDoneSharedWords;
 constexpr size_t kWsRoutingBytes = 98304;
 static_assert((size_t)kWsRoutingWords * 4 <= kWsRoutingBytes, "routing scratch does not fit its reservation");
 

@@ -39,7 +39,8 @@ constexpr int kPF = 8;                       // staged path: weight tiles in fli
 #endif
 constexpr int kPFD = LYNX_PFD;               // direct path: the same (most; see DirectDepth for the depth per format)
 constexpr int kStageBytes = 2 * 18432;       // two LDS buffers for the staged token tile
-constexpr int kStageBytesBig = 2 * 128 * (4 * 64 + 16);   // the same in the large-batch kernels (128 tokens x 4 k-steps)
+// LDS for the staged token tile of passes of up to `tokens` tokens: 64 as above, else 4 k-steps double-buffered
+constexpr int stage_bytes(int tokens) { return tokens <= 64 ? kStageBytes : 2 * tokens * (4 * 64 + 16); }
 
 // Optional per-workgroup timeline of the expert kernel (-DLYNX_TIMELINE; measurement builds only): for every workgroup
 // four stamps of the chip-wide 100 MHz clock (start, item known, wait over, work done) and what it was (projection,
@@ -398,11 +399,13 @@ __device__ __forceinline__ BufferRsrc weights_resource(const uint4 *wave_base)
 }
 constexpr int kAuxNonTemporal = 2;
 // index: in 16-byte units from this lane's piece of the run's first tile; live = false: nothing is fetched, zero returns
+// KEEP: an ordinary cached load, for weights that another workgroup of the launch reads too
+template <bool KEEP = false>
 __device__ __forceinline__ uint4 ring_load_weights(BufferRsrc rs, int index, bool live)
 {
     unsigned off = live ? ((unsigned)index + (unsigned)lane_id()) * 16u : kNoToken;
     asm volatile("" : "+v"(off));
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kAuxNonTemporal);
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, KEEP ? 0 : kAuxNonTemporal);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
@@ -667,41 +670,66 @@ __device__ __forceinline__ void direct_finish(const WorkItem &w, const DirectPla
     }
 }
 
-// Staged: the token tile is staged through LDS in chunks of KS k-steps, double buffered and shared by
-// the four waves, which own four consecutive 16-row tiles and walk all of K.
-// PAIR (down projection, 128-row workgroups): the wave owns two consecutive 16-row tiles and walks them together,
-// pair_second uint4 units apart, so that every token fragment read from LDS feeds two MFMAs, as gate and up do (accg =
-// first tile, accu = second): half the LDS reads per weight byte and half as many down workgroups (measured 2-4 %
-// off the launch for every shape beyond 64 tokens).
-template <bool DUAL, int NT, int KS, int WF, bool PAIR = false>
-__device__ __forceinline__ void stream_staged(const uint4 *__restrict__ Wt, int KT, int K,
-                                              const uint16_t *__restrict__ B, const int *rowoff, char *stage,
-                                              const uint2 *__restrict__ Sl, int kt0, bool sc_second, int pair_second,
-                                              f32x4 (&accg)[NT], f32x4 (&accu)[NT])   // KT weight tiles from Wt; B columns [0, K)
-{   // (MXFP4: Sl = this lane's scale dwords of the wave's row group, kt0 = the first k-tile's index, sc_second = a
-    // down-projection wave on the second row tile of its pair)
-    constexpr bool TWO = DUAL || PAIR;
-    const int second = DUAL ? kWave : pair_second;
+// Staged path: the token tile is staged through LDS in chunks of KS k-steps of 32 columns, double buffered and shared by
+// the four waves, each of which owns RT consecutive 16-row tiles (of gate and of up, or of down) and walks all of K.
+// Every token fragment read from LDS feeds the S = RT (down) or 2 RT (gate/up) weight streams of the wave.
+// The fragments are requested ahead of their products, in order: left to itself the compiler read one, waited for it and
+// multiplied (every 64 cycles of MFMA behind a full LDS latency; with one column tile per fragment and stream, Mixtral
+// shapes at 512 tokens 830 -> 758 us per layer).
+// D = weight tiles in flight per stream.  The sizes are bounded by the 256 registers of a wave at two workgroups per CU:
+// sums S*NT*4, ring S*D*4, pieces of the next token chunk NT*KS.
+template <int S, int NT, int WF>
+struct StagedShape {
+    static constexpr int D = S == 4 ? (WF == 0 && NT < 8 ? 8 : 4) : kPF;
+    static constexpr int KS = NT == 2 ? 8 : (NT == 8 && S == 4) ? 2 : 4;
+    static constexpr int BQ = S == 4 && NT == 8 ? 2 : 4;   // token fragments read ahead (the same at 2 and 4)
+};
+
+// KEEP: the weights are read by another workgroup too (an expert with several token blocks): cached loads.
+template <bool DUAL, int RT, int NT, int WF, bool KEEP>
+__device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowoff, const int *outrow, char *stage)
+{
+    constexpr int MATS = DUAL ? 2 : 1;
+    constexpr int S = RT * MATS;
+    constexpr int D = StagedShape<S, NT, WF>::D, KS = StagedShape<S, NT, WF>::KS;
+    constexpr int KC = TileCols<WF>::value;
     constexpr int TS = 1 << WF;                  // 32-column steps of the staged token tile per weight tile
     constexpr int ROWB = KS * 64 + 16;           // LDS bytes per token row (+16: conflict-free 16-byte reads)
     constexpr int BUFB = NT * 16 * ROWB;
-    static_assert(2 * BUFB <= (NT > 4 ? kStageBytesBig : kStageBytes), "token tile does not fit the LDS stage");
+    static_assert(2 * BUFB <= stage_bytes(NT * 16), "token tile does not fit the LDS stage");
     constexpr int PIECES = NT * 16 * KS * 4;     // 16-byte pieces per chunk
-    static_assert(PIECES % kFfnThreads == 0, "pieces must divide evenly over the workgroup");
+    static_assert(PIECES % kFfnThreads == 0 && kFfnThreads % (KS * 4) == 0, "pieces must divide evenly over the workgroup");
     constexpr int PPT = PIECES / kFfnThreads;
-    static_assert((kPF * TS) % KS == 0, "a ring turn must hold whole chunks");
-    constexpr int WSTEP = DUAL ? 2 * kWave : kWave;
+    static_assert((D * TS) % KS == 0 && KS % TS == 0, "a ring turn must hold whole chunks, a chunk whole tiles");
+    constexpr int WSTEP = MATS * kWave;
 
     const int tid = threadIdx.x, lane = lane_id();
+    const int KTrow = w.K / KC;                  // tiles between consecutive row tiles
+    const int KT = w.ksteps, K = KT * KC;        // weight tiles and token columns of this item
+    const int rt = (w.tile * kFfnWaves + wave_id()) * RT;   // w.tile counts units of 64 * RT rows
+    const bool wave_active = rt * 16 < w.R;      // idle waves read tile 0 (in bounds) and store nothing
+    const int rtc = wave_active ? rt : 0;
     const int last = KT - 1;
     const int lastc = (KT * TS + KS - 1) / KS - 1;
+    // the second of a wave's row tiles may lie past the last row (gate/up; R / 16 is even for down): it re-reads the first
+    const int tile2 = (RT == 1 || rtc * 16 + 16 < w.R) ? KTrow * WSTEP : 0;
+
+    // MXFP4: scale dwords of the wave's row groups (gate/up: one per row tile; down: one per row pair)
+    constexpr int SG = DUAL ? RT : (RT + 1) / 2;
+    const uint2 *Sl[SG];
+#pragma unroll
+    for (int g = 0; g < SG; ++g)
+        Sl[g] = WF == 2 ? reinterpret_cast<const uint2 *>(w.sc) +
+                              (size_t)(DUAL ? rtc + (tile2 ? g : 0) : rtc >> 1) * mx_kt4(w.K) * kWave + lane
+                        : nullptr;
+    const bool sc_second = !DUAL && RT == 1 && (rtc & 1);
 
     // This thread's staging pieces: (token row, 16-byte piece inside the chunk).  The rows' offsets stay in the LDS
     // table and are looked up again for every chunk: registers are what this path is short of.  The pieces are read
     // through a buffer resource over the B array; a piece of a row without a token, or past the row's last column
     // (the last chunk of a ragged K, or a row shorter than one chunk), carries an offset out of range: nothing is
     // fetched for it and it arrives as zero, which is what the stage has to hold there.
-    const BufferRsrc rb = token_rows_resource(B);
+    const BufferRsrc rb = token_rows_resource(w.B + (size_t)w.kbeg * KC);
     const int pc0 = (tid % (KS * 4)) * 8;   // column of every piece of this thread inside a chunk (256 % (KS*4) == 0)
     uint4 xr[PPT];
     // chunk c: request it ... (nothing here reads what was loaded: a read would have to wait for the load, and
@@ -724,25 +752,35 @@ __device__ __forceinline__ void stream_staged(const uint4 *__restrict__ Wt, int 
         }
     };
 
-    const BufferRsrc rw = weights_resource(Wt);
-    uint4 wg[kPF], wu[kPF];
-    uint2 sq[kPF];
+    const BufferRsrc rw = weights_resource(w.W + ((size_t)rtc * KTrow + w.kbeg) * WSTEP);
+    uint4 wr[D][S];
+    uint2 sq[D][SG];
+    auto load_w = [&](int slot, int s) {   // stream m + MATS * r: matrix m of row tile r; past the end nothing is fetched
 #pragma unroll
-    for (int j = 0; j < kPF; ++j) {
-        const int s = min(j, last);
-        wg[j] = ring_load_weights(rw, j * WSTEP, j <= last);
-        wu[j] = TWO ? ring_load_weights(rw, j * WSTEP + second, j <= last) : zero4();
-        if (WF == 2) sq[j] = ring_load_scales(Sl, ((kt0 + s) >> 2) * kWave);
-    }
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int m = 0; m < MATS; ++m)
+                wr[slot][r * MATS + m] = ring_load_weights<KEEP>(rw, s * WSTEP + m * kWave + r * tile2, s <= last);
+        if (WF == 2)
+#pragma unroll
+            for (int g = 0; g < SG; ++g) sq[slot][g] = ring_load_scales(Sl[g], ((w.kbeg + min(s, last)) >> 2) * kWave);
+    };
+    f32x4 acc[S][NT];
+#pragma unroll
+    for (int j = 0; j < S; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < D; ++j) load_w(j, j);
     load_x(0);
     store_x(0);
     __syncthreads();
 
-    // this lane's B-fragment offset inside a token tile (its column group: 8 columns, or 16 for 64-column tiles)
+    // this lane's B-fragment offset inside a token tile (its column group: 8, 16 or 32 columns)
     const int brow = (lane & 15) * ROWB + (lane >> 4) * (16 << WF);
-    for (int s0 = 0; s0 < KT; s0 += kPF) {
+    for (int s0 = 0; s0 < KT; s0 += D) {
 #pragma unroll
-        for (int u = 0; u < kPF; ++u) {
+        for (int u = 0; u < D; ++u) {
             const int s = s0 + u;
             const int c = (s * TS) / KS;
             if ((u * TS) % KS == 0) {
@@ -752,60 +790,74 @@ __device__ __forceinline__ void stream_staged(const uint4 *__restrict__ Wt, int 
             // (tiles past the end of the run were not fetched and arrived as zeros; a wave without rows multiplies
             // tile 0 and stores nothing)
             const char *buf = stage + (c & 1) * BUFB + brow + ((u * TS) % KS) * 64;
-            bf16x8 ag[TS], au[TS];
-            const int kt = kt0 + min(s, last);
-            decode_tile<WF>(wg[u], WF == 2 ? mx_scale(sc_second ? sq[u].y : sq[u].x, kt) : 1.0f, ag);
-            if (TWO) decode_tile<WF>(wu[u], WF == 2 ? mx_scale(sq[u].y, kt) : 1.0f, au);
+            const int kt = w.kbeg + min(s, last);
+            bf16x8 a[S][TS];
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int h = 0; h < TS; ++h) {
-                    const bf16x8 b = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + nt * 16 * ROWB + 16 * h));
-                    accg[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag[h], b, accg[nt], 0, 0, 0);
-                    if (TWO) accu[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au[h], b, accu[nt], 0, 0, 0);
+            for (int j = 0; j < S; ++j) {
+                float sc = 1.0f;
+                if (WF == 2) {
+                    const uint2 q = sq[u][DUAL ? j / MATS : j / 2];
+                    sc = mx_scale((DUAL ? (j & 1) : RT == 1 ? (int)sc_second : (j & 1)) ? q.y : q.x, kt);
                 }
+                decode_tile<WF>(wr[u][j], sc, a[j]);
+            }
+            // token fragments in the order (k-step, token column), BQ of them requested ahead of their products
+            constexpr int G = TS * NT, BQ = StagedShape<S, NT, WF>::BQ < G ? StagedShape<S, NT, WF>::BQ : G;
+            auto read_b = [&](int i) {
+                return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + (i % NT) * 16 * ROWB + 16 * (i / NT)));
+            };
+            bf16x8 bq[BQ];
+#pragma unroll
+            for (int i = 0; i < BQ; ++i) bq[i] = read_b(i);
             __builtin_amdgcn_sched_barrier(0);
-            const int sn = s + kPF;        // refills past the end of the run fetch nothing
-            wg[u] = ring_load_weights(rw, sn * WSTEP, sn <= last);
-            if (TWO) wu[u] = ring_load_weights(rw, sn * WSTEP + second, sn <= last);
-            if (WF == 2) sq[u] = ring_load_scales(Sl, ((kt0 + min(sn, last)) >> 2) * kWave);
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+#pragma unroll
+                for (int j = 0; j < S; ++j)
+                    acc[j][i % NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j][i / NT], bq[i % BQ], acc[j][i % NT], 0, 0, 0);
+                if (i + BQ < G) bq[i % BQ] = read_b(i + BQ);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            if ((u * TS + TS - 1) % KS == KS - 1) {
+            load_w(u, s + D);
+            __builtin_amdgcn_sched_barrier(0);
+            if ((u * TS + TS) % KS == 0) {
                 store_x(c + 1);
                 __syncthreads();
             }
         }
     }
-}
-
-template <bool DUAL, int NT, int KS, int WF, bool PAIR = false>
-__device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowoff, const int *outrow, char *stage)
-{
-    constexpr int WSTEP = DUAL ? 2 * kWave : kWave;
-    constexpr int KC = TileCols<WF>::value;
-    const int KT = w.K / KC;
-    // w.tile counts 64-row units; a wave of a PAIR pass owns two row tiles of the 128 rows that start there
-    const int rt = w.tile * kFfnWaves + (PAIR ? 2 : 1) * wave_id();
-    const bool wave_active = rt * 16 < w.R;   // (down: R/16 is even, so the second tile of a pair exists too)
-    const int rtc = wave_active ? rt : 0;   // idle waves read tile 0 (in bounds) and contribute nothing
-    f32x4 accg[NT], accu[NT];
-    clear_acc<NT>(accg, accu);
-    const uint2 *Sl = nullptr;
-    if (WF == 2)
-        Sl = reinterpret_cast<const uint2 *>(w.sc) + (size_t)(DUAL ? rtc : rtc >> 1) * mx_kt4(w.K) * kWave + lane_id();
-    stream_staged<DUAL, NT, KS, WF, PAIR>(w.W + ((size_t)rtc * KT + w.kbeg) * WSTEP, w.ksteps, w.ksteps * KC,
-                                          w.B + (size_t)w.kbeg * KC, rowoff, stage, Sl, w.kbeg, !DUAL && !PAIR && (rtc & 1),
-                                          KT * kWave, accg, accu);
     if (!wave_active) return;
     int orow[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) orow[nt] = outrow[nt * 16 + (lane_id() & 15)];
-    if (PAIR) {
-        epilogue<false, NT, WF>(accg, accg, w.out, w.ldo, rt * 16, orow, w.sc, w.R);
-        epilogue<false, NT, WF>(accu, accu, w.out, w.ldo, rt * 16 + 16, orow, w.sc, w.R);
-    } else {
-        epilogue<DUAL, NT, WF>(accg, accu, w.out, w.ldo, rt * 16, orow, w.sc, w.R);
+    for (int nt = 0; nt < NT; ++nt) orow[nt] = outrow[nt * 16 + (lane & 15)];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        if ((rt + r) * 16 >= w.R) break;
+        epilogue<DUAL, NT, WF>(acc[r * MATS], acc[r * MATS + MATS - 1], w.out, w.ldo, (rt + r) * 16, orow, w.sc, w.R);
     }
+}
+
+// Tokens per pass of the staged path.  The large-batch kernels take 128 with bf16 weights.  With quantised weights the
+// operands that a tile is converted to leave no registers for eight token columns beside four weight streams (40-60
+// spilled): passes of 64, whose workgroups share an expert's weights through the L2 (see resolve_item).
+constexpr int staged_tokens(int big, int wf) { return big && wf == 0 ? kTokBlockBig : kTokBlock; }
+
+// One pass of the staged path over nb tokens.  Weights that other workgroups stream too (an expert of several token
+// blocks) are read with cached loads: the later block finds them in the memory-side cache (Mixtral shapes, 1000 tokens,
+// 1336 against 1230 us per layer).
+template <bool DUAL, int RT, int BIG, int WF>
+__device__ __forceinline__ void staged_pass(const WorkItem &w, int nb, const int *rowoff, const int *outrow, char *stage)
+{
+    constexpr int TB = staged_tokens(BIG, WF);
+    if (nb <= 32)
+        expert_staged<DUAL, RT, 2, WF, false>(w, rowoff, outrow, stage);
+    else if (TB > 64 && nb <= 64)
+        expert_staged<DUAL, RT, 4, WF, false>(w, rowoff, outrow, stage);
+    else if (BIG && w.te_all > TB)
+        expert_staged<DUAL, RT, TB / 16, WF, BIG != 0>(w, rowoff, outrow, stage);
+    else
+        expert_staged<DUAL, RT, TB / 16, WF, false>(w, rowoff, outrow, stage);
 }
 
 // Both projections of every invoked and shared expert in ONE launch.  Grid: all gate/up workgroups, then
@@ -847,21 +899,30 @@ constexpr int kSpinLimit = 1 << 17;   // polls of a counter (about a microsecond
 
 __device__ __forceinline__ int done_slot(const GemmParams &p, const WorkItem &w)
 {
-    return w.shared_s < 0 ? w.e : LYNX_MAX_N + w.shared_s * p.shared_tblocks + w.tok0 / p.tok_block;
+    return w.shared_s < 0 ? w.e : kWsDoneShared - kWsDone + w.shared_s * p.shared_tblocks + w.tok0 / p.tok_block;
 }
 
+// 16-row tiles per wave on the staged path.  Two in the large-batch kernels (gate/up, and down with undivided K): a token
+// fragment read from LDS then feeds four MFMAs (gate/up) or two (down), and a unit of 128 rows stages the tokens half as
+// often as two of 64.
+constexpr int staged_row_tiles(bool dual, int kw, int big) { return big && (dual ? big == 2 : kw == 1) ? 2 : 1; }
+
 // sub >= 0 (gate/up, KW = 4 only): the workgroup takes row tile `sub` of the four that workgroup b stands for.
-template <bool DUAL, int KW, bool BIG, int WF>
+template <bool DUAL, int KW, int BIG, int WF>
 __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const FfnParams &fp, char *stage, int *rowoff,
                                             int *outrow, int sub = -1)
 {
-    constexpr int TB = BIG ? kTokBlockBig : kTokBlock;   // tokens per pass
+    constexpr int TB = staged_tokens(BIG, WF);   // tokens per pass
     int units;
     LYNX_TS_BEGIN(DUAL ? (sub >= 0 ? 2 : 1) : 0, b);
     WorkItem w = resolve_item<DUAL, WF>(p, b, units);
     if (!w.valid) return;
     if (sub >= 0) w.tile = w.tile * kFfnWaves + sub;
     int32_t *counter = fp.done + done_slot(p, w);
+    if (DUAL && BIG == 2 && w.te_all <= kDirectMaxTokens) {   // the item's 128 rows as two direct units of 64
+        w.tile *= 2;
+        units = min(2, (w.R + 63) / 64 - w.tile);
+    }
     const int unit0 = w.tile;
     LYNX_TS(1);
     // Waits for this expert's (this token block's) intermediate vectors (down projection in the same launch as
@@ -907,58 +968,52 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
     } else {
         wait_for_h();
         LYNX_TS(2);
-        // staged path: units of 64 rows.  A direct workgroup covers 16*RW rows (gate/up) or 32*RW rows (down).
-        constexpr int kRowsPerWG = 16 * (kFfnWaves / KW) * (DUAL ? 1 : 2);
-        constexpr int kUnits = kRowsPerWG >= 64 ? kRowsPerWG / 64 : 1;      // staged units per row unit
-        constexpr int kShare = kRowsPerWG >= 64 ? 1 : 64 / kRowsPerWG;      // workgroups that share one staged unit
-        // (a gate/up workgroup that shares its unit with others and leaves the work to one of them still reports
-        // below: a down workgroup waits for the row tiles of all gate/up workgroups of its expert)
-        // (shared experts see every token, so the host knows that they are staged and gives them one workgroup
-        // per unit)
-        const bool shared = w.shared_s >= 0;
-        const int tid = threadIdx.x;
-        for (int un = 0; un < units; ++un) {
-            const int tile = unit0 + un;
-            // Of the workgroups that share a unit one does the work and the others leave.  Which one rotates with the
-            // unit and the expert: the sharing workgroups have consecutive indices, so a fixed choice would put all the
-            // staged work of the launch on the XCDs that the first of every four workgroups goes to (measured: two of
-            // the eight XCDs ended their gate/up work at 44 us, the others at 31 us).
-            if (!shared && (tile % kShare) != ((tile / kShare + w.e) % kShare)) continue;
-            const int s0 = shared ? tile : (tile / kShare) * kUnits;
-            // a 128-row down workgroup does its two 64-row units in one pass, two row tiles per wave
-            constexpr bool kPair = !DUAL && kUnits == 2;
-            const bool pair = kPair && !shared;
-            const int sn = (shared || pair) ? 1 : kUnits;
-            for (int su = 0; su < sn; ++su) {
-                w.tile = s0 + su;
-                if (w.tile * 64 >= w.R) break;
-                for (int i0 = w.tok0; i0 < w.Te; i0 += TB) {
-                    const int nb = min(w.Te - i0, TB);
-                    __syncthreads();   // the previous pass has read rowoff / outrow and the stage
-                    if (tid < TB) {
-                        int ro, orow;
-                        token_rows<DUAL>(p, w, tid < nb ? i0 + tid : w.Te, ro, orow);
-                        rowoff[tid] = ro;
-                        outrow[tid] = orow;
+        // staged path.  The token tables of one pass: tokens [i0, i0 + nb) of the expert
+        auto load_tables = [&](int i0, int nb) {
+            const int tid = threadIdx.x;
+            if (tid < TB) {
+                int ro, orow;
+                token_rows<DUAL>(p, w, tid < nb ? i0 + tid : w.Te, ro, orow);
+                rowoff[tid] = ro;
+                outrow[tid] = orow;
+            }
+            __syncthreads();
+        };
+        constexpr int kRT = staged_row_tiles(DUAL, KW, BIG);
+        if constexpr (BIG) {
+            // the item is one pass over one unit of 64 * kRT rows (straight-line on purpose: loops around the passes
+            // cost registers that they do not have)
+            const int nb = w.Te - w.tok0;
+            load_tables(w.tok0, nb);
+            staged_pass<DUAL, kRT, BIG, WF>(w, nb, rowoff, outrow, stage);
+        } else {
+            // units of 64 rows.  A direct workgroup covers 16*RW rows (gate/up) or 32*RW rows (down).
+            constexpr int kRowsPerWG = 16 * (kFfnWaves / KW) * (DUAL ? 1 : 2);
+            constexpr int kUnits = kRowsPerWG >= 64 ? kRowsPerWG / 64 : 1;      // staged units per row unit
+            constexpr int kShare = kRowsPerWG >= 64 ? 1 : 64 / kRowsPerWG;      // workgroups that share one staged unit
+            // (a gate/up workgroup that shares its unit with others and leaves the work to one of them still reports
+            // below: a down workgroup waits for the row tiles of all gate/up workgroups of its expert)
+            // (shared experts see every token, so the host knows that they are staged and gives them one workgroup
+            // per unit)
+            const bool shared = w.shared_s >= 0;
+            for (int un = 0; un < units; ++un) {
+                const int tile = unit0 + un;
+                // Of the workgroups that share a unit one does the work and the others leave.  Which one rotates with the
+                // unit and the expert: the sharing workgroups have consecutive indices, so a fixed choice would put all
+                // the staged work of the launch on the XCDs that the first of every four workgroups goes to (measured:
+                // two of the eight XCDs ended their gate/up work at 44 us, the others at 31 us).
+                if (!shared && (tile % kShare) != ((tile / kShare + w.e) % kShare)) continue;
+                const int s0 = shared ? tile : (tile / kShare) * kUnits;
+                const int sn = shared ? 1 : kUnits;
+                for (int su = 0; su < sn; ++su) {
+                    w.tile = s0 + su;
+                    if (w.tile * 64 >= w.R) break;
+                    for (int i0 = w.tok0; i0 < w.Te; i0 += TB) {
+                        const int nb = min(w.Te - i0, TB);
+                        __syncthreads();   // the previous pass has read rowoff / outrow and the stage
+                        load_tables(i0, nb);
+                        staged_pass<DUAL, kRT, BIG, WF>(w, nb, rowoff, outrow, stage);
                     }
-                    __syncthreads();
-                    if constexpr (kPair) {
-                        if (pair) {
-                            if (nb <= 32)
-                                expert_staged<DUAL, 2, 8, WF, true>(w, rowoff, outrow, stage);
-                            else if (!BIG || nb <= 64)
-                                expert_staged<DUAL, 4, 4, WF, true>(w, rowoff, outrow, stage);
-                            else
-                                expert_staged<DUAL, 8, 4, WF, true>(w, rowoff, outrow, stage);
-                            continue;
-                        }
-                    }
-                    if (nb <= 32)
-                        expert_staged<DUAL, 2, 8, WF>(w, rowoff, outrow, stage);
-                    else if (!BIG || nb <= 64)
-                        expert_staged<DUAL, 4, 4, WF>(w, rowoff, outrow, stage);
-                    else
-                        expert_staged<DUAL, 8, 4, WF>(w, rowoff, outrow, stage);
                 }
             }
         }
@@ -976,13 +1031,14 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
 #endif
 constexpr int kWgPerCuSmall = LYNX_WGCU;   // workgroups per CU of the kernels for batches of at most 64 tokens
 
-template <int KWD, bool BIG, int WF>
+template <int KWD, int BIG, int WF>
 __global__ __launch_bounds__(kFfnThreads, (BIG || WF != 0) ? 2 : kWgPerCuSmall) void ffn_kernel(FfnParams fp)
 {
     // staged token tile, or the K-slice partial sums
-    __shared__ __attribute__((aligned(16))) char stage[BIG ? kStageBytesBig : kStageBytes];
-    __shared__ int rowoff[BIG ? kTokBlockBig : kTokBlock];   // staged path: element offset of each token's B row, -1 = none
-    __shared__ int outrow[BIG ? kTokBlockBig : kTokBlock];   // staged path: output row of each token, -1 = none
+    constexpr int TB = staged_tokens(BIG, WF);
+    __shared__ __attribute__((aligned(16))) char stage[stage_bytes(TB)];
+    __shared__ int rowoff[TB];   // staged path: element offset of each token's B row, -1 = none
+    __shared__ int outrow[TB];   // staged path: output row of each token, -1 = none
     const int b = blockIdx.x + fp.block0;
     if (b < fp.gu_blocks) {
         // Gate/up workgroups take four row tiles, one per wave, and the dispatcher hands workgroups to the CUs
@@ -1026,6 +1082,7 @@ __global__ __launch_bounds__(256) void plan_kernel(const int32_t *__restrict__ o
     __shared__ int count[LYNX_MAX_N], offs[LYNX_MAX_N], blk0[LYNX_MAX_N];
     const int tid = threadIdx.x;
     for (int i = tid; i < kWsDoneWords + 16; i += 256) ws[kWsDone + i] = 0;
+    for (int i = tid; i < ps.shared_pairs; i += 256) ws[kWsDoneShared + i] = 0;
     if (tid < N) {
         const int o0 = offsets[tid], o1 = offsets[tid + 1];
         const bool ok = o0 >= 0 && o1 > o0 && o1 <= P;
@@ -1292,7 +1349,8 @@ static Tunables g_tune;
 // Everything the host decides from the sizes alone.
 struct FfnShape {
     int kwd;            // K slices of a down workgroup's waves
-    bool big, single;   // 128-token staged passes; one launch for both projections
+    int big;            // 0 = at most 64 tokens; 1, 2 = larger batches, gate/up units of 64 or of 128 rows
+    bool single;        // one launch for both projections
     int tok_block;
     int max_blocks;     // most (expert, token block) pairs of a batch
     PlanShape plan;
@@ -1307,16 +1365,23 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     s.kwd = pick_k_waves(F, false, T, max_experts, 16 >> format);
     const int forced = g_tune.dn_kw.load();
     if (forced == 1 || forced == 2 || (forced == 4 && T <= kDirectMaxTokens)) s.kwd = forced;
-    s.big = T > kTokBlock;
+    // Gate/up units of 128 rows when the experts hold more than 64 tokens on average: fewer, longer workgroups that stage
+    // the tokens half as often (Mixtral shapes, 1000 tokens: 1156 -> 1126 us; DeepSeek-V2-Lite shapes, 1000: 343 -> 333).
+    // With fewer tokens the weight stream is the bound and the finer units fill the chip more evenly (Mixtral shapes, 128
+    // tokens: 454 against 466 us, 256: 557 against 574).
+    s.big = T <= kTokBlock ? 0 : (long)T * k > (long)kTokBlock * N ? 2 : 1;
     s.single = single_launch(T, F);
-    s.tok_block = s.big ? kTokBlockBig : kTokBlock;
+    s.tok_block = staged_tokens(s.big, format);
     s.max_blocks = plan_max_blocks(T, N, k, s.tok_block);
+    s.plan.shared_pairs = n_shared * (T > kDirectMaxTokens ? (T + s.tok_block - 1) / s.tok_block : 1);
     const int rows_dn = 16 * (kFfnWaves / s.kwd) * 2;
-    s.plan.units_gu = (F + 16 * kFfnWaves - 1) / (16 * kFfnWaves);
+    const int rows_gu = 64 * staged_row_tiles(true, 1, s.big);
+    s.plan.units_gu = (F + rows_gu - 1) / rows_gu;
     s.plan.units_dn = (H + rows_dn - 1) / rows_dn;
     s.plan.tok_block = s.tok_block;
     // Longer down items only where the staged unit and the direct workgroup are the same 64 rows (two K slices).
-    s.plan.dn_m_max = s.kwd <= 2 ? max(1, g_tune.dn_m_max.load()) : 1;
+    // (not in the large-batch kernels, whose items are single passes)
+    s.plan.dn_m_max = s.kwd <= 2 && !s.big ? max(1, g_tune.dn_m_max.load()) : 1;
     s.plan.dn_cap = max(1, g_tune.dn_cap.load());
     return s;
 }
@@ -1326,15 +1391,15 @@ PlanShape ffn_plan_shape(int T, int H, int F, int N, int k, int n_shared, int fo
     return ffn_shape(T, H, F, N, k, n_shared, format).plan;
 }
 
-static void set_tiles(GemmParams &p, int units_r, int rows_per_wg, int routed_items)
+static void set_tiles(GemmParams &p, int units_r, int rows_per_wg, int routed_items, int tok_block)
 {
     p.tiles_r = units_r;
     // shared experts process all T tokens: staged (units of 64 rows, one per workgroup) when T is past the direct limit
-    const int rows_shared = p.T > kDirectMaxTokens ? 64 : rows_per_wg;
+    const int rows_shared = p.T > kDirectMaxTokens && p.T <= kTokBlock ? 64 : rows_per_wg;
     p.tiles_s = p.n_shared ? (p.Rs + rows_shared - 1) / rows_shared : 0;
     // ... and then a workgroup with all T tokens would make one pass per 64 tokens over the same weights and be by
     // far the longest of the launch: the passes go to workgroups of their own instead.
-    p.tok_block = p.T > kTokBlock ? kTokBlockBig : kTokBlock;
+    p.tok_block = tok_block;
     p.shared_tblocks = p.T > kDirectMaxTokens ? (p.T + p.tok_block - 1) / p.tok_block : 1;
     p.tiles_s_stride = p.shared_tblocks > 1 ? (p.tiles_s + 7) / 8 * 8 : p.tiles_s;
     p.shared_blocks = p.n_shared * p.shared_splits * p.shared_tblocks * p.tiles_s_stride;
@@ -1348,14 +1413,15 @@ static unsigned grid_blocks(const GemmParams &p) { return (unsigned)(p.shared_bl
 // workgroups.  A dynamic-LDS pad makes exactly kWgPerCu workgroups fit a CU, which spreads such grids.
 constexpr int kLdsPerCu = 160 * 1024;
 
-template <int KWD, bool BIG, int WF>
+template <int KWD, int BIG, int WF>
 static int launch_padded(const FfnParams &fp, unsigned blocks, hipStream_t st)
 {
-    constexpr int kWgPerCu = (BIG || WF != 0) ? 2 : kWgPerCuSmall;
-    constexpr int kLdsTargetPerWg = kWgPerCu == 2 ? 56 * 1024 : kLdsPerCu / kWgPerCu / 1024 * 1024;   // (at most 64 KiB per workgroup)
+    constexpr int kWgPerCu = BIG == 3 ? 1 : (BIG || WF != 0) ? 2 : kWgPerCuSmall;
+    constexpr int kLdsTargetPerWg = kWgPerCu == 1 ? 84 * 1024 : kWgPerCu == 2 ? 56 * 1024 : kLdsPerCu / kWgPerCu / 1024 * 1024;   // (at most 64 KiB per workgroup)
     static_assert(kLdsTargetPerWg * (kWgPerCu + 1) > kLdsPerCu && kLdsTargetPerWg * kWgPerCu <= kLdsPerCu, "LDS pad");
     // what the kernel declares itself: the stage and the two token tables
-    constexpr int kStatic = (BIG ? kStageBytesBig : kStageBytes) + 2 * 4 * (BIG ? kTokBlockBig : kTokBlock) ;
+    constexpr int TB = staged_tokens(BIG, WF);
+    constexpr int kStatic = stage_bytes(TB) + 2 * 4 * TB;
     constexpr int pad = kLdsTargetPerWg > kStatic ? kLdsTargetPerWg - kStatic : 0;
     static_assert((kStatic + pad) * kWgPerCu <= kLdsPerCu, "the workgroups must fit a CU");
     hipLaunchKernelGGL((ffn_kernel<KWD, BIG, WF>), dim3(blocks), dim3(kFfnThreads), pad, st, fp);
@@ -1375,8 +1441,8 @@ template <int WF>
 static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
 {
     const GemmParams &d = fp.dn;
-    set_tiles(fp.gu, sh.plan.units_gu, 16 * kFfnWaves, sh.plan.units_gu * sh.max_blocks);   // gate/up: four row tiles per workgroup
-    set_tiles(fp.dn, sh.plan.units_dn, 16 * (kFfnWaves / sh.kwd) * 2, plan_down_grid(sh.plan, sh.max_blocks));
+    set_tiles(fp.gu, sh.plan.units_gu, 64 * staged_row_tiles(true, 1, sh.big), sh.plan.units_gu * sh.max_blocks, sh.tok_block);   // gate/up: four row tiles per workgroup
+    set_tiles(fp.dn, sh.plan.units_dn, 16 * (kFfnWaves / sh.kwd) * 2, plan_down_grid(sh.plan, sh.max_blocks), sh.tok_block);
     fp.gu.dn_m_max = fp.dn.dn_m_max = sh.plan.dn_m_max;
     // the split of the last round needs up to three more workgroups per workgroup it replaces
     // (not for batches of more than 32 tokens: more and more experts are then on the staged path, whose unit is the
@@ -1390,16 +1456,20 @@ static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
         fp.wait = sh.single ? 1 : 0;
         fp.block0 = part == 0 ? 0 : fp.gu_blocks;
         const unsigned blocks = sh.single ? (unsigned)fp.gu_blocks + dn_blocks : part == 0 ? (unsigned)fp.gu_blocks : dn_blocks;
-        if (sh.big && sh.kwd == 1)
-            rc = launch_padded<1, true, WF>(fp, blocks, st);
+        if (sh.big == 2 && sh.kwd == 1)
+            rc = launch_padded<1, 2, WF>(fp, blocks, st);
+        else if (sh.big == 2)
+            rc = launch_padded<2, 2, WF>(fp, blocks, st);
+        else if (sh.big && sh.kwd == 1)
+            rc = launch_padded<1, 1, WF>(fp, blocks, st);
         else if (sh.big)
-            rc = launch_padded<2, true, WF>(fp, blocks, st);
+            rc = launch_padded<2, 1, WF>(fp, blocks, st);
         else if (sh.kwd == 4)
-            rc = launch_padded<4, false, WF>(fp, blocks, st);
+            rc = launch_padded<4, 0, WF>(fp, blocks, st);
         else if (sh.kwd == 2)
-            rc = launch_padded<2, false, WF>(fp, blocks, st);
+            rc = launch_padded<2, 0, WF>(fp, blocks, st);
         else
-            rc = launch_padded<1, false, WF>(fp, blocks, st);
+            rc = launch_padded<1, 0, WF>(fp, blocks, st);
         if (rc == LYNX_OK) rc = check_launch("lynx_moe_ffn(gate/up, down)");
     }
     return rc;
@@ -1485,7 +1555,9 @@ int moe_ffn_validate(const void *x_bf16, const void *Wgu_packed, const void *Wd_
     if (!x_bf16 || !Wgu_packed || !Wd_packed || !idx || !gate || !offsets || !perm || !y || !workspace)
         return fail(LYNX_ERR_INVALID_ARG, "lynx_moe_ffn: null pointer");
     if (n_shared == 0) F_shared = 0;
+    // (counted in blocks of 128 tokens, with quantised weights too: at most 768 pairs of them, 1536 of 64 tokens)
     const int tok_block = T > kTokBlock ? kTokBlockBig : kTokBlock;
+    static_assert(2 * (kWsDoneWords - LYNX_MAX_N) <= kWsDoneSharedWords, "completion counters of the shared experts");
     if (LYNX_MAX_N + (long)n_shared * ((T + tok_block - 1) / tok_block) > kWsDoneWords)
         return fail(LYNX_ERR_UNSUPPORTED, "lynx_moe_ffn: too many shared experts for this batch size (n_shared=%d T=%d)",
                     n_shared, T);

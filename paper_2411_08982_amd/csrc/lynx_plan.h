@@ -24,7 +24,7 @@ namespace lynx {
 
 constexpr int kDirectMaxTokens = 16;         // experts with more tokens take the staged path
 constexpr int kTokBlock = 64;                // tokens per pass of the staged path (batches of up to 64 tokens)
-constexpr int kTokBlockBig = 128;            // the same in the kernels launched for larger batches
+constexpr int kTokBlockBig = 128;            // the same in the bf16 kernels launched for larger batches
 
 // What the host knows of the FFN launch when the plan is built.
 struct PlanShape {
@@ -33,6 +33,7 @@ struct PlanShape {
     int tok_block;   // tokens per block of an expert on the staged path
     int dn_cap;      // down items the grid is sized for: the device takes the fewest units per item that fit it
     int dn_m_max;    // most units per down item
+    int shared_pairs;   // (shared expert, token block) pairs: completion counters to clear
 };
 
 constexpr int kPlanB = 0, kPlanM = 1, kPlanNa = 2;   // words of the header

@@ -1058,6 +1058,7 @@ int routing_fused(const uint16_t *x, const float *Wr, const float *bias, int T, 
     ZeroList z;
     z.n = 0;
     add_zero(z, ws + kWsDone, kWsDoneWords + 16);   // the FFN's completion counters and flags
+    if (ps.shared_pairs > 0) add_zero(z, ws + kWsDoneShared, ps.shared_pairs);
     if (T > kSmallT) {   // the logits kernel clears what the multi-workgroup kernels accumulate into
         add_zero(z, ws + kWsTickets, 16);
         add_zero(z, ws + kWsActive, N);

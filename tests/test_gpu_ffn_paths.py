@@ -1,0 +1,91 @@
+"""The expert FFN with the tokens of every expert prescribed, so that each path of the weight-streaming kernel is met at the
+edges of its tiles: token counts around the column tiles and token blocks, row counts and contraction lengths that leave
+remainders, in the three weight formats, against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+import workloads as wl
+from gpu_util import dev, host, row_rel_err, to_bf16_dev
+
+pytestmark = pytest.mark.gpu
+
+Y_TOL = 1e-2   # per token row: bf16 operands, fp32 sums, the intermediate vector rounded to bf16 (2^-9 per element)
+
+
+@pytest.fixture(scope="module")
+def L():
+    assert torch.cuda.is_available()
+    import paper_2411_08982_amd as L
+    L.lib()
+    return L
+
+
+def run_case(L, fmt, T, counts, H, F, S, Fs):
+    print(f"ffn paths {fmt} T={T} counts={counts} H={H} F={F} shared={S}x{Fs}", flush=True)
+    N = k = len(counts)
+    rng = np.random.default_rng([T, H, F, sum(counts)])
+    idx = np.full((T, k), -1, np.int32)      # column e: the tokens of expert e; -1 is a skipped pair
+    for e, c in enumerate(counts):
+        idx[rng.permutation(T)[:c], e] = e
+    gate = rng.uniform(0.1, 1.0, (T, k)).astype(np.float32)
+    every = np.tile(np.arange(N, dtype=np.int32), (T, 1))   # the oracle takes no skipped pairs: weight 0 instead
+    gate_ref = np.where(idx >= 0, gate, 0.0)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
+    mk = lambda *shape: wl.f32_to_bf16_bits((rng.standard_normal(shape) * 0.05).astype(np.float32))
+    W = [mk(N, F, H), mk(N, F, H), mk(N, H, F)]
+    Sw = [mk(S, Fs, H), mk(S, Fs, H), mk(S, H, Fs)] if S else None
+    idx_d = dev(idx)
+    p = L.lynx_permute(idx_d, N)
+    ws = L.new_workspace(T, H, F, N, k, S, Fs)
+    ws.fill_(0xFF)
+    y = torch.full((T, H), float("nan"), dtype=torch.float32, device="cuda")
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    if fmt == "bf16":
+        ref = oracle.moe_ffn(x, *W, every, gate_ref, *(Sw or ()))
+        Sgu, Sdp = L.lynx_pack_weights(*map(to_bf16_dev, Sw)) if S else (None, None)
+        L.lynx_moe_ffn(to_bf16_dev(x), *L.lynx_pack_weights(*map(to_bf16_dev, W)), idx_d, dev(gate), p, N, F, Sgu, Sdp, S, Fs,
+                       workspace=ws, y=y, status=status)
+    else:
+        quantize, ffn, oq, offn = {
+            "fp8": (L.lynx_quantize_weights_fp8, L.lynx_moe_ffn_fp8, oracle.quantize_rows_e4m3, oracle.moe_ffn_q8),
+            "fp4": (L.lynx_quantize_weights_fp4, L.lynx_moe_ffn_fp4, oracle.quantize_mxfp4, oracle.moe_ffn_q4),
+        }[fmt]
+        codes, scales = zip(*(oq(w) for w in W))
+        extra = ()
+        if S:
+            scodes, sscales = zip(*(oq(w) for w in Sw))
+            extra = (*scodes, *sscales)
+        ref = offn(x, *codes, *scales, every, gate_ref, *extra)
+        ffn(to_bf16_dev(x), quantize(*map(to_bf16_dev, W)), idx_d, dev(gate), p, N, F,
+            quantize(*map(to_bf16_dev, Sw)) if S else None, S, Fs, workspace=ws, y=y, status=status)
+    torch.cuda.synchronize()
+    got = host(y)
+    assert host(status)[0] == 0
+    assert np.all(np.isfinite(got))
+    err = row_rel_err(got, ref).max()
+    assert err <= Y_TOL, f"max row error {err:.3e}"
+
+
+# More than 64 tokens.  With more than 64 per expert on average a gate/up unit is 128 rows and a wave owns two row tiles of
+# it: row counts of 128 n + 32, 64 and 96 leave it a partly filled last unit.  Contraction lengths that end inside a chunk of
+# the token stage and inside a turn of the weight ring.
+LARGE = [
+    # T, tokens per expert, H, F, shared experts, their width
+    (65, (65, 64, 63, 33, 1), 256, 128, 0, 0),
+    (130, (130, 129, 128, 127, 17), 384, 640, 0, 0),       # blocks of one expert: a full one and a remainder of 1 or 2
+    (300, (300, 256, 257, 16, 32), 128, 384, 1, 256),      # 3 blocks (5 of 64); a shared expert over all tokens
+    (97, (97, 0, 81, 5, 49), 512, 256, 1, 768),            # an expert that is not invoked; a wide shared expert (K slices)
+    (80, (3, 20, 0, 33, 65), 640, 384, 0, 0),              # few tokens per expert: units of 64 rows
+]
+RAGGED = {"bf16": (32, 96), "fp8": (64, 64), "fp4": (0, 0)}   # added to H and F: the format's smallest steps
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "fp4"])
+@pytest.mark.parametrize("case", LARGE)
+def test_large_batches(L, fmt, case):
+    T, counts, H, F, S, Fs = case
+    dH, dF = RAGGED[fmt]
+    run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs)
