@@ -38,7 +38,7 @@ constexpr int kPF = 8;                       // staged path: weight tiles in fli
 #define LYNX_PFD 8
 #endif
 constexpr int kPFD = LYNX_PFD;               // direct path: the same (most; see DirectDepth for the depth per format)
-constexpr int kStageBytes = 2 * 18432;       // two LDS buffers for the staged token tile
+constexpr int kStageBytes = 2 * (32768 + 16 * 16 * 4);   // two LDS buffers for token rows: 32 KiB and 16 bytes per row (and K slice)
 // LDS for the staged token tile of passes of up to `tokens` tokens: 64 as above, else 4 k-steps double-buffered
 constexpr int stage_bytes(int tokens) { return tokens <= 64 ? kStageBytes : 2 * tokens * (4 * 64 + 16); }
 
@@ -470,18 +470,11 @@ __device__ __forceinline__ void decode_tile(uint4 w, float scale, bf16x8 (&a)[1 
     }
 }
 
-// Tiles in flight per wave and stream on the direct path.  MXFP4 tiles carry four k-steps, so the token
-// fragments that travel with a slot are 64 bytes per lane, twice the slot's weights: four slots keep the ring
-// inside the register file (measured: 3 and 4 equal, 5 and more spill and are slower; an MXFP4 launch at these
-// sizes is short enough that the fixed part of a launch weighs more than the depth of the ring).
+// Weight tiles in flight per wave and stream on the direct path (twice as many: equal or slower for every format, spills
+// with bf16; half: 1-8 % slower).  A chunk of the token stage has to hold whole turns of the ring.
 template <int WF>
 struct DirectDepth {
     static constexpr int value = WF == 2 ? 4 : kPFD;
-};
-
-struct WeightRing {
-    uint4 w0[kPFD], w1[kPFD];
-    uint2 sq[kPFD];      // MXFP4: the scale exponents of both streams (see the layout above)
 };
 
 // Where a wave of the direct path streams from: needs the expert, not its tokens.
@@ -489,11 +482,22 @@ struct DirectPlan {
     const uint4 *Wb;     // the wave's first weight tile (the same for all lanes)
     const uint2 *Sl;     // MXFP4: this lane's scale dwords of the wave's row group, k-tile group 0
     int step, second;    // uint4 strides: next k-step, second stream
-    int kb, n;           // first k-step and k-steps of this wave
-    int kt0;             // first k-tile actually read (kb, or 0 for a wave without work)
+    int n;               // k-tiles of this wave
+    int kt0;             // first k-tile actually read (0 for a wave without work)
     int rt;              // first 16-row tile
     bool rows_ok;
 };
+
+template <int WF>
+struct WeightRing {
+    static constexpr int D = DirectDepth<WF>::value;
+    uint4 w0[D], w1[D];
+    uint2 sq[D];   // MXFP4: the scale exponents of both streams (see the layout above)
+};
+
+// k-tiles per K slice of the item (the last slices may hold fewer, or none)
+template <int KW>
+__device__ __forceinline__ int slice_tiles(const WorkItem &w) { return (w.ksteps + KW - 1) / KW; }
 
 template <bool DUAL, int KW, int WF>
 __device__ __forceinline__ DirectPlan plan_direct(const WorkItem &w)
@@ -506,15 +510,14 @@ __device__ __forceinline__ DirectPlan plan_direct(const WorkItem &w)
     const int grp = w.tile * RW + rw;                  // row group of this wave
     d.rt = DUAL ? grp : 2 * grp;
     d.rows_ok = d.rt * 16 < w.R;                       // (down: R/16 is even, so the second tile exists too)
-    const int per = (w.ksteps + KW - 1) / KW;
-    d.kb = w.kbeg + kw * per;
-    d.n = min(w.kbeg + w.ksteps, d.kb + per) - d.kb;
+    const int per = slice_tiles<KW>(w);
+    const int kb = w.kbeg + kw * per;
+    d.n = max(min(w.kbeg + w.ksteps, kb + per) - kb, 0);
     const int rtc = d.rows_ok ? d.rt : 0;              // waves past the last row read tile 0 and store nothing
-    const int kbc = d.n > 0 ? d.kb : 0;
-    d.kt0 = kbc;
+    d.kt0 = d.n > 0 ? kb : 0;
     d.step = DUAL ? 2 * kWave : kWave;
     d.second = DUAL ? kWave : KT * kWave;
-    d.Wb = w.W + ((size_t)rtc * KT + kbc) * d.step;
+    d.Wb = w.W + ((size_t)rtc * KT + d.kt0) * d.step;
     d.Sl = nullptr;
     if (WF == 2)
         d.Sl = reinterpret_cast<const uint2 *>(w.sc) + (size_t)(d.rows_ok ? grp : 0) * mx_kt4(w.K) * kWave + lane_id();
@@ -527,145 +530,166 @@ __device__ __forceinline__ uint2 ring_load_scales(const uint2 *__restrict__ base
     return base[index];
 }
 
+// Tile s of the wave's run into slot u; past the end of the run nothing is fetched and the tile reads as zero.
 template <int WF>
-__device__ __forceinline__ void prefetch_weights(const DirectPlan &d, WeightRing &r)
+__device__ __forceinline__ void load_slot(const DirectPlan &d, BufferRsrc rw, WeightRing<WF> &r, int u, int s)
 {
-    constexpr int D = DirectDepth<WF>::value;
-    const int last = max(d.n, 1) - 1;
-    const BufferRsrc rw = weights_resource(d.Wb);
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const int s = min(j, last);
-        r.w0[j] = ring_load_weights(rw, j * d.step, j <= last);
-        r.w1[j] = ring_load_weights(rw, j * d.step + d.second, j <= last);
-        if (WF == 2) r.sq[j] = ring_load_scales(d.Sl, ((d.kt0 + s) >> 2) * kWave);
-    }
+    r.w0[u] = ring_load_weights(rw, s * d.step, s < d.n);
+    r.w1[u] = ring_load_weights(rw, s * d.step + d.second, s < d.n);
+    if (WF == 2) r.sq[u] = ring_load_scales(d.Sl, ((d.kt0 + max(min(s, d.n - 1), 0)) >> 2) * kWave);
 }
 
-// The ring arrives with its first turn of weight tiles already requested (prefetch_weights).
-template <int NT, int WF>
-__device__ __forceinline__ void stream_direct(const DirectPlan &d, WeightRing &r, BufferRsrc rs, const unsigned (&boff)[NT],
-                                              f32x4 (&acc0)[NT], f32x4 (&acc1)[NT])
+template <int WF>
+__device__ __forceinline__ void prefetch_weights(const DirectPlan &d, WeightRing<WF> &r)
 {
-    constexpr int D = DirectDepth<WF>::value;
-    constexpr int BP = 1 << WF;              // 16-byte pieces of a token row per lane and weight tile = its k-steps
-    constexpr int BS = TileCols<WF>::value / 8;   // uint4 units between the pieces of consecutive tiles
     const BufferRsrc rw = weights_resource(d.Wb);
-    const int step = d.step, second = d.second;
-    const int n = d.rows_ok ? d.n : 0;     // k-steps whose products count
-    const int last = max(d.n, 1) - 1;
-    uint4 bb[D][NT][BP];
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int h = 0; h < BP; ++h) bb[j][nt][h] = ring_load_b(rs, j <= last ? boff[nt] : kNoToken, j * BS + h);
-    }
-    // One turn of the ring: consume the D slots in order, refilling each right after its last read.
-    auto turn = [&](int s0) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            const int s = s0 + u;
-            const bool live = s < n;
-            // consume slot u ...
-            bf16x8 a0[BP], a1[BP];
-            const int kt = d.kt0 + min(s, last);
-            decode_tile<WF>(sel4(live, r.w0[u]), WF == 2 ? mx_scale(r.sq[u].x, kt) : 1.0f, a0);
-            decode_tile<WF>(sel4(live, r.w1[u]), WF == 2 ? mx_scale(r.sq[u].y, kt) : 1.0f, a1);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int h = 0; h < BP; ++h) {
-                    const bf16x8 b = __builtin_bit_cast(bf16x8, bb[u][nt][h]);
-                    acc0[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[h], b, acc0[nt], 0, 0, 0);
-                    acc1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[h], b, acc1[nt], 0, 0, 0);
-                }
-            // ... then refill it (the scheduling fences keep the refill behind the last read of the slot,
-            // so that it can land in the same registers and the ring needs no copies)
-            __builtin_amdgcn_sched_barrier(0);
-            const int sn = s + D;          // refills past the end of the run fetch nothing
-            const bool more = sn <= last;
-            r.w0[u] = ring_load_weights(rw, sn * step, more);
-            r.w1[u] = ring_load_weights(rw, sn * step + second, more);
-            if (WF == 2) r.sq[u] = ring_load_scales(d.Sl, ((d.kt0 + min(sn, last)) >> 2) * kWave);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int h = 0; h < BP; ++h) bb[u][nt][h] = ring_load_b(rs, more ? boff[nt] : kNoToken, sn * BS + h);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    // The first turn is peeled off the loop.  On entry the ring holds the weight loads of prefetch_weights
-    // followed by the token loads above; from the first turn on, the loads of a slot are interleaved
-    // (weights, weights, tokens).  The compiler inserts the waits for the oldest load from what may be
-    // outstanding on ANY path into a block: with the first turn inside the loop it would have to assume the
-    // entry order in every turn, and would wait until a third of the ring is left before the first slot.
-    if (n > 0) {
-        turn(0);
-        for (int s0 = D; s0 < n; s0 += D) turn(s0);
-    }
+    for (int j = 0; j < DirectDepth<WF>::value; ++j) load_slot<WF>(d, rw, r, j, j);
 }
 
-// One expert with <= 16*NT tokens: the four waves are RW row groups x KW slices of K; the slices are
-// summed through LDS at the end.  A row group is one 16-row tile of gate and up (gate/up) or two
-// consecutive 16-row tiles (down), so that every token fragment loaded feeds two MFMAs.
-// The two halves of one row unit on the direct path.  direct_stream: the wave's products over its slice of K (the
-// ring arrives with its first turn of weight tiles requested).  direct_finish: the K slices are summed through LDS and
-// the results stored.  Between the two the ring's registers are free, so the caller requests the next unit's first
-// tiles there: they are in flight while this unit's sums are exchanged and written.
-// ro / orow: B row (element offset) and output row of this lane's token column, the same for every unit of an item.
-template <int NT, int KW, int WF>
-__device__ __forceinline__ void direct_stream(const WorkItem &w, const DirectPlan &d, WeightRing &ring, const int (&ro)[NT],
-                                              f32x4 (&acc0)[NT], f32x4 (&acc1)[NT])
+// Direct path: experts with at most 16 tokens.  Bound by the weight stream (a plain read runs at 7.1 TB/s) and, in short
+// launches, by the latency of its chain of loads.  The workgroup's waves are RW row groups x KW slices of K (a row group is
+// one 16-row tile of gate and up, or two consecutive 16-row tiles of down, so that every token fragment feeds two MFMAs);
+// the slices are summed through LDS at the end.
+//
+// The expert's token rows are staged in LDS, as many columns at a time as fit 32 KiB (twice, double buffered): all of them
+// at once for most shapes, and then no barrier interrupts the stream.  (They used to travel with the weights through the
+// same in-order queue: with 4-bit weights the fragments of a tile are 64 bytes per lane against the tile's 16, and the
+// ring's registers held them too.  MXFP4, us per FFN call: Mixtral shapes 16 tokens 157 -> 128, 8 tokens 129 -> 112, 1 token
+// 49 -> 43; FP8, Mixtral shapes 16 tokens 237 -> 228; bf16 within 1 %.)  R = the token count rounded up to a power of two: R rows of 512 / (KW * R) k-steps per
+// slice; the other lanes of a fragment read a row again, and their results are never stored.
+template <int KW>
+struct TokenStage {
+    int lr, lk;          // log2 of the rows R, of the k-steps (32 columns) per chunk
+    int rowb;            // bytes per row (+16: conflict-free 16-byte reads)
+    __device__ __forceinline__ TokenStage(int te)
+    {
+        lr = te <= 1 ? 0 : 32 - __clz(te - 1);
+        lk = 9 - (KW == 4 ? 2 : KW == 2 ? 1 : 0) - lr;
+        rowb = (64 << lk) + 16;
+    }
+    __device__ __forceinline__ int slice_bytes() const { return rowb << lr; }
+    __device__ __forceinline__ int buffer_bytes() const { return KW * slice_bytes(); }
+};
+constexpr int kStagePieces = 32 * 1024 / 16 / kFfnThreads;   // 16-byte pieces per thread and chunk
+
+// Chunk c of the token rows into registers (ro: element offset of the row of token lane % 16, -1 = none); pieces of rows
+// without a token or past the end of the slice arrive as zero.
+template <int KW, int WF>
+__device__ __forceinline__ void load_tokens(const WorkItem &w, const TokenStage<KW> &ts, BufferRsrc rb, int ro, int c,
+                                            uint4 (&xr)[kStagePieces])
 {
     constexpr int KC = TileCols<WF>::value;
-    const int lane = lane_id();
-    const int kbc = d.n > 0 ? d.kb : 0;
-    unsigned boff[NT];
+    const int per = slice_tiles<KW>(w);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)   // columns without a token fetch nothing and read as zero; their results are never stored
-        boff[nt] = ro[nt] < 0 ? kNoToken : 2u * ((unsigned)ro[nt] + (unsigned)kbc * KC + (unsigned)(lane >> 4) * (KC / 4));
-    clear_acc<NT>(acc0, acc1);
-    stream_direct<NT, WF>(d, ring, token_rows_resource(w.B), boff, acc0, acc1);
+    for (int i = 0; i < kStagePieces; ++i) {
+        const int q = threadIdx.x + kFfnThreads * i;             // [slice][row][piece]
+        const int pc = q & ((4 << ts.lk) - 1), row = (q >> (ts.lk + 2)) & ((1 << ts.lr) - 1), kw = q >> (ts.lk + 2 + ts.lr);
+        const int col = ((c << ts.lk) * 32) + pc * 8;            // column inside the slice
+        const int tiles = min(per, w.ksteps - kw * per);         // of the slice
+        const int r = __shfl(ro, row, kWave);
+        xr[i] = ring_load_b(rb, (r >= 0 && col < tiles * KC) ? 2u * (unsigned)(r + (w.kbeg + kw * per) * KC + col) : kNoToken, 0);
+    }
+}
+template <int KW>
+__device__ __forceinline__ void store_tokens(const TokenStage<KW> &ts, int c, const uint4 (&xr)[kStagePieces], char *stage)
+{
+    char *buf = stage + (c & 1) * ts.buffer_bytes();
+#pragma unroll
+    for (int i = 0; i < kStagePieces; ++i) {
+        const int q = threadIdx.x + kFfnThreads * i;
+        const int pc = q & ((4 << ts.lk) - 1), row = q >> (ts.lk + 2);   // (rows of all slices in a row)
+        *reinterpret_cast<uint4 *>(buf + row * ts.rowb + pc * 16) = xr[i];
+    }
 }
 
-template <bool DUAL, int NT, int KW, int WF>
-__device__ __forceinline__ void direct_finish(const WorkItem &w, const DirectPlan &d, const int (&orow)[NT], f32x4 (&acc0)[NT],
-                                              f32x4 (&acc1)[NT], float *red)
+// The wave's products over its slice of K.  The ring arrives with its first turn of weight tiles requested and the stage
+// with the first chunk of token rows.  Every wave makes the same number of turns.
+template <int KW, int WF>
+__device__ __forceinline__ void stream_direct(const WorkItem &w, const DirectPlan &d, const TokenStage<KW> &ts,
+                                              WeightRing<WF> &r, BufferRsrc rb, int ro, char *stage, f32x4 &acc0, f32x4 &acc1)
 {
-    constexpr int NACC = NT * 2;
+    constexpr int D = DirectDepth<WF>::value;
+    constexpr int TS = 1 << WF;              // k-steps per weight tile
+    const BufferRsrc rw = weights_resource(d.Wb);
+    const int lane = lane_id();
+    const int per = slice_tiles<KW>(w);
+    const int C = (1 << ts.lk) / TS;         // tiles per chunk: a multiple of D
+    const int chunks = (per + C - 1) / C;
+    const char *base = stage + (wave_id() % KW) * ts.slice_bytes() + (lane & ((1 << ts.lr) - 1) & 15) * ts.rowb +
+                       (lane >> 4) * (16 << WF);
+    for (int c = 0; c < chunks; ++c) {
+        uint4 xr[kStagePieces];
+        const bool more = c + 1 < chunks;
+        if (more) load_tokens<KW, WF>(w, ts, rb, ro, c + 1, xr);
+        const char *buf = base + (c & 1) * ts.buffer_bytes();
+        const int end = min(per, (c + 1) * C);
+        for (int s0 = c * C; s0 < end; s0 += D, buf += D * TS * 64) {
+            bf16x8 b[2][TS];
+#pragma unroll
+            for (int h = 0; h < TS; ++h) b[0][h] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + 16 * h));
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                const int s = s0 + u;
+                if (u + 1 < D) {
+#pragma unroll
+                    for (int h = 0; h < TS; ++h)
+                        b[(u + 1) & 1][h] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + (u + 1) * TS * 64 + 16 * h));
+                }
+                bf16x8 a0[TS], a1[TS];
+                const int kt = d.kt0 + max(min(s, d.n - 1), 0);
+                decode_tile<WF>(r.w0[u], WF == 2 ? mx_scale(r.sq[u].x, kt) : 1.0f, a0);
+                decode_tile<WF>(r.w1[u], WF == 2 ? mx_scale(r.sq[u].y, kt) : 1.0f, a1);
+#pragma unroll
+                for (int h = 0; h < TS; ++h) {
+                    acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[h], b[u & 1][h], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[h], b[u & 1][h], acc1, 0, 0, 0);
+                }
+                // ... then refill the slot (the scheduling fences keep the refill behind the last read of the slot,
+                // so that it can land in the same registers and the ring needs no copies)
+                __builtin_amdgcn_sched_barrier(0);
+                load_slot<WF>(d, rw, r, u, s + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (more) {
+            store_tokens<KW>(ts, c + 1, xr, stage);
+            __syncthreads();
+        }
+    }
+}
+
+// The K slices are summed through LDS and the results stored (orow: output row of this lane's token column).  The stage has
+// been read by then: a barrier first.
+template <bool DUAL, int KW, int WF>
+__device__ __forceinline__ void direct_finish(const WorkItem &w, const DirectPlan &d, int orow, f32x4 acc0, f32x4 acc1, char *stage)
+{
     const int lane = lane_id(), wv = wave_id();
     const int rw = wv / KW, kw = wv % KW;
     if (KW > 1) {
-        f32x4 *r4 = reinterpret_cast<f32x4 *>(red);   // [rw][kw-1][NACC][lane]
+        f32x4 *r4 = reinterpret_cast<f32x4 *>(stage) + (size_t)rw * (KW - 1) * 2 * kWave + lane;   // [rw][kw-1][2][lane]
+        __syncthreads();
         if (kw > 0) {
-            f32x4 *dst = r4 + ((size_t)(rw * (KW - 1) + (kw - 1)) * NACC) * kWave + lane;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                dst[(size_t)nt * kWave] = acc0[nt];
-                dst[(size_t)(NT + nt) * kWave] = acc1[nt];
-            }
+            r4[(size_t)(kw - 1) * 2 * kWave] = acc0;
+            r4[(size_t)(kw - 1) * 2 * kWave + kWave] = acc1;
         }
         __syncthreads();
         if (kw == 0) {
 #pragma unroll
-            for (int j = 1; j < KW; ++j) {
-                const f32x4 *src = r4 + ((size_t)(rw * (KW - 1) + (j - 1)) * NACC) * kWave + lane;
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    acc0[nt] += src[(size_t)nt * kWave];
-                    acc1[nt] += src[(size_t)(NT + nt) * kWave];
-                }
+            for (int j = 0; j < KW - 1; ++j) {
+                acc0 += r4[(size_t)j * 2 * kWave];
+                acc1 += r4[(size_t)j * 2 * kWave + kWave];
             }
         }
     }
     if (kw == 0 && d.rows_ok) {
+        const f32x4 a0[1] = {acc0}, a1[1] = {acc1};
+        const int orows[1] = {orow};
         if (DUAL) {
-            epilogue<true, NT, WF>(acc0, acc1, w.out, w.ldo, d.rt * 16, orow, w.sc, w.R);
+            epilogue<true, 1, WF>(a0, a1, w.out, w.ldo, d.rt * 16, orows, w.sc, w.R);
         } else {
-            epilogue<false, NT, WF>(acc0, acc0, w.out, w.ldo, d.rt * 16, orow, w.sc, w.R);
-            epilogue<false, NT, WF>(acc1, acc1, w.out, w.ldo, d.rt * 16 + 16, orow, w.sc, w.R);
+            epilogue<false, 1, WF>(a0, a0, w.out, w.ldo, d.rt * 16, orows, w.sc, w.R);
+            epilogue<false, 1, WF>(a1, a1, w.out, w.ldo, d.rt * 16 + 16, orows, w.sc, w.R);
         }
     }
 }
@@ -888,7 +912,7 @@ struct FfnParams {
     int wait;         // 0: the down workgroups of this launch follow a finished gate/up launch and do not wait
     int spin_limit;   // polls of a completion counter before a down workgroup gives up
     int target_bias;  // added to the count a down workgroup waits for (0; tests of the give-up path set it)
-    int32_t *done;    // [LYNX_MAX_N] routed experts, then [n_shared * token blocks]; zero before the launch
+    int32_t *done;    // completion counters (kWsDone), zero before the launch
     int32_t *flags;
 };
 
@@ -944,26 +968,36 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
         __syncthreads();
     };
     if (w.te_all <= kDirectMaxTokens) {
-        // Direct path.  The weight stream starts before anything else is waited for, and the next unit's first tiles
-        // are requested before this unit's results are exchanged and stored.
+        // Direct path.  The weight stream starts before h is waited for, and the next unit's first tiles are requested
+        // before this unit's results are exchanged and stored.
+        const TokenStage<KW> ts(w.Te);
+        const BufferRsrc rb = token_rows_resource(w.B);
         DirectPlan plan = plan_direct<DUAL, KW, WF>(w);
-        WeightRing ring;
+        WeightRing<WF> ring;
+        int ro, orow;
+        token_rows_direct<DUAL>(p, w, ro, orow);
+        uint4 xr[kStagePieces];
+        if (DUAL) load_tokens<KW, WF>(w, ts, rb, ro, 0, xr);   // (ahead of the weights: memory returns in order)
         prefetch_weights<WF>(plan, ring);
-        int ro[1], orow[1];
-        token_rows_direct<DUAL>(p, w, ro[0], orow[0]);
         wait_for_h();
         LYNX_TS(2);
+        if (!DUAL) load_tokens<KW, WF>(w, ts, rb, ro, 0, xr);
         for (int un = 0; un < units; ++un) {
-            f32x4 acc0[1], acc1[1];
-            direct_stream<1, KW, WF>(w, plan, ring, ro, acc0, acc1);
+            if (un > 0) {
+                __syncthreads();   // the stage has been read
+                load_tokens<KW, WF>(w, ts, rb, ro, 0, xr);
+            }
+            store_tokens<KW>(ts, 0, xr, stage);
+            __syncthreads();
+            f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+            stream_direct<KW, WF>(w, plan, ts, ring, rb, ro, stage, acc0, acc1);
             const DirectPlan done = plan;
             if (un + 1 < units) {
                 w.tile = unit0 + un + 1;
                 plan = plan_direct<DUAL, KW, WF>(w);
                 prefetch_weights<WF>(plan, ring);
             }
-            direct_finish<DUAL, 1, KW, WF>(w, done, orow, acc0, acc1, reinterpret_cast<float *>(stage));
-            if (KW > 1 && un + 1 < units) __syncthreads();   // the next unit reuses the K-slice sums in LDS
+            direct_finish<DUAL, KW, WF>(w, done, orow, acc0, acc1, stage);
         }
     } else {
         wait_for_h();
@@ -1308,6 +1342,10 @@ __global__ __launch_bounds__(256) void quantize_fp4_kernel(const uint16_t *__res
     }
 }
 
+// Four K slices with quantised weights need experts of at most 8 tokens: with 16 rows per slice the token stage holds less
+// than a turn of the weight ring (see TokenStage).
+static int max_experts_kw4(int T, int bits_per_weight) { return bits_per_weight < 16 && T > 8 ? 0 : 8; }
+
 // How many of a workgroup's four waves split the contraction dimension (the rest split rows).  Long
 // per-wave streams amortise the fill and drain of the prefetch ring, so K is only split when the
 // batch cannot invoke enough experts to give every CU several waves otherwise.
@@ -1330,7 +1368,7 @@ static int pick_k_waves(int K, bool dual, int T, int max_experts, int bits_per_w
     // more experts two ways (64-row workgroups: 4-5 % faster than 128-row ones for DeepSeek-V2-Lite and
     // Qwen1.5-MoE shapes), unless the streams would get too short.
     const long group_bytes = (long)16 * K * 2 * bits_per_weight / 8;      // weight bytes behind one row group
-    int kw = max_experts <= 8 ? 4 : 2;
+    int kw = max_experts <= max_experts_kw4(T, bits_per_weight) ? 4 : 2;
     while (kw > 1 && group_bytes / kw < 32 * 1024) kw >>= 1;              // keep at least 32 KiB per wave
     return kw;
 }
@@ -1364,7 +1402,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     const int max_experts = (int)min((long)N, (long)T * k) + n_shared;
     s.kwd = pick_k_waves(F, false, T, max_experts, 16 >> format);
     const int forced = g_tune.dn_kw.load();
-    if (forced == 1 || forced == 2 || (forced == 4 && T <= kDirectMaxTokens)) s.kwd = forced;
+    if (forced == 1 || forced == 2 || (forced == 4 && T <= (format ? 8 : kDirectMaxTokens))) s.kwd = forced;
     // Gate/up units of 128 rows when the experts hold more than 64 tokens on average: fewer, longer workgroups that stage
     // the tokens half as often (Mixtral shapes, 1000 tokens: 1156 -> 1126 us; DeepSeek-V2-Lite shapes, 1000: 343 -> 333).
     // With fewer tokens the weight stream is the bound and the finer units fill the chip more evenly (Mixtral shapes, 128

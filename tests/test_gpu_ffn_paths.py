@@ -89,3 +89,27 @@ def test_large_batches(L, fmt, case):
     T, counts, H, F, S, Fs = case
     dH, dF = RAGGED[fmt]
     run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs)
+
+
+# At most 16 tokens per expert: 1, 2, 4, 8 or 16 token rows in LDS, as many columns at a time as fit (contractions that need
+# one chunk, several, and a remainder), K in one, two and four slices with short or empty last ones, a shared expert beside it.
+SMALL = [
+    # T, tokens per expert, H, F, shared experts, their width
+    (1, (1, 0, 1), 128, 256, 0, 0),
+    (2, (2, 1), 2048, 384, 1, 128),
+    (5, (5, 3, 1, 0, 2), 640, 2048, 0, 0),
+    (8, (8, 7, 1, 3), 8192, 256, 1, 640),                      # gate/up in several chunks
+    (8, (8, 4, 1, 2), 256, 16384, 0, 0),                       # down: four slices, several chunks each
+    (11, (11, 9, 8, 2, 1, 4, 0, 6, 3, 5, 7), 1152, 1024, 2, 128),
+    (16, (16, 15, 9, 1), 2176, 4096, 0, 0),
+    (23, (16, 17, 1, 23, 8), 4096, 640, 0, 0),                 # both paths in one launch
+    (90, (16, 13, 66, 3, 90, 81, 80), 384, 256, 0, 0),         # the same in the kernel for large batches, units of 128 rows
+]
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "fp4"])
+@pytest.mark.parametrize("case", SMALL)
+def test_few_tokens_per_expert(L, fmt, case):
+    T, counts, H, F, S, Fs = case
+    dH, dF = RAGGED[fmt]
+    run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs)
