@@ -183,15 +183,29 @@ constexpr int kWsTickets = 0;                              // 16 words
 constexpr int kWsOrder = 16;                               // LYNX_MAX_N words
 constexpr int kWsActive = kWsOrder + LYNX_MAX_N;           // LYNX_MAX_N words
 constexpr int kWsMember = kWsActive + LYNX_MAX_N;          // LYNX_MAX_N * LYNX_MAX_T/32 words
-constexpr int kWsDone = kWsMember + LYNX_MAX_N * (LYNX_MAX_T / 32);   // FFN: gate/up completion counters
-constexpr int kWsDoneWords = 1024;                         // routed experts (LYNX_MAX_N; the rest is a limit: see moe_ffn_validate)
-constexpr int kWsFlags = kWsDone + kWsDoneWords;           // FFN: bit 0 = a bounded wait ran out
+constexpr int kWsOldDone = kWsMember + LYNX_MAX_N * (LYNX_MAX_T / 32);   // (1024 words free)
+constexpr int kWsFlags = kWsOldDone + 1024;               // FFN: bit 0 = a bounded wait ran out
 constexpr int kWsPlanHdr = kWsFlags + 16;                  // FFN work plan (lynx_plan.h): header, 16 words
 constexpr int kPlanMaxBlocks = 512;                        // most (expert, token block) pairs: LYNX_MAX_N + LYNX_MAX_T * LYNX_MAX_K / 128, rounded up
 constexpr int kWsPlanBlk = kWsPlanHdr + 16;                // one record of four words per (expert, token block) pair
 constexpr int kWsPlanPairs = kWsPlanBlk + 4 * kPlanMaxBlocks;   // 16 pair ids of 16 bits per block: 8 words each
-constexpr int kWsDoneShared = kWsPlanPairs + 8 * kPlanMaxBlocks;  // FFN: the same per (shared expert, token block) pair
+// FFN: gate/up completion counters, of the routed experts and of the (shared expert, token block) pairs.  Atomic adds and
+// polls of one cache line are served one after another at the memory side (about 15 ns each, from all XCDs), so the counters
+// are spread over lines: the routed ones at the widest stride that holds N (done_stride), the shared ones round the lines.
+// (All in one line, the last gate/up workgroup of a layer of 8 small experts was done at 7.5 us and its expert's down
+// workgroups saw it at 12 to 16; layer of 512 x 1024, 16 tokens 34.6 -> 28.5 us, DeepSeek-V2-Lite shapes, MXFP4, 16 tokens
+// 50.5 -> 43.5.)
+constexpr int kWsDone = (kWsPlanPairs + 8 * kPlanMaxBlocks + 31) / 32 * 32;
+constexpr int kWsDoneWords = 4096;
+constexpr int kWsDoneShared = kWsDone + kWsDoneWords;
 constexpr int kWsDoneSharedWords = 2048;
+__host__ __device__ __forceinline__ int done_stride(int N)
+{
+    int s = kWsDoneWords / 8;
+    while (s * N > kWsDoneWords) s >>= 1;
+    return s;   // N <= 8: 2 KiB apart, N = 256: 64 bytes
+}
+__host__ __device__ __forceinline__ int done_shared_slot(int pair) { return (pair % (kWsDoneSharedWords / 32)) * 32 + pair / (kWsDoneSharedWords / 32); }
 constexpr int kWsRoutingWords = kWsDoneShared + kWsDoneSharedWords;
 constexpr size_t kWsRoutingBytes = 98304;
 static_assert((size_t)kWsRoutingWords * 4 <= kWsRoutingBytes, "routing scratch does not fit its reservation");

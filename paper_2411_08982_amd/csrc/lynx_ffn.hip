@@ -923,7 +923,8 @@ constexpr int kSpinLimit = 1 << 17;   // polls of a counter (about a microsecond
 
 __device__ __forceinline__ int done_slot(const GemmParams &p, const WorkItem &w)
 {
-    return w.shared_s < 0 ? w.e : kWsDoneShared - kWsDone + w.shared_s * p.shared_tblocks + w.tok0 / p.tok_block;
+    return w.shared_s < 0 ? w.e * done_stride(p.N)
+                          : kWsDoneWords + done_shared_slot(w.shared_s * p.shared_tblocks + w.tok0 / p.tok_block);
 }
 
 // 16-row tiles per wave on the staged path.  Two in the large-batch kernels (gate/up, and down with undivided K): a token
@@ -1115,8 +1116,9 @@ __global__ __launch_bounds__(256) void plan_kernel(const int32_t *__restrict__ o
 {
     __shared__ int count[LYNX_MAX_N], offs[LYNX_MAX_N], blk0[LYNX_MAX_N];
     const int tid = threadIdx.x;
-    for (int i = tid; i < kWsDoneWords + 16; i += 256) ws[kWsDone + i] = 0;
-    for (int i = tid; i < ps.shared_pairs; i += 256) ws[kWsDoneShared + i] = 0;
+    const int clear = kWsDoneWords + (ps.shared_pairs > 0 ? kWsDoneSharedWords : 0);
+    for (int i = tid * 4; i < clear; i += 256 * 4) *reinterpret_cast<int4 *>(ws + kWsDone + i) = make_int4(0, 0, 0, 0);
+    if (tid < 16) ws[kWsFlags + tid] = 0;
     if (tid < N) {
         const int o0 = offsets[tid], o1 = offsets[tid + 1];
         const bool ok = o0 >= 0 && o1 > o0 && o1 <= P;
@@ -1595,8 +1597,9 @@ int moe_ffn_validate(const void *x_bf16, const void *Wgu_packed, const void *Wd_
     if (n_shared == 0) F_shared = 0;
     // (counted in blocks of 128 tokens, with quantised weights too: at most 768 pairs of them, 1536 of 64 tokens)
     const int tok_block = T > kTokBlock ? kTokBlockBig : kTokBlock;
-    static_assert(2 * (kWsDoneWords - LYNX_MAX_N) <= kWsDoneSharedWords, "completion counters of the shared experts");
-    if (LYNX_MAX_N + (long)n_shared * ((T + tok_block - 1) / tok_block) > kWsDoneWords)
+    constexpr int kMaxSharedPairs = 768;
+    static_assert(2 * kMaxSharedPairs <= kWsDoneSharedWords, "completion counters of the shared experts");
+    if ((long)n_shared * ((T + tok_block - 1) / tok_block) > kMaxSharedPairs)
         return fail(LYNX_ERR_UNSUPPORTED, "lynx_moe_ffn: too many shared experts for this batch size (n_shared=%d T=%d)",
                     n_shared, T);
     const Workspace ws = workspace_layout(T, H, F, k, n_shared, F_shared, shared_down_splits(F, n_shared, F_shared));

@@ -1057,8 +1057,8 @@ int routing_fused(const uint16_t *x, const float *Wr, const float *bias, int T, 
     int32_t *ws = reinterpret_cast<int32_t *>(workspace);
     ZeroList z;
     z.n = 0;
-    add_zero(z, ws + kWsDone, kWsDoneWords + 16);   // the FFN's completion counters and flags
-    if (ps.shared_pairs > 0) add_zero(z, ws + kWsDoneShared, ps.shared_pairs);
+    add_zero(z, ws + kWsDone, kWsDoneWords + (ps.shared_pairs > 0 ? kWsDoneSharedWords : 0));   // the FFN's completion counters
+    add_zero(z, ws + kWsFlags, 16);
     if (T > kSmallT) {   // the logits kernel clears what the multi-workgroup kernels accumulate into
         add_zero(z, ws + kWsTickets, 16);
         add_zero(z, ws + kWsActive, N);
