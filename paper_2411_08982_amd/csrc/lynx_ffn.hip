@@ -581,8 +581,11 @@ __device__ __forceinline__ void load_tokens(const WorkItem &w, const TokenStage<
 {
     constexpr int KC = TileCols<WF>::value;
     const int per = slice_tiles<KW>(w);
+    // (one token: up to 4096 columns are a quarter of the pieces)
+    const bool one = KW == 1 && ts.lr == 0 && (per << WF) * 4 <= kFfnThreads * kStagePieces / 4;
 #pragma unroll
     for (int i = 0; i < kStagePieces; ++i) {
+        if (i >= kStagePieces / 4 && one) break;
         const int q = threadIdx.x + kFfnThreads * i;             // [slice][row][piece]
         const int pc = q & ((4 << ts.lk) - 1), row = (q >> (ts.lk + 2)) & ((1 << ts.lr) - 1), kw = q >> (ts.lk + 2 + ts.lr);
         const int col = ((c << ts.lk) * 32) + pc * 8;            // column inside the slice
@@ -978,11 +981,10 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
         int ro, orow;
         token_rows_direct<DUAL>(p, w, ro, orow);
         uint4 xr[kStagePieces];
-        if (DUAL) load_tokens<KW, WF>(w, ts, rb, ro, 0, xr);   // (ahead of the weights: memory returns in order)
         prefetch_weights<WF>(plan, ring);
         wait_for_h();
         LYNX_TS(2);
-        if (!DUAL) load_tokens<KW, WF>(w, ts, rb, ro, 0, xr);
+        load_tokens<KW, WF>(w, ts, rb, ro, 0, xr);
         for (int un = 0; un < units; ++un) {
             if (un > 0) {
                 __syncthreads();   // the stage has been read
@@ -1344,10 +1346,6 @@ __global__ __launch_bounds__(256) void quantize_fp4_kernel(const uint16_t *__res
     }
 }
 
-// Four K slices with quantised weights need experts of at most 8 tokens: with 16 rows per slice the token stage holds less
-// than a turn of the weight ring (see TokenStage).
-static int max_experts_kw4(int T, int bits_per_weight) { return bits_per_weight < 16 && T > 8 ? 0 : 8; }
-
 // How many of a workgroup's four waves split the contraction dimension (the rest split rows).  Long
 // per-wave streams amortise the fill and drain of the prefetch ring, so K is only split when the
 // batch cannot invoke enough experts to give every CU several waves otherwise.
@@ -1370,7 +1368,9 @@ static int pick_k_waves(int K, bool dual, int T, int max_experts, int bits_per_w
     // more experts two ways (64-row workgroups: 4-5 % faster than 128-row ones for DeepSeek-V2-Lite and
     // Qwen1.5-MoE shapes), unless the streams would get too short.
     const long group_bytes = (long)16 * K * 2 * bits_per_weight / 8;      // weight bytes behind one row group
-    int kw = max_experts <= max_experts_kw4(T, bits_per_weight) ? 4 : 2;
+    // Four only up to 8 tokens: with 16 rows per slice the token stage holds no more than a turn of the weight ring (less
+    // with quantised weights, which cannot be; bf16, Mixtral shapes, 16 tokens: 427.7 us with four, 424.4 with two).
+    int kw = max_experts <= 8 && T <= 8 ? 4 : 2;
     while (kw > 1 && group_bytes / kw < 32 * 1024) kw >>= 1;              // keep at least 32 KiB per wave
     return kw;
 }
@@ -1404,7 +1404,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     const int max_experts = (int)min((long)N, (long)T * k) + n_shared;
     s.kwd = pick_k_waves(F, false, T, max_experts, 16 >> format);
     const int forced = g_tune.dn_kw.load();
-    if (forced == 1 || forced == 2 || (forced == 4 && T <= (format ? 8 : kDirectMaxTokens))) s.kwd = forced;
+    if (forced == 1 || forced == 2 || (forced == 4 && T <= 8)) s.kwd = forced;
     // Gate/up units of 128 rows when the experts hold more than 64 tokens on average: fewer, longer workgroups that stage
     // the tokens half as often (Mixtral shapes, 1000 tokens: 1156 -> 1126 us; DeepSeek-V2-Lite shapes, 1000: 343 -> 333).
     // With fewer tokens the weight stream is the bound and the finer units fill the chip more evenly (Mixtral shapes, 128
