@@ -1150,24 +1150,34 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
 {
     const int t = blockIdx.y;
     const int h = (blockIdx.x * 256 + threadIdx.x) * 4;
-    const bool failed = *flags != 0;
-    if (status && t == 0 && blockIdx.x == 0 && threadIdx.x == 0) *status = failed ? 1 : 0;
+    // Latency-bound: the rows' loads must not wait for the picks one by one, so eight are requested before the first is
+    // used.  A pick outside [0, N) has no row: its load is not made and it adds nothing.
+    const int32_t *it = idx + (size_t)t * k;
+    const float *gt = gate + (size_t)t * k;
+    const int failed_word = *flags;
+    if (status && t == 0 && blockIdx.x == 0 && threadIdx.x == 0) *status = failed_word != 0 ? 1 : 0;
     if (h >= H) return;
-    if (failed) {
-        const float q = __int_as_float(0x7fc00000);
-        *reinterpret_cast<float4 *>(y + (size_t)t * H + h) = make_float4(q, q, q, q);
-        return;
-    }
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j = 0; j < k; ++j) {
-        const int e = idx[(size_t)t * k + j];
-        if (e < 0 || e >= N) continue;
-        const float g = gate[(size_t)t * k + j];
-        const float4 v = *reinterpret_cast<const float4 *>(o + ((size_t)t * k + j) * H + h);
-        acc.x = fmaf(g, v.x, acc.x);
-        acc.y = fmaf(g, v.y, acc.y);
-        acc.z = fmaf(g, v.z, acc.z);
-        acc.w = fmaf(g, v.w, acc.w);
+    constexpr int U = 8;
+    for (int j0 = 0; j0 < k; j0 += U) {
+        float4 v[U];
+        float g[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = min(j0 + u, k - 1);
+            const int e = it[j];
+            const bool live = j0 + u < k && e >= 0 && e < N;
+            g[u] = live ? gt[j] : 0.f;
+            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (live) v[u] = *reinterpret_cast<const float4 *>(o + ((size_t)t * k + j) * H + h);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc.x = fmaf(g[u], v[u].x, acc.x);
+            acc.y = fmaf(g[u], v[u].y, acc.y);
+            acc.z = fmaf(g[u], v[u].z, acc.z);
+            acc.w = fmaf(g[u], v[u].w, acc.w);
+        }
     }
     for (int s = 0; s < n_shared; ++s) {
         const float4 v = *reinterpret_cast<const float4 *>(o + ((size_t)T * k + (size_t)s * T + t) * H + h);
@@ -1175,6 +1185,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
         acc.y += v.y;
         acc.z += v.z;
         acc.w += v.w;
+    }
+    if (failed_word != 0) {
+        const float q = __int_as_float(0x7fc00000);
+        acc = make_float4(q, q, q, q);
     }
     *reinterpret_cast<float4 *>(y + (size_t)t * H + h) = acc;
 }

@@ -65,7 +65,6 @@ __global__ __launch_bounds__(256) void logits_kernel(const uint16_t *__restrict_
 {
     __shared__ __attribute__((aligned(16))) uint16_t xs[kRouteTT * kRouteHC];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    zero_slices(z, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid, 256);
     const int t0 = blockIdx.x * kRouteTT;
     const int ntok = min(kRouteTT, T - t0);
     const int e = blockIdx.y * 4 + wave;
@@ -99,6 +98,8 @@ __global__ __launch_bounds__(256) void logits_kernel(const uint16_t *__restrict_
             if (tt < ntok) v = *reinterpret_cast<const uint4 *>(x + (size_t)(t0 + tt) * H + h0 + pc * 8);
             *reinterpret_cast<uint4 *>(xs + tt * kRouteHC + pc * 8) = v;
         }
+        // (behind the loads: ahead of them its scalar loads of the list delay every one)
+        if (h0 == 0) zero_slices(z, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid, 256);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kIter; ++i) {
@@ -173,7 +174,6 @@ __global__ __launch_bounds__(kLogitsWaves * kWave) void logits_mfma_kernel(const
 {
     __shared__ logits_f32x4 part[kLogitsWaves - 1][kWave];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    zero_slices(z, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid, kLogitsWaves * kWave);
     const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16;
     const int KT = H / 32;                                   // k-steps; wave w takes [kb, kb + n)
     const int per = (KT + kLogitsWaves - 1) / kLogitsWaves;
@@ -186,6 +186,7 @@ __global__ __launch_bounds__(kLogitsWaves * kWave) void logits_mfma_kernel(const
     LogitsStep ring[kLogitsRing];
 #pragma unroll
     for (int j = 0; j < kLogitsRing; ++j) ring[j] = logits_load(xrow, wrow, min(j, last));
+    zero_slices(z, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid, kLogitsWaves * kWave);
     for (int s0 = 0; s0 < n; s0 += kLogitsRing) {
 #pragma unroll
         for (int u = 0; u < kLogitsRing; ++u) {
