@@ -38,9 +38,19 @@ constexpr int kPF = 8;                       // staged path: weight tiles in fli
 #define LYNX_PFD 8
 #endif
 constexpr int kPFD = LYNX_PFD;               // direct path: the same (most; see DirectDepth for the depth per format)
-constexpr int kStageBytes = 2 * (32768 + 16 * 16 * 4);   // two LDS buffers for token rows: 32 KiB and 16 bytes per row (and K slice)
-// LDS for the staged token tile of passes of up to `tokens` tokens: 64 as above, else 4 k-steps double-buffered
-constexpr int stage_bytes(int tokens) { return tokens <= 64 ? kStageBytes : 2 * tokens * (4 * 64 + 16); }
+// Two LDS buffers for token rows.  They are two arrays, not halves of one: the compiler tells loads into the one from reads of
+// the other by that, and does not wait for them.  Together they end at 64 KiB, which loads into LDS can address.
+constexpr int kStageBuffer = 32768;
+
+// Token rows lie in LDS as 256-byte segments of sixteen 16-byte pieces in the order piece ^ (row % 16), so that the sixteen
+// rows of an MFMA operand are read from different banks.  A segment holds four k-steps; the piece of k-step q of a segment
+// that this lane's operand needs, for the tile layout of the weight format:
+template <int WF>
+__device__ __forceinline__ int stage_piece(int q)
+{
+    const int g = (int)((threadIdx.x & (kWave - 1)) >> 4);
+    return WF == 0 ? q * 4 + g : WF == 1 ? (q >> 1) * 8 + g * 2 + (q & 1) : g * 4 + q;
+}
 
 // Optional per-workgroup timeline of the expert kernel (-DLYNX_TIMELINE; measurement builds only): for every workgroup
 // four stamps of the chip-wide 100 MHz clock (start, item known, wait over, work done) and what it was (projection,
@@ -561,15 +571,12 @@ __device__ __forceinline__ void prefetch_weights(const DirectPlan &d, WeightRing
 template <int KW>
 struct TokenStage {
     int lr, lk;          // log2 of the rows R, of the k-steps (32 columns) per chunk
-    int rowb;            // bytes per row (+16: conflict-free 16-byte reads)
     __device__ __forceinline__ TokenStage(int te)
     {
         lr = te <= 1 ? 0 : 32 - __clz(te - 1);
         lk = 9 - (KW == 4 ? 2 : KW == 2 ? 1 : 0) - lr;
-        rowb = (64 << lk) + 16;
     }
-    __device__ __forceinline__ int slice_bytes() const { return rowb << lr; }
-    __device__ __forceinline__ int buffer_bytes() const { return KW * slice_bytes(); }
+    __device__ __forceinline__ int slice_bytes() const { return 64 << (lk + lr); }
 };
 constexpr int kStagePieces = 32 * 1024 / 16 / kFfnThreads;   // 16-byte pieces per thread and chunk
 
@@ -595,14 +602,14 @@ __device__ __forceinline__ void load_tokens(const WorkItem &w, const TokenStage<
     }
 }
 template <int KW>
-__device__ __forceinline__ void store_tokens(const TokenStage<KW> &ts, int c, const uint4 (&xr)[kStagePieces], char *stage)
+__device__ __forceinline__ void store_tokens(const TokenStage<KW> &ts, int c, const uint4 (&xr)[kStagePieces], char *stage0, char *stage1)
 {
-    char *buf = stage + (c & 1) * ts.buffer_bytes();
+    char *buf = (c & 1) ? stage1 : stage0;
 #pragma unroll
     for (int i = 0; i < kStagePieces; ++i) {
         const int q = threadIdx.x + kFfnThreads * i;
         const int pc = q & ((4 << ts.lk) - 1), row = q >> (ts.lk + 2);   // (rows of all slices in a row)
-        *reinterpret_cast<uint4 *>(buf + row * ts.rowb + pc * 16) = xr[i];
+        *reinterpret_cast<uint4 *>(buf + (row << (ts.lk + 6)) + (pc ^ (row & ((1 << ts.lr) - 1))) * 16) = xr[i];
     }
 }
 
@@ -610,7 +617,8 @@ __device__ __forceinline__ void store_tokens(const TokenStage<KW> &ts, int c, co
 // with the first chunk of token rows.  Every wave makes the same number of turns.
 template <int KW, int WF>
 __device__ __forceinline__ void stream_direct(const WorkItem &w, const DirectPlan &d, const TokenStage<KW> &ts,
-                                              WeightRing<WF> &r, BufferRsrc rb, int ro, char *stage, f32x4 &acc0, f32x4 &acc1)
+                                              WeightRing<WF> &r, BufferRsrc rb, int ro, char *stage0, char *stage1,
+                                              f32x4 &acc0, f32x4 &acc1)
 {
     constexpr int D = DirectDepth<WF>::value;
     constexpr int TS = 1 << WF;              // k-steps per weight tile
@@ -619,25 +627,32 @@ __device__ __forceinline__ void stream_direct(const WorkItem &w, const DirectPla
     const int per = slice_tiles<KW>(w);
     const int C = (1 << ts.lk) / TS;         // tiles per chunk: a multiple of D
     const int chunks = (per + C - 1) / C;
-    const char *base = stage + (wave_id() % KW) * ts.slice_bytes() + (lane & ((1 << ts.lr) - 1) & 15) * ts.rowb +
-                       (lane >> 4) * (16 << WF);
+    const int row = lane & ((1 << ts.lr) - 1);
+    int xaddr[4];                            // this lane's place in its row, for each of a segment's four k-steps
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        xaddr[q] = (wave_id() % KW) * ts.slice_bytes() + (row << (ts.lk + 6)) + (stage_piece<WF>(q) ^ row) * 16;
+    static_assert((D * TS) % 4 == 0, "a turn must hold whole segments");
     for (int c = 0; c < chunks; ++c) {
         uint4 xr[kStagePieces];
         const bool more = c + 1 < chunks;
         if (more) load_tokens<KW, WF>(w, ts, rb, ro, c + 1, xr);
-        const char *buf = base + (c & 1) * ts.buffer_bytes();
+        const char *buf = (c & 1) ? stage1 : stage0;
+        auto read_b = [&](int kk) {   // k-step kk of the turn
+            return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + (kk / 4) * 256 + xaddr[kk & 3]));
+        };
         const int end = min(per, (c + 1) * C);
         for (int s0 = c * C; s0 < end; s0 += D, buf += D * TS * 64) {
             bf16x8 b[2][TS];
 #pragma unroll
-            for (int h = 0; h < TS; ++h) b[0][h] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + 16 * h));
+            for (int h = 0; h < TS; ++h) b[0][h] = read_b(h);
 #pragma unroll
             for (int u = 0; u < D; ++u) {
                 const int s = s0 + u;
                 if (u + 1 < D) {
 #pragma unroll
                     for (int h = 0; h < TS; ++h)
-                        b[(u + 1) & 1][h] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + (u + 1) * TS * 64 + 16 * h));
+                        b[(u + 1) & 1][h] = read_b((u + 1) * TS + h);
                 }
                 bf16x8 a0[TS], a1[TS];
                 const int kt = d.kt0 + max(min(s, d.n - 1), 0);
@@ -656,7 +671,7 @@ __device__ __forceinline__ void stream_direct(const WorkItem &w, const DirectPla
             }
         }
         if (more) {
-            store_tokens<KW>(ts, c + 1, xr, stage);
+            store_tokens<KW>(ts, c + 1, xr, stage0, stage1);
             __syncthreads();
         }
     }
@@ -703,41 +718,43 @@ __device__ __forceinline__ void direct_finish(const WorkItem &w, const DirectPla
 // The fragments are requested ahead of their products, in order: left to itself the compiler read one, waited for it and
 // multiplied (every 64 cycles of MFMA behind a full LDS latency; with one column tile per fragment and stream, Mixtral
 // shapes at 512 tokens 830 -> 758 us per layer).
+// The token chunks go from memory to LDS directly (buffer loads with an LDS destination): no registers hold them, and a
+// chunk of 32 KiB is requested a whole chunk ahead.  (Through registers the chunks were half that, requested as far ahead as
+// the registers allowed: Mixtral shapes 1000 tokens 1104 -> 1079 us per layer, 128 tokens 467 -> 462; MXFP4 FFN of 100 tokens
+// 193 -> 181, FP8 FFN of 512 tokens 638 -> 600.  Both ends of a buffer have to lie below 64 KiB of LDS: beyond it such loads
+// were seen to land elsewhere.)
 // D = weight tiles in flight per stream.  The sizes are bounded by the 256 registers of a wave at two workgroups per CU:
-// sums S*NT*4, ring S*D*4, pieces of the next token chunk NT*KS.
+// sums S*NT*4, ring S*D*4, fragments.
 template <int S, int NT, int WF>
 struct StagedShape {
-    static constexpr int D = S == 4 ? (WF == 0 && NT < 8 ? 8 : 4) : kPF;
-    static constexpr int KS = NT == 2 ? 8 : (NT == 8 && S == 4) ? 2 : 4;
+    static constexpr int KS = 32 / NT;                // k-steps of 32 columns per chunk
+    static constexpr int TPC = KS >> WF;              // weight tiles per chunk
+    static constexpr int D = S == 4 ? (WF == 0 && NT < 8 ? 8 : 4) : 2 * TPC < kPF ? 2 * TPC : kPF;
     static constexpr int BQ = S == 4 && NT == 8 ? 2 : 4;   // token fragments read ahead (the same at 2 and 4)
 };
 
 // KEEP: the weights are read by another workgroup too (an expert with several token blocks): cached loads.
 template <bool DUAL, int RT, int NT, int WF, bool KEEP>
-__device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowoff, const int *outrow, char *stage)
+__device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowoff, const int *outrow, char *stage0, char *stage1)
 {
     constexpr int MATS = DUAL ? 2 : 1;
     constexpr int S = RT * MATS;
-    constexpr int D = StagedShape<S, NT, WF>::D, KS = StagedShape<S, NT, WF>::KS;
+    typedef StagedShape<S, NT, WF> Shape;
+    constexpr int D = Shape::D, KS = Shape::KS, TPC = Shape::TPC;
     constexpr int KC = TileCols<WF>::value;
     constexpr int TS = 1 << WF;                  // 32-column steps of the staged token tile per weight tile
-    constexpr int ROWB = KS * 64 + 16;           // LDS bytes per token row (+16: conflict-free 16-byte reads)
-    constexpr int BUFB = NT * 16 * ROWB;
-    static_assert(2 * BUFB <= stage_bytes(NT * 16), "token tile does not fit the LDS stage");
-    constexpr int PIECES = NT * 16 * KS * 4;     // 16-byte pieces per chunk
-    static_assert(PIECES % kFfnThreads == 0 && kFfnThreads % (KS * 4) == 0, "pieces must divide evenly over the workgroup");
-    constexpr int PPT = PIECES / kFfnThreads;
-    static_assert((D * TS) % KS == 0 && KS % TS == 0, "a ring turn must hold whole chunks, a chunk whole tiles");
+    static_assert(NT * KS * 1024 <= kStageBuffer, "a chunk must fit its buffer");
+    static_assert(TPC >= 1 && (2 * TPC) % D == 0, "two chunks must hold whole turns of the ring");
     constexpr int WSTEP = MATS * kWave;
 
-    const int tid = threadIdx.x, lane = lane_id();
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
     const int KTrow = w.K / KC;                  // tiles between consecutive row tiles
     const int KT = w.ksteps, K = KT * KC;        // weight tiles and token columns of this item
-    const int rt = (w.tile * kFfnWaves + wave_id()) * RT;   // w.tile counts units of 64 * RT rows
+    const int rt = (w.tile * kFfnWaves + wv) * RT;   // w.tile counts units of 64 * RT rows
     const bool wave_active = rt * 16 < w.R;      // idle waves read tile 0 (in bounds) and store nothing
     const int rtc = wave_active ? rt : 0;
     const int last = KT - 1;
-    const int lastc = (KT * TS + KS - 1) / KS - 1;
+    const int lastc = (KT + TPC - 1) / TPC - 1;
     // the second of a wave's row tiles may lie past the last row (gate/up; R / 16 is even for down): it re-reads the first
     const int tile2 = (RT == 1 || rtc * 16 + 16 < w.R) ? KTrow * WSTEP : 0;
 
@@ -751,32 +768,42 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
                         : nullptr;
     const bool sc_second = !DUAL && RT == 1 && (rtc & 1);
 
-    // This thread's staging pieces: (token row, 16-byte piece inside the chunk).  The rows' offsets stay in the LDS
-    // table and are looked up again for every chunk: registers are what this path is short of.  The pieces are read
-    // through a buffer resource over the B array; a piece of a row without a token, or past the row's last column
-    // (the last chunk of a ragged K, or a row shorter than one chunk), carries an offset out of range: nothing is
-    // fetched for it and it arrives as zero, which is what the stage has to hold there.
+    // Token rows: one load of a wave fetches 256 consecutive bytes of four rows (a load that gathers 64 bytes of sixteen rows
+    // in operand order costs more than the staging saves).  Block (nt, seg) of a buffer: 16 rows x 256 bytes.
+    // A row without a token carries an offset out of range: nothing is fetched, and its column is never stored.  Columns
+    // past the end (the last chunk of a ragged K) re-read the row's last ones: they meet weights that read as zero.
     const BufferRsrc rb = token_rows_resource(w.B + (size_t)w.kbeg * KC);
-    const int pc0 = (tid % (KS * 4)) * 8;   // column of every piece of this thread inside a chunk (256 % (KS*4) == 0)
-    uint4 xr[PPT];
-    // chunk c: request it ... (nothing here reads what was loaded: a read would have to wait for the load, and
-    // with it for every weight tile requested before it)
-    auto load_x = [&](int c) {
-        const int col = c * KS * 32 + pc0;
+    constexpr int SEG = KS / 4;                  // 256-byte segments of a row per chunk
+    constexpr int LPW = NT * SEG * 4 / kFfnWaves;   // loads per wave and chunk: eight, SEG of each of its groups of four rows
+    int ro[LPW / SEG];
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            const int ro = rowoff[(tid + kFfnThreads * i) / (KS * 4)];
-            xr[i] = ring_load_b(rb, (ro >= 0 && col < K) ? 2u * (unsigned)(ro + col) : kNoToken, 0);
+    for (int r = 0; r < LPW / SEG; ++r) ro[r] = rowoff[(wv * (LPW / SEG) + r) * 4 + (lane >> 4)];
+    auto load_x = [&](char *buf, int c) {
+        int wvx = wv;
+        asm volatile("" : "+s"(wvx));   // (sixteen LDS addresses kept in scalar registers would spill others)
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const int grp = wvx * (LPW / SEG) + i / SEG, seg = i % SEG;   // grp: four rows of column tile grp / 4
+            const int t = (grp & 3) * 4 + (lane >> 4);
+            const int col = min((c * SEG + seg) * 128 + ((lane & 15) ^ t) * 8, K - 8);
+            const unsigned off = (ro[i / SEG] >= 0 && c <= lastc) ? 2u * (unsigned)(ro[i / SEG] + col) : kNoToken;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rb, (__attribute__((address_space(3))) void *)(buf + ((grp >> 2) * SEG + seg) * 4096 + (grp & 3) * 1024), 16, off, 0, 0, 0);
         }
     };
-    // ... and, a chunk of weight tiles later, put it into the stage
-    auto store_x = [&](int c) {
-        char *buf = stage + (c & 1) * BUFB;
+    int xaddr[4];                                // this lane's place in a block, for each of the block's four k-steps
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            const int q = tid + kFfnThreads * i;
-            *reinterpret_cast<uint4 *>(buf + (q / (KS * 4)) * ROWB + (q % (KS * 4)) * 16) = xr[i];
-        }
+    for (int q = 0; q < 4; ++q) xaddr[q] = (lane & 15) * 256 + (stage_piece<WF>(q) ^ (lane & 15)) * 16;
+    // The wave's own pieces of the chunk in buf have landed (it reads the last of them: the compiler waits for exactly
+    // that load), and then everybody's have, and nobody reads the other buffer any more.
+    auto chunk_ready = [&](const char *buf) {
+        const unsigned v = *reinterpret_cast<const unsigned *>(
+            buf + (((wv + 1) * (LPW / SEG) - 1) / 4 * SEG + SEG - 1) * 4096 + (((wv + 1) * (LPW / SEG) - 1) & 3) * 1024 + lane * 16);
+        asm volatile("" ::"v"(v) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
     };
 
     const BufferRsrc rw = weights_resource(w.W + ((size_t)rtc * KTrow + w.kbeg) * WSTEP);
@@ -797,61 +824,59 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
     for (int j = 0; j < S; ++j)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    load_x(stage0, 0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < D; ++j) load_w(j, j);
-    load_x(0);
-    store_x(0);
-    __syncthreads();
+    chunk_ready(stage0);
 
-    // this lane's B-fragment offset inside a token tile (its column group: 8, 16 or 32 columns)
-    const int brow = (lane & 15) * ROWB + (lane >> 4) * (16 << WF);
-    for (int s0 = 0; s0 < KT; s0 += D) {
+    for (int s0 = 0; s0 < KT; s0 += 2 * TPC) {
 #pragma unroll
-        for (int u = 0; u < D; ++u) {
-            const int s = s0 + u;
-            const int c = (s * TS) / KS;
-            if ((u * TS) % KS == 0) {
-                load_x(min(c + 1, lastc));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // (tiles past the end of the run were not fetched and arrived as zeros; a wave without rows multiplies
-            // tile 0 and stores nothing)
-            const char *buf = stage + (c & 1) * BUFB + brow + ((u * TS) % KS) * 64;
-            const int kt = w.kbeg + min(s, last);
-            bf16x8 a[S][TS];
+        for (int half = 0; half < 2; ++half) {   // the two buffers are told apart at compile time
+            if (half == 1 && s0 + TPC >= KT) break;
+            const char *cur = half ? stage1 : stage0;
+            char *nxt = half ? stage0 : stage1;
+            load_x(nxt, s0 / TPC + half + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < S; ++j) {
-                float sc = 1.0f;
-                if (WF == 2) {
-                    const uint2 q = sq[u][DUAL ? j / MATS : j / 2];
-                    sc = mx_scale((DUAL ? (j & 1) : RT == 1 ? (int)sc_second : (j & 1)) ? q.y : q.x, kt);
+            for (int ut = 0; ut < TPC; ++ut) {
+                const int u = (half * TPC + ut) % D;
+                const int s = s0 + half * TPC + ut;
+                // (tiles past the end of the run were not fetched and arrived as zeros; a wave without rows multiplies
+                // tile 0 and stores nothing)
+                const int kt = w.kbeg + min(s, last);
+                bf16x8 a[S][TS];
+#pragma unroll
+                for (int j = 0; j < S; ++j) {
+                    float sc = 1.0f;
+                    if (WF == 2) {
+                        const uint2 q = sq[u][DUAL ? j / MATS : j / 2];
+                        sc = mx_scale((DUAL ? (j & 1) : RT == 1 ? (int)sc_second : (j & 1)) ? q.y : q.x, kt);
+                    }
+                    decode_tile<WF>(wr[u][j], sc, a[j]);
                 }
-                decode_tile<WF>(wr[u][j], sc, a[j]);
-            }
-            // token fragments in the order (k-step, token column), BQ of them requested ahead of their products
-            constexpr int G = TS * NT, BQ = StagedShape<S, NT, WF>::BQ < G ? StagedShape<S, NT, WF>::BQ : G;
-            auto read_b = [&](int i) {
-                return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + (i % NT) * 16 * ROWB + 16 * (i / NT)));
-            };
-            bf16x8 bq[BQ];
+                // token fragments in the order (k-step, token column), BQ of them requested ahead of their products
+                constexpr int G = TS * NT, BQ = Shape::BQ < G ? Shape::BQ : G;
+                auto read_b = [&](int i) {
+                    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
+                        cur + ((i % NT) * SEG + (ut * TS + i / NT) / 4) * 4096 + xaddr[(ut * TS + i / NT) & 3]));
+                };
+                bf16x8 bq[BQ];
 #pragma unroll
-            for (int i = 0; i < BQ; ++i) bq[i] = read_b(i);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int i = 0; i < BQ; ++i) bq[i] = read_b(i);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
+                for (int i = 0; i < G; ++i) {
 #pragma unroll
-                for (int j = 0; j < S; ++j)
-                    acc[j][i % NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j][i / NT], bq[i % BQ], acc[j][i % NT], 0, 0, 0);
-                if (i + BQ < G) bq[i % BQ] = read_b(i + BQ);
+                    for (int j = 0; j < S; ++j)
+                        acc[j][i % NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j][i / NT], bq[i % BQ], acc[j][i % NT], 0, 0, 0);
+                    if (i + BQ < G) bq[i % BQ] = read_b(i + BQ);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                load_w(u, s + D);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            load_w(u, s + D);
-            __builtin_amdgcn_sched_barrier(0);
-            if ((u * TS + TS) % KS == 0) {
-                store_x(c + 1);
-                __syncthreads();
-            }
+            chunk_ready(nxt);
         }
     }
     if (!wave_active) return;
@@ -874,17 +899,18 @@ constexpr int staged_tokens(int big, int wf) { return big && wf == 0 ? kTokBlock
 // blocks) are read with cached loads: the later block finds them in the memory-side cache (Mixtral shapes, 1000 tokens,
 // 1336 against 1230 us per layer).
 template <bool DUAL, int RT, int BIG, int WF>
-__device__ __forceinline__ void staged_pass(const WorkItem &w, int nb, const int *rowoff, const int *outrow, char *stage)
+__device__ __forceinline__ void staged_pass(const WorkItem &w, int nb, const int *rowoff, const int *outrow, char *stage0,
+                                            char *stage1)
 {
     constexpr int TB = staged_tokens(BIG, WF);
     if (nb <= 32)
-        expert_staged<DUAL, RT, 2, WF, false>(w, rowoff, outrow, stage);
+        expert_staged<DUAL, RT, 2, WF, false>(w, rowoff, outrow, stage0, stage1);
     else if (TB > 64 && nb <= 64)
-        expert_staged<DUAL, RT, 4, WF, false>(w, rowoff, outrow, stage);
+        expert_staged<DUAL, RT, 4, WF, false>(w, rowoff, outrow, stage0, stage1);
     else if (BIG && w.te_all > TB)
-        expert_staged<DUAL, RT, TB / 16, WF, BIG != 0>(w, rowoff, outrow, stage);
+        expert_staged<DUAL, RT, TB / 16, WF, BIG != 0>(w, rowoff, outrow, stage0, stage1);
     else
-        expert_staged<DUAL, RT, TB / 16, WF, false>(w, rowoff, outrow, stage);
+        expert_staged<DUAL, RT, TB / 16, WF, false>(w, rowoff, outrow, stage0, stage1);
 }
 
 // Both projections of every invoked and shared expert in ONE launch.  Grid: all gate/up workgroups, then
@@ -937,7 +963,7 @@ constexpr int staged_row_tiles(bool dual, int kw, int big) { return big && (dual
 
 // sub >= 0 (gate/up, KW = 4 only): the workgroup takes row tile `sub` of the four that workgroup b stands for.
 template <bool DUAL, int KW, int BIG, int WF>
-__device__ __forceinline__ void expert_work(const GemmParams &p, int b, const FfnParams &fp, char *stage, int *rowoff,
+__device__ __forceinline__ void expert_work(const GemmParams &p, int b, const FfnParams &fp, char *stage0, char *stage1, int *rowoff,
                                             int *outrow, int sub = -1)
 {
     constexpr int TB = staged_tokens(BIG, WF);   // tokens per pass
@@ -990,17 +1016,17 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
                 __syncthreads();   // the stage has been read
                 load_tokens<KW, WF>(w, ts, rb, ro, 0, xr);
             }
-            store_tokens<KW>(ts, 0, xr, stage);
+            store_tokens<KW>(ts, 0, xr, stage0, stage1);
             __syncthreads();
             f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-            stream_direct<KW, WF>(w, plan, ts, ring, rb, ro, stage, acc0, acc1);
+            stream_direct<KW, WF>(w, plan, ts, ring, rb, ro, stage0, stage1, acc0, acc1);
             const DirectPlan done = plan;
             if (un + 1 < units) {
                 w.tile = unit0 + un + 1;
                 plan = plan_direct<DUAL, KW, WF>(w);
                 prefetch_weights<WF>(plan, ring);
             }
-            direct_finish<DUAL, KW, WF>(w, done, orow, acc0, acc1, stage);
+            direct_finish<DUAL, KW, WF>(w, done, orow, acc0, acc1, stage0);
         }
     } else {
         wait_for_h();
@@ -1022,7 +1048,7 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
             // cost registers that they do not have)
             const int nb = w.Te - w.tok0;
             load_tables(w.tok0, nb);
-            staged_pass<DUAL, kRT, BIG, WF>(w, nb, rowoff, outrow, stage);
+            staged_pass<DUAL, kRT, BIG, WF>(w, nb, rowoff, outrow, stage0, stage1);
         } else {
             // units of 64 rows.  A direct workgroup covers 16*RW rows (gate/up) or 32*RW rows (down).
             constexpr int kRowsPerWG = 16 * (kFfnWaves / KW) * (DUAL ? 1 : 2);
@@ -1049,7 +1075,7 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
                         const int nb = min(w.Te - i0, TB);
                         __syncthreads();   // the previous pass has read rowoff / outrow and the stage
                         load_tables(i0, nb);
-                        staged_pass<DUAL, kRT, BIG, WF>(w, nb, rowoff, outrow, stage);
+                        staged_pass<DUAL, kRT, BIG, WF>(w, nb, rowoff, outrow, stage0, stage1);
                     }
                 }
             }
@@ -1073,7 +1099,7 @@ __global__ __launch_bounds__(kFfnThreads, (BIG || WF != 0) ? 2 : kWgPerCuSmall) 
 {
     // staged token tile, or the K-slice partial sums
     constexpr int TB = staged_tokens(BIG, WF);
-    __shared__ __attribute__((aligned(16))) char stage[stage_bytes(TB)];
+    __shared__ __attribute__((aligned(16))) char stage0[kStageBuffer], stage1[kStageBuffer];
     __shared__ int rowoff[TB];   // staged path: element offset of each token's B row, -1 = none
     __shared__ int outrow[TB];   // staged path: output row of each token, -1 = none
     const int b = blockIdx.x + fp.block0;
@@ -1103,11 +1129,11 @@ __global__ __launch_bounds__(kFfnThreads, (BIG || WF != 0) ? 2 : kWgPerCuSmall) 
             }
         }
         if (WF != 0 || sub < 0)
-            expert_work<true, 1, BIG, WF>(fp.gu, bb, fp, stage, rowoff, outrow);
+            expert_work<true, 1, BIG, WF>(fp.gu, bb, fp, stage0, stage1, rowoff, outrow);
         else if constexpr (WF == 0)
-            expert_work<true, kFfnWaves, BIG, WF>(fp.gu, bb, fp, stage, rowoff, outrow, sub);
+            expert_work<true, kFfnWaves, BIG, WF>(fp.gu, bb, fp, stage0, stage1, rowoff, outrow, sub);
     } else {
-        expert_work<false, KWD, BIG, WF>(fp.dn, b - fp.gu_blocks, fp, stage, rowoff, outrow);
+        expert_work<false, KWD, BIG, WF>(fp.dn, b - fp.gu_blocks, fp, stage0, stage1, rowoff, outrow);
     }
 }
 
@@ -1475,7 +1501,7 @@ static int launch_padded(const FfnParams &fp, unsigned blocks, hipStream_t st)
     static_assert(kLdsTargetPerWg * (kWgPerCu + 1) > kLdsPerCu && kLdsTargetPerWg * kWgPerCu <= kLdsPerCu, "LDS pad");
     // what the kernel declares itself: the stage and the two token tables
     constexpr int TB = staged_tokens(BIG, WF);
-    constexpr int kStatic = stage_bytes(TB) + 2 * 4 * TB;
+    constexpr int kStatic = 2 * kStageBuffer + 2 * 4 * TB;
     constexpr int pad = kLdsTargetPerWg > kStatic ? kLdsTargetPerWg - kStatic : 0;
     static_assert((kStatic + pad) * kWgPerCu <= kLdsPerCu, "the workgroups must fit a CU");
     hipLaunchKernelGGL((ffn_kernel<KWD, BIG, WF>), dim3(blocks), dim3(kFfnThreads), pad, st, fp);
