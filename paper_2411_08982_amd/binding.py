@@ -95,6 +95,8 @@ def _check(rc: int):
 def _ptr(t, dtype, what):
     if t is None:
         return None
+    if type(t) is torch.Tensor and t.dtype is dtype and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{what}: expected a CUDA/HIP tensor")
     if t.dtype != dtype:
@@ -105,7 +107,8 @@ def _ptr(t, dtype, what):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the handle alone: building a Stream object around it on every call costs microseconds of a short call
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 BF16, F32, I32 = torch.bfloat16, torch.float32, torch.int32
