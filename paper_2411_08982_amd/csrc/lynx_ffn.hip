@@ -7,10 +7,10 @@
 //     1 KiB load (16 bytes per lane) that IS the A operand of v_mfma_f32_16x16x32_bf16;
 //   * a wave owns 16 output rows and walks (a slice of) the contraction dimension with a ring of
 //     prefetched tiles in registers, so each weight byte is fetched from HBM once per call;
-//   * the tokens of the expert are the B operand.  Experts with few tokens (<= 16, the usual decode
-//     case) read the token columns straight from global memory in MFMA layout ("direct" path: no
-//     LDS, no barrier in the loop); experts with many tokens stage the token tile through LDS, shared
-//     by four row tiles ("staged" path);
+//   * the tokens of the expert are the B operand, read from LDS.  Experts with few tokens (<= 16, the usual
+//     decode case) put their rows there before the stream starts ("direct" path: one column tile, K split over
+//     the waves where that pays); experts with many tokens stream the token tiles through LDS in chunks shared
+//     by the four waves ("staged" path);
 //   * the grid is fixed (most experts the batch can invoke + shared experts, times row tiles); a
 //     workgroup whose rank is past the device-side num_active leaves at once, so nothing is read back
 //     to the host;
@@ -345,14 +345,12 @@ __device__ __forceinline__ void epilogue(const f32x4 (&accg_in)[NT], const f32x4
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Weight streaming.  Both kernels keep a ring of kPF prefetched 1 KiB weight tiles per wave and matrix
-// in registers.  The loop bodies are branch-free on purpose: loads past the end are clamped to the last
-// tile (re-reading it from cache) and their MFMA operand is zeroed, so that the compiler can count the
-// outstanding loads and wait for exactly the oldest one instead of draining the queue.
+// Weight streaming.  Both paths keep a ring of prefetched 1 KiB weight tiles per wave and stream in registers.  The loop
+// bodies are branch-free on purpose: loads past the end of a run carry an offset out of range (nothing is fetched, the tile
+// reads as zero), so that the compiler can count the outstanding loads and wait for exactly the oldest one instead of
+// draining the queue.
 // ---------------------------------------------------------------------------------------------------
 
-// Direct: Wt = first weight tile of this wave (uint4 units); n = k-steps of this wave (>= 1);
-// boff[nt] = byte offset of this lane's B piece at the wave's first column (4 x 16 bytes = 32 columns per step).
 // The address passes through an empty asm so that the compiler treats every ring load as a distinct,
 // unmovable-by-value-numbering load: otherwise it merges the prefetch for the next turn of the ring
 // with the loads of that turn and issues them only when they are needed.
@@ -369,11 +367,8 @@ __device__ __forceinline__ uint4 ring_load(const uint4 *__restrict__ base, int i
 // and rows start on 128-byte lines, so no cache on the reading side can hold an older copy of a line.  (Device-
 // coherent loads instead would send every workgroup's re-reads of the same few rows to memory.)
 //
-// They are read through a buffer resource over the B array with a byte offset per lane.  A lane whose token column
-// is empty (an expert with 3 tokens fills 3 of the 16 columns of a fragment) carries an offset past the resource's
-// range: the hardware returns zero for it and fetches nothing.  The load path's time goes with the lanes that are in
-// range (measured on a cache-resident region: 16 bytes per lane with 2 of 16 token columns in range cost 0.38 of
-// the full load), and with 4-bit weights the token fragments are four times the bytes of the weights they meet.
+// They are read through a buffer resource over the B array with a byte offset per lane, on their way to LDS.  A lane whose
+// row holds no token carries an offset past the resource's range: the hardware returns zero for it and fetches nothing.
 constexpr unsigned kNoToken = 0x80000000u;   // past any resource (the B arrays stay below 2 GiB, checked on the host)
 typedef __amdgpu_buffer_rsrc_t BufferRsrc;
 __device__ __forceinline__ BufferRsrc token_rows_resource(const uint16_t *B)
@@ -918,8 +913,9 @@ __device__ __forceinline__ void staged_pass(const WorkItem &w, int nb, const int
 // device-built plan (lynx_plan.h): live items are contiguous from the front of each part, and a workgroup past them
 // leaves after one load.  A row unit is 16*RW rows of gate and up, or 32*RW rows of down, RW = 4 / KW.  An expert
 // with at most kDirectMaxTokens tokens takes the direct path with the workgroup's four waves as RW row tiles x KW
-// slices of K.  A larger expert takes the staged path, in which a workgroup covers 64 rows: of every KW
-// consecutive workgroups one does the work, one pass of up to 64 (128) tokens per item, and the others leave.  A down
+// slices of K.  A larger expert takes the staged path, in which a workgroup covers 64 rows (128 in the large-batch kernels:
+// see staged_row_tiles): where a direct workgroup covers fewer, one of those that share the rows does the work, one pass of
+// up to 64 (128) tokens per item, and the others leave.  A down
 // item covers m consecutive row units, m chosen on the device from the number of (expert, token block) pairs: few
 // invoked experts get short items that fill the chip, many get fewer, longer ones, whose start-up (tables, first
 // tiles) weighs less.  The gate/up part of the grid ends with spare workgroups: when the last round of live gate/up
@@ -1389,7 +1385,7 @@ __global__ __launch_bounds__(256) void quantize_fp4_kernel(const uint16_t *__res
 // How many of a workgroup's four waves split the contraction dimension (the rest split rows).  Long
 // per-wave streams amortise the fill and drain of the prefetch ring, so K is only split when the
 // batch cannot invoke enough experts to give every CU several waves otherwise.
-static int pick_k_waves(int K, bool dual, int T, int max_experts, int bits_per_weight)
+static int pick_k_waves(int K, int R, bool dual, int T, int max_experts, int bits_per_weight)
 {
     // Gate/up: a wave streams a whole row tile of both matrices (2 * K * 32 bytes, contiguous); measured best
     // at every expert count.  It also makes a workgroup exactly one 64-row unit of the staged path.
@@ -1399,9 +1395,10 @@ static int pick_k_waves(int K, bool dual, int T, int max_experts, int bits_per_w
     // do are expensive).
     // Beyond 64 tokens (passes of up to 128 tokens): 128-row workgroups, whose staged passes give every wave two row
     // tiles that share each token fragment read from LDS (measured 2-4 % faster on every shape).
-    // (not with quantised weights and at most 8 experts: 256 down workgroups of a Mixtral-shaped layer then carry too
-    // few bytes each: FP8 419 against 386 us, MXFP4 360 against 323 us per layer at 128 tokens)
-    if (T > kTokBlock && !(bits_per_weight < 16 && max_experts <= 8)) return 1;
+    // (not with quantised weights where 128-row workgroups are fewer than the CUs: 8 experts of 512 x 1024, FP8, 100 tokens
+    // 22.8 against 21.7 us.  With 8 experts of 4096 rows, 256 of them, MXFP4: 1000 tokens 727 against 820 us, 256 tokens 282
+    // against 307, 100 tokens 179 against 182; FP8 within 1 %.)
+    if (T > kTokBlock && !(bits_per_weight < 16 && max_experts <= 8 && (long)max_experts * R < 256 * 128)) return 1;
     if (T > kDirectMaxTokens) return 2;
     // Down, direct path only.  Measured: splitting K four ways pays when the batch can invoke so few experts
     // that whole row groups would leave the chip with too few, too long workgroups (Mixtral-like shapes); with
@@ -1442,7 +1439,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
 {
     FfnShape s;
     const int max_experts = (int)min((long)N, (long)T * k) + n_shared;
-    s.kwd = pick_k_waves(F, false, T, max_experts, 16 >> format);
+    s.kwd = pick_k_waves(F, H, false, T, max_experts, 16 >> format);
     const int forced = g_tune.dn_kw.load();
     if (forced == 1 || forced == 2 || (forced == 4 && T <= 8)) s.kwd = forced;
     // Gate/up units of 128 rows when the experts hold more than 64 tokens on average: fewer, longer workgroups that stage
@@ -1496,8 +1493,8 @@ constexpr int kLdsPerCu = 160 * 1024;
 template <int KWD, int BIG, int WF>
 static int launch_padded(const FfnParams &fp, unsigned blocks, hipStream_t st)
 {
-    constexpr int kWgPerCu = BIG == 3 ? 1 : (BIG || WF != 0) ? 2 : kWgPerCuSmall;
-    constexpr int kLdsTargetPerWg = kWgPerCu == 1 ? 84 * 1024 : kWgPerCu == 2 ? 56 * 1024 : kLdsPerCu / kWgPerCu / 1024 * 1024;   // (at most 64 KiB per workgroup)
+    constexpr int kWgPerCu = (BIG || WF != 0) ? 2 : kWgPerCuSmall;
+    constexpr int kLdsTargetPerWg = kWgPerCu == 2 ? 56 * 1024 : kLdsPerCu / kWgPerCu / 1024 * 1024;   // (at most 64 KiB per workgroup)
     static_assert(kLdsTargetPerWg * (kWgPerCu + 1) > kLdsPerCu && kLdsTargetPerWg * kWgPerCu <= kLdsPerCu, "LDS pad");
     // what the kernel declares itself: the stage and the two token tables
     constexpr int TB = staged_tokens(BIG, WF);
