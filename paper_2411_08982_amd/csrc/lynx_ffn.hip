@@ -1095,7 +1095,9 @@ __global__ __launch_bounds__(kFfnThreads, (BIG || WF != 0) ? 2 : kWgPerCuSmall) 
 {
     // staged token tile, or the K-slice partial sums
     constexpr int TB = staged_tokens(BIG, WF);
-    __shared__ __attribute__((aligned(16))) char stage0[kStageBuffer], stage1[kStageBuffer];
+    // (the alignment puts them ahead of the tables: they have to end at 64 KiB)
+    __shared__ __attribute__((aligned(1024))) char stage0[kStageBuffer], stage1[kStageBuffer];
+    static_assert(2 * kStageBuffer <= 65536, "loads into LDS address 64 KiB");
     __shared__ int rowoff[TB];   // staged path: element offset of each token's B row, -1 = none
     __shared__ int outrow[TB];   // staged path: output row of each token, -1 = none
     const int b = blockIdx.x + fp.block0;
@@ -1556,7 +1558,7 @@ static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
 
 extern "C" size_t lynx_workspace_bytes(int T, int H, int F, int N, int k, int n_shared, int F_shared)
 {
-    // (N does not enter: the tables per expert are reserved for LYNX_MAX_N experts, inside the first 64 KiB)
+    // (N does not enter: the tables per expert are reserved for LYNX_MAX_N experts)
     if (T < 0 || H < 0 || F < 0 || N < 0 || k < 0 || n_shared < 0 || F_shared < 0) return 0;
     if (n_shared == 0) F_shared = 0;
     return lynx::workspace_layout(T, H, F, k, n_shared, F_shared, lynx::shared_down_splits(F, n_shared, F_shared)).total;
