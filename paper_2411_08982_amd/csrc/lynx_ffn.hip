@@ -1448,7 +1448,13 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     // the tokens half as often (Mixtral shapes, 1000 tokens: 1156 -> 1126 us; DeepSeek-V2-Lite shapes, 1000: 343 -> 333).
     // With fewer tokens the weight stream is the bound and the finer units fill the chip more evenly (Mixtral shapes, 128
     // tokens: 454 against 466 us, 256: 557 against 574).
-    s.big = T <= kTokBlock ? 0 : (long)T * k > (long)kTokBlock * N ? 2 : 1;
+    // MXFP4: from 32 tokens on average where the units fill the chip, since a unit's fixed work weighs more beside fewer
+    // weight bytes (FFN calls: DeepSeek-V2-Lite shapes, 600 tokens 147 -> 137 us; Mixtral shapes, 200 tokens 252 -> 242;
+    // Qwen1.5-MoE shapes, 500 tokens 128 -> 121; but Mixtral shapes, 100 tokens, 25 on average, 180 -> 183, and 8 experts of
+    // 512 x 1024, 200 tokens, FP8 22.9 -> 25.3; FP8 with large experts -2 to +1 %).
+    const bool sooner = format == 2 && (long)N * F >= 256L * 128 && (long)T * k >= 32L * N;
+    const bool many = sooner || (long)T * k > (long)kTokBlock * N;
+    s.big = T <= kTokBlock ? 0 : many ? 2 : 1;
     s.single = single_launch(T, F);
     s.tok_block = staged_tokens(s.big, format);
     s.max_blocks = plan_max_blocks(T, N, k, s.tok_block);

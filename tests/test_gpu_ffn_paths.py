@@ -23,15 +23,16 @@ def L():
     return L
 
 
-def run_case(L, fmt, T, counts, H, F, S, Fs):
-    print(f"ffn paths {fmt} T={T} counts={counts} H={H} F={F} shared={S}x{Fs}", flush=True)
-    N = k = len(counts)
+def run_case(L, fmt, T, counts, H, F, S, Fs, spare=0):
+    print(f"ffn paths {fmt} T={T} counts={counts} spare={spare} H={H} F={F} shared={S}x{Fs}", flush=True)
+    k = len(counts)
+    N = k + spare      # experts that no token picks
     rng = np.random.default_rng([T, H, F, sum(counts)])
     idx = np.full((T, k), -1, np.int32)      # column e: the tokens of expert e; -1 is a skipped pair
     for e, c in enumerate(counts):
         idx[rng.permutation(T)[:c], e] = e
     gate = rng.uniform(0.1, 1.0, (T, k)).astype(np.float32)
-    every = np.tile(np.arange(N, dtype=np.int32), (T, 1))   # the oracle takes no skipped pairs: weight 0 instead
+    every = np.tile(np.arange(k, dtype=np.int32), (T, 1))   # the oracle takes no skipped pairs: weight 0 instead
     gate_ref = np.where(idx >= 0, gate, 0.0)
     x = wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
     mk = lambda *shape: wl.f32_to_bf16_bits((rng.standard_normal(shape) * 0.05).astype(np.float32))
@@ -78,17 +79,19 @@ LARGE = [
     (130, (130, 129, 128, 127, 17), 384, 640, 0, 0),       # blocks of one expert: a full one and a remainder of 1 or 2
     (300, (300, 256, 257, 16, 32), 128, 384, 1, 256),      # 3 blocks (5 of 64); a shared expert over all tokens
     (97, (97, 0, 81, 5, 49), 512, 256, 1, 768),            # an expert that is not invoked; a wide shared expert (K slices)
-    (80, (3, 20, 0, 33, 65), 640, 384, 0, 0),              # few tokens per expert: units of 64 rows
+    (80, (3, 20, 0, 33, 65), 640, 384, 0, 0),
 ]
+# few tokens per expert on average (the unused experts count): units of 64 rows for bf16, or for every format
+SPARSE = [(130, (130, 20, 65, 5), 384, 640, 1, 128, 8), (90, (17, 90, 33, 64, 1), 256, 256, 0, 0, 20)]
 RAGGED = {"bf16": (32, 96), "fp8": (64, 64), "fp4": (0, 0)}   # added to H and F: the format's smallest steps
 
 
 @pytest.mark.parametrize("fmt", ["bf16", "fp8", "fp4"])
-@pytest.mark.parametrize("case", LARGE)
+@pytest.mark.parametrize("case", LARGE + SPARSE)
 def test_large_batches(L, fmt, case):
-    T, counts, H, F, S, Fs = case
+    T, counts, H, F, S, Fs, *spare = case
     dH, dF = RAGGED[fmt]
-    run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs)
+    run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs, *spare)
 
 
 # At most 16 tokens per expert: 1, 2, 4, 8 or 16 token rows in LDS, as many columns at a time as fit (contractions that need
