@@ -749,7 +749,6 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
     const bool wave_active = rt * 16 < w.R;      // idle waves read tile 0 (in bounds) and store nothing
     const int rtc = wave_active ? rt : 0;
     const int last = KT - 1;
-    const int lastc = (KT + TPC - 1) / TPC - 1;
     // the second of a wave's row tiles may lie past the last row (gate/up; R / 16 is even for down): it re-reads the first
     const int tile2 = (RT == 1 || rtc * 16 + 16 < w.R) ? KTrow * WSTEP : 0;
 
@@ -765,25 +764,32 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
 
     // Token rows: one load of a wave fetches 256 consecutive bytes of four rows (a load that gathers 64 bytes of sixteen rows
     // in operand order costs more than the staging saves).  Block (nt, seg) of a buffer: 16 rows x 256 bytes.
-    // A row without a token carries an offset out of range: nothing is fetched, and its column is never stored.  Columns
-    // past the end (the last chunk of a ragged K) re-read the row's last ones: they meet weights that read as zero.
+    // A row without a token carries an offset out of range: nothing is fetched, and its column is never stored.  So do the
+    // columns past the end (the last chunk of a ragged K): they arrive in LDS as zeros.  The weights that they meet read as
+    // zero too, but that alone would not do: zero times an infinity of the row is NaN.
     const BufferRsrc rb = token_rows_resource(w.B + (size_t)w.kbeg * KC);
     constexpr int SEG = KS / 4;                  // 256-byte segments of a row per chunk
     constexpr int LPW = NT * SEG * 4 / kFfnWaves;   // loads per wave and chunk: eight, SEG of each of its groups of four rows
-    int ro[LPW / SEG];
+    // The piece of its row that a lane fetches is piece0 ^ (its group's place among the four of a column tile) * 4; ro: the
+    // byte offset of that piece in the first segment (past the range for a row without a token, whatever is added).
+    const int piece0 = (lane & 15) ^ (lane >> 4);
+    unsigned ro[LPW / SEG];
 #pragma unroll
-    for (int r = 0; r < LPW / SEG; ++r) ro[r] = rowoff[(wv * (LPW / SEG) + r) * 4 + (lane >> 4)];
+    for (int r = 0; r < LPW / SEG; ++r) {
+        const int grp = wv * (LPW / SEG) + r;    // four rows of column tile grp / 4
+        const int o = rowoff[grp * 4 + (lane >> 4)];
+        ro[r] = (o >= 0 ? 2u * (unsigned)o : kNoToken) + (unsigned)(piece0 ^ ((grp & 3) * 4)) * 16u;
+    }
     auto load_x = [&](char *buf, int c) {
         int wvx = wv;
         asm volatile("" : "+s"(wvx));   // (sixteen LDS addresses kept in scalar registers would spill others)
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
-            const int grp = wvx * (LPW / SEG) + i / SEG, seg = i % SEG;   // grp: four rows of column tile grp / 4
-            const int t = (grp & 3) * 4 + (lane >> 4);
-            const int col = min((c * SEG + seg) * 128 + ((lane & 15) ^ t) * 8, K - 8);
-            const unsigned off = (ro[i / SEG] >= 0 && c <= lastc) ? 2u * (unsigned)(ro[i / SEG] + col) : kNoToken;
+            const int grp = wvx * (LPW / SEG) + i / SEG, seg = i % SEG;
+            const int col = (c * SEG + seg) * 128;   // first column of the segment
+            const unsigned off = (piece0 ^ ((grp & 3) * 4)) * 8 < K - col ? ro[i / SEG] : kNoToken;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rb, (__attribute__((address_space(3))) void *)(buf + ((grp >> 2) * SEG + seg) * 4096 + (grp & 3) * 1024), 16, off, 0, 0, 0);
+                rb, (__attribute__((address_space(3))) void *)(buf + ((grp >> 2) * SEG + seg) * 4096 + (grp & 3) * 1024), 16, off, 2 * col, 0, 0);
         }
     };
     int xaddr[4];                                // this lane's place in a block, for each of the block's four k-steps

@@ -116,3 +116,43 @@ def test_few_tokens_per_expert(L, fmt, case):
     T, counts, H, F, S, Fs = case
     dH, dF = RAGGED[fmt]
     run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs)
+
+
+# An infinity in the last columns of a token row (of x, or of the intermediate vector, which can overflow bf16) is part of
+# the token's sums and of nothing else.  The contractions end inside a chunk of the token stage: what the stage holds past
+# the end meets weights that read as zero, and has to be zero itself (zero times infinity is NaN).
+@pytest.mark.parametrize("where", ["x", "h"])
+@pytest.mark.parametrize("fmt,H,F", [("bf16", 288, 416), ("fp8", 320, 448), ("fp4", 384, 640)])
+@pytest.mark.parametrize("T,counts", [(40, (40, 17, 3)), (130, (130, 70, 65, 20, 8)), (70, (20, 33, 64))])
+def test_infinity_past_a_ragged_contraction(L, fmt, H, F, T, counts, where):
+    print(f"ffn infinity {fmt} T={T} counts={counts} H={H} F={F} in {where}", flush=True)
+    k = N = len(counts)
+    rng = np.random.default_rng([T, H, F])
+    idx = np.full((T, k), -1, np.int32)
+    for e, c in enumerate(counts):
+        idx[rng.permutation(T)[:c], e] = e
+    gate = rng.uniform(0.1, 1.0, (T, k)).astype(np.float32)
+    # all positive: a sum with an infinity in it is +Inf, whatever the order
+    pos = lambda *shape: np.abs(rng.standard_normal(shape)).astype(np.float32) * 0.02 + 0.05   # (no code of theirs is zero)
+    x, Wg, Wu, Wd = pos(T, H), pos(N, F, H), pos(N, F, H), pos(N, H, F)
+    if where == "x":
+        hit = rng.permutation(T)[:T // 3]
+        x[hit[:, None], H - 1 - rng.integers(0, 8, (hit.size, 1))] = np.inf
+    else:
+        hit = np.arange(T)
+        Wg[:, F - 3] *= 1e21
+        Wu[:, F - 3] *= 1e21
+    hit = np.isin(np.arange(T), hit) & (idx >= 0).any(axis=1)
+    W = [wl.f32_to_bf16_bits(w) for w in (Wg, Wu, Wd)]
+    x = wl.f32_to_bf16_bits(x)
+    idx_d = dev(idx)
+    p = L.lynx_permute(idx_d, N)
+    if fmt == "bf16":
+        y = L.lynx_moe_ffn(to_bf16_dev(x), *L.lynx_pack_weights(*map(to_bf16_dev, W)), idx_d, dev(gate), p, N, F)
+    else:
+        quantize, ffn = {"fp8": (L.lynx_quantize_weights_fp8, L.lynx_moe_ffn_fp8),
+                         "fp4": (L.lynx_quantize_weights_fp4, L.lynx_moe_ffn_fp4)}[fmt]
+        y = ffn(to_bf16_dev(x), quantize(*map(to_bf16_dev, W)), idx_d, dev(gate), p, N, F)
+    torch.cuda.synchronize()
+    y = host(y)
+    assert np.all(np.isposinf(y[hit])) and np.all(np.isfinite(y[~hit]))
