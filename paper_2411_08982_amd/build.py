@@ -5,6 +5,11 @@ import os
 import subprocess
 import sys
 
+if __package__:
+    from . import check_code
+else:
+    import check_code
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblynx.so")
@@ -32,6 +37,7 @@ def build(verbose: bool = False, extra_flags=(), lib_path: str = LIB, obj_suffix
                        text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
+    check_code.check(lib_path)
     return lib_path
 
 

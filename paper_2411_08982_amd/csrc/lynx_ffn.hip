@@ -39,8 +39,11 @@ constexpr int kPF = 8;                       // staged path: weight tiles in fli
 #endif
 constexpr int kPFD = LYNX_PFD;               // direct path: the same (most; see DirectDepth for the depth per format)
 // Two LDS buffers for token rows.  They are two arrays, not halves of one: the compiler tells loads into the one from reads of
-// the other by that, and does not wait for them.  Together they end at 64 KiB, which loads into LDS can address.
+// the other by that, and does not wait for them.  They have to lie in the first 64 KiB, which loads into LDS can address.
+// The compiler places them (by falling alignment, as it happens); the build compares the size of the kernel's LDS segment:
+// anything ahead of them or between them would add a whole kStageAlign.
 constexpr int kStageBuffer = 32768;
+constexpr int kStageAlign = 4096;
 
 // Token rows lie in LDS as 256-byte segments of sixteen 16-byte pieces in the order piece ^ (row % 16), so that the sixteen
 // rows of an MFMA operand are read from different banks.  A segment holds four k-steps; the piece of k-step q of a segment
@@ -1101,11 +1104,11 @@ __global__ __launch_bounds__(kFfnThreads, (BIG || WF != 0) ? 2 : kWgPerCuSmall) 
 {
     // staged token tile, or the K-slice partial sums
     constexpr int TB = staged_tokens(BIG, WF);
-    // (the alignment puts them ahead of the tables: they have to end at 64 KiB)
-    __shared__ __attribute__((aligned(1024))) char stage0[kStageBuffer], stage1[kStageBuffer];
-    static_assert(2 * kStageBuffer <= 65536, "loads into LDS address 64 KiB");
+    __shared__ __attribute__((aligned(kStageAlign))) char stage0[kStageBuffer], stage1[kStageBuffer];
     __shared__ int rowoff[TB];   // staged path: element offset of each token's B row, -1 = none
     __shared__ int outrow[TB];   // staged path: output row of each token, -1 = none
+    static_assert(2 * kStageBuffer <= 65536 && kStageBuffer % kStageAlign == 0 && sizeof(rowoff) + sizeof(outrow) < kStageAlign,
+                  "loads into LDS address 64 KiB; the build checks the placement by the segment's size");
     const int b = blockIdx.x + fp.block0;
     if (b < fp.gu_blocks) {
         // Gate/up workgroups take four row tiles, one per wave, and the dispatcher hands workgroups to the CUs
