@@ -785,7 +785,7 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
     }
     auto load_x = [&](char *buf, int c) {
         int wvx = wv;
-        asm volatile("" : "+s"(wvx));   // (sixteen LDS addresses kept in scalar registers would spill others)
+        asm volatile("" : "+s"(wvx), "+s"(c));   // (addresses of every load kept in scalar registers would spill others)
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
             const int grp = wvx * (LPW / SEG) + i / SEG, seg = i % SEG;
