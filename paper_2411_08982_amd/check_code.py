@@ -4,6 +4,11 @@ Placement: the kernel's two LDS buffers for token rows are the destination of di
 bits wide, so they have to lie in the first 64 KiB.  The language does not say where a __shared__ array goes.  Both are
 aligned to kStageAlign and the kernel's other arrays are smaller than that together: whatever lies ahead of or between
 the buffers moves the end of the segment by a whole kStageAlign, and the segment's size shows it.
+
+Waits: a wave reports its pieces of a chunk of token rows at a barrier, before which they must have landed.  The kernel waits
+until at most as many loads are outstanding as it has issued behind them, a number that follows from its source as long as
+the compiler neither drops nor merges loads.  They are counted again in the machine code, ahead of every barrier behind a
+direct-to-LDS load, in the order of the listing (the kernel's loops around them are laid out straight).
 """
 from __future__ import annotations
 
@@ -23,7 +28,7 @@ def _run(tool, *args, cwd=None):
 
 
 def code_object_texts(lib_path: str):
-    """The metadata notes of every gfx950 code object in the library that holds the kernel."""
+    """(metadata notes, disassembly) of every gfx950 code object in the library that holds the kernel."""
     with tempfile.TemporaryDirectory() as d:
         os.symlink(os.path.abspath(lib_path), os.path.join(d, "lib.so"))   # (the extracted objects land beside it)
         _run("llvm-objdump", "--offloading", "lib.so", cwd=d)
@@ -32,7 +37,7 @@ def code_object_texts(lib_path: str):
                 continue
             notes = _run("llvm-readelf", "--notes", name, cwd=d)
             if KERNEL in notes:
-                yield notes
+                yield notes, _run("llvm-objdump", "-d", name, cwd=d)
 
 
 def check_placement(notes: str) -> int:
@@ -45,9 +50,42 @@ def check_placement(notes: str) -> int:
     return len(kernels)
 
 
+def check_waits(listing: str) -> int:
+    """Raises if a barrier of the kernel can be reached before the direct-to-LDS loads ahead of it have landed; the number of
+    such barriers."""
+    barriers = 0
+    name = ""
+    behind = None         # memory operations issued behind the last direct-to-LDS load, None = none to wait for
+    landed = False
+    for line in listing.splitlines():
+        head = re.match(r"[0-9a-f]+ <(\S+)>:", line)
+        if head:
+            name, behind = head.group(1), None
+            continue
+        words = line.split("//")[0].split()
+        if not words or KERNEL not in name:
+            continue
+        op = words[0]
+        if op.startswith(("buffer_", "global_", "flat_", "scratch_")):
+            if words[-1] == "lds":
+                behind, landed = 0, False
+            elif behind is not None:
+                behind += 1
+        elif op == "s_waitcnt" and behind is not None:
+            count = re.search(r"vmcnt\((\d+)\)", line)
+            landed = landed or (count is not None and int(count.group(1)) <= behind)
+        elif op == "s_barrier" and behind is not None:
+            if not landed:
+                raise RuntimeError(f"{name}: a barrier {behind} loads behind direct-to-LDS loads that nothing waits for")
+            barriers += 1
+            behind = None
+    return barriers
+
+
 def check(lib_path: str) -> None:
-    n = 0
-    for notes in code_object_texts(lib_path):
-        n += check_placement(notes)
-    if n == 0:
-        raise RuntimeError(f"{lib_path}: no {KERNEL} found")
+    kernels = barriers = 0
+    for notes, listing in code_object_texts(lib_path):
+        kernels += check_placement(notes)
+        barriers += check_waits(listing)
+    if kernels == 0 or barriers < kernels:
+        raise RuntimeError(f"{lib_path}: {kernels} kernels and {barriers} barriers found: the checks do not read this library")

@@ -22,6 +22,7 @@
 // Launches: the expert kernel (once or twice) and a small combine.
 
 #include <atomic>
+#include <type_traits>
 
 #include "../../include/lynx_bench.h"
 #include "lynx_plan.h"
@@ -731,6 +732,14 @@ struct StagedShape {
     static constexpr int BQ = S == 4 && NT == 8 ? 2 : 4;   // token fragments read ahead (the same at 2 and 4)
 };
 
+// Waits until at most N of the wave's loads are outstanding (they return in order).
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    constexpr int n = N < 63 ? N : 63;   // (the counter's field; a smaller count waits for more)
+    __builtin_amdgcn_s_waitcnt((n & 15) | (n >> 4) << 14 | 7 << 4 | 15 << 8);   // loads only
+}
+
 // KEEP: the weights are read by another workgroup too (an expert with several token blocks): cached loads.
 template <bool DUAL, int RT, int NT, int WF, bool KEEP>
 __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowoff, const int *outrow, char *stage0, char *stage1)
@@ -798,12 +807,12 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
     int xaddr[4];                                // this lane's place in a block, for each of the block's four k-steps
 #pragma unroll
     for (int q = 0; q < 4; ++q) xaddr[q] = (lane & 15) * 256 + (stage_piece<WF>(q) ^ (lane & 15)) * 16;
-    // The wave's own pieces of the chunk in buf have landed (it reads the last of them: the compiler waits for exactly
-    // that load), and then everybody's have, and nobody reads the other buffer any more.
-    auto chunk_ready = [&](const char *buf) {
-        const unsigned v = *reinterpret_cast<const unsigned *>(
-            buf + (((wv + 1) * (LPW / SEG) - 1) / 4 * SEG + SEG - 1) * 4096 + (((wv + 1) * (LPW / SEG) - 1) & 3) * 1024 + lane * 16);
-        asm volatile("" ::"v"(v) : "memory");
+    // The wave's own pieces of the chunk requested last have landed, and then everybody's have, and nobody reads the other
+    // buffer any more.  The count is of the loads that the wave has issued behind those pieces (`tiles` turns of load_w;
+    // every load of the loop sits between scheduling fences).  The build counts them again in the machine code.
+    constexpr int kLoadsPerTile = S + (WF == 2 ? SG : 0);
+    auto chunk_ready = [&](auto tiles) {
+        wait_loads<tiles.value * kLoadsPerTile>();
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -832,7 +841,7 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < D; ++j) load_w(j, j);
-    chunk_ready(stage0);
+    chunk_ready(std::integral_constant<int, D>());
 
     for (int s0 = 0; s0 < KT; s0 += 2 * TPC) {
 #pragma unroll
@@ -880,7 +889,7 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
                 load_w(u, s + D);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            chunk_ready(nxt);
+            chunk_ready(std::integral_constant<int, TPC>());
         }
     }
     if (!wave_active) return;

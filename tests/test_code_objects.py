@@ -15,7 +15,7 @@ def texts():
 
 
 def test_token_row_buffers_lie_in_the_first_64_kib(texts):
-    assert sum(check_code.check_placement(notes) for notes in texts) >= 9   # three weight formats, three sizes at least
+    assert sum(check_code.check_placement(notes) for notes, _ in texts) >= 9   # three weight formats, three sizes at least
 
 
 @pytest.mark.parametrize("size,ok", [(65536, True), (66560, True), (65536 + 4096, False), (66560 + 4096, False), (32768, False)])
@@ -32,3 +32,23 @@ def test_other_placements_are_refused(size, ok):
     else:
         with pytest.raises(RuntimeError, match="first 65536"):
             check_code.check_placement(notes)
+
+
+def test_barriers_wait_for_the_loads_into_lds(texts):
+    assert sum(check_code.check_waits(listing) for _, listing in texts) >= 100   # several passes per kernel, two buffers each
+
+
+@pytest.mark.parametrize("between,wait,ok", [(3, "s_waitcnt vmcnt(3)", True), (3, "s_waitcnt vmcnt(4)", False), (3, "", False),
+                                             (3, "s_waitcnt lgkmcnt(0)", False), (0, "s_waitcnt vmcnt(0) lgkmcnt(0)", True),
+                                             (5, "s_waitcnt vmcnt(2) lgkmcnt(1)", True)])
+def test_a_missing_wait_is_refused(between, wait, ok):
+    body = ["buffer_load_dwordx4 v2, s[24:27], 0 offen lds  // 00000000D44C: E05D1000 80060002"]
+    body += ["buffer_load_dwordx4 v[4:7], v3, s[28:31], 0 offen nt  // 00000000D474: E05D1000"] * between
+    body += [wait + "  // 00000000D494:"] * bool(wait) + ["s_barrier"]
+    listing = "0000000000006700 <_ZN4lynx10ffn_kernelILi1ELi2ELi0EEEvNS_9FfnParamsE>:\n" + "\n".join("\t" + l for l in body)
+    if ok:
+        assert check_code.check_waits(listing) == 1
+    else:
+        with pytest.raises(RuntimeError, match="nothing waits"):
+            check_code.check_waits(listing)
+    assert check_code.check_waits(listing.replace("ffn_kernel", "other_kernel")) == 0
