@@ -1011,7 +1011,10 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
         }
         __syncthreads();
     };
-    if (w.te_all <= kDirectMaxTokens) {
+    // (With K in four slices a chunk of sixteen rows holds half a turn of the ring of the quantised formats.  Such kernels are
+    // for at most eight tokens, but an assignment that sends a token to one expert twice can still give it more rows.)
+    constexpr int kDirectRows = KW == kFfnWaves && WF != 0 ? kDirectMaxTokens / 2 : kDirectMaxTokens;
+    if (w.te_all <= kDirectRows) {
         // Direct path.  The weight stream starts before h is waited for, and the next unit's first tiles are requested
         // before this unit's results are exchanged and stored.
         const TokenStage<KW> ts(w.Te);
