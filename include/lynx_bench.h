@@ -61,7 +61,7 @@ int lynx_read_probe(const void *buf, size_t bytes, int non_temporal, uint32_t *s
  *   LYNX_DEBUG_DOWN_ITEM_UNITS  most row units per down-projection work item (a power of two; default 1; batches of
  *                               at most 64 tokens)
  *   LYNX_DEBUG_DOWN_K_WAVES     K slices that the four waves of a down-projection workgroup form (1, 2, or 4 for batches
- *                               of at most 8 tokens; default 0 = the library's rule)
+ *                               of at most 16 tokens; default 0 = the library's rule)
  */
 #define LYNX_DEBUG_SPIN_LIMIT 1
 #define LYNX_DEBUG_TARGET_BIAS 2

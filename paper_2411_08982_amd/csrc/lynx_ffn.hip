@@ -1464,7 +1464,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     const int max_experts = (int)min((long)N, (long)T * k) + n_shared;
     s.kwd = pick_k_waves(F, H, false, T, max_experts, 16 >> format);
     const int forced = g_tune.dn_kw.load();
-    if (forced == 1 || forced == 2 || (forced == 4 && T <= 8)) s.kwd = forced;
+    if (forced == 1 || forced == 2 || (forced == 4 && T <= kDirectMaxTokens)) s.kwd = forced;
     // Gate/up units of 128 rows when the experts hold more than 64 tokens on average: fewer, longer workgroups that stage
     // the tokens half as often (Mixtral shapes, 1000 tokens: 1156 -> 1126 us; DeepSeek-V2-Lite shapes, 1000: 343 -> 333).
     // With fewer tokens the weight stream is the bound and the finer units fill the chip more evenly (Mixtral shapes, 128

@@ -193,3 +193,19 @@ def test_more_rows_than_tokens(L, fmt, H, F, T, per_expert):
     torch.cuda.synchronize()
     err = row_rel_err(host(y), ref).max()
     assert err <= Y_TOL, f"max row error {err:.3e}"
+
+
+# The K slices of a down workgroup as the knob sets them, where the library's rule would choose another number.
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "fp4"])
+@pytest.mark.parametrize("slices,case", [(4, (16, (16, 15, 9, 1), 384, 1024, 1, 640)), (4, (11, (11, 8, 3), 256, 4096, 0, 0)),
+                                         (1, (8, (8, 5), 256, 2048, 1, 128)), (2, (130, (130, 77, 40, 12), 384, 640, 1, 256)),
+                                         (1, (97, (97, 81, 5), 512, 256, 0, 0))])
+def test_k_slices_set_by_the_knob(L, fmt, slices, case):
+    from paper_2411_08982_amd import binding as B
+    T, counts, H, F, S, Fs = case
+    dH, dF = RAGGED[fmt]
+    L.lynx_debug_set(B.DEBUG_DOWN_K_WAVES, slices)
+    try:
+        run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs)
+    finally:
+        L.lynx_debug_set(B.DEBUG_DOWN_K_WAVES, 0)
