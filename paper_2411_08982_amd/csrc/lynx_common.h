@@ -186,7 +186,7 @@ constexpr int kWsMember = kWsActive + LYNX_MAX_N;          // LYNX_MAX_N * LYNX_
 constexpr int kWsOldDone = kWsMember + LYNX_MAX_N * (LYNX_MAX_T / 32);   // (1024 words free)
 constexpr int kWsFlags = kWsOldDone + 1024;               // FFN: bit 0 = a bounded wait ran out
 constexpr int kWsPlanHdr = kWsFlags + 16;                  // FFN work plan (lynx_plan.h): header, 16 words
-constexpr int kPlanMaxBlocks = 512;                        // most (expert, token block) pairs: LYNX_MAX_N + LYNX_MAX_T * LYNX_MAX_K / 128, rounded up
+constexpr int kPlanMaxBlocks = 512;                        // most (expert, token block) pairs: one per expert and one per 64 pairs (lynx_plan.h checks it)
 constexpr int kWsPlanBlk = kWsPlanHdr + 16;                // one record of four words per (expert, token block) pair
 constexpr int kWsPlanPairs = kWsPlanBlk + 4 * kPlanMaxBlocks;   // 16 pair ids of 16 bits per block: 8 words each
 // FFN: gate/up completion counters, of the routed experts and of the (shared expert, token block) pairs.  Atomic adds and

@@ -26,6 +26,8 @@ constexpr int kDirectMaxTokens = 16;         // experts with more tokens take th
 constexpr int kTokBlock = 64;                // tokens per pass of the staged path (batches of up to 64 tokens)
 constexpr int kTokBlockBig = 128;            // the same in the bf16 kernels launched for larger batches
 
+static_assert(LYNX_MAX_N + LYNX_MAX_T * LYNX_MAX_K / kTokBlock <= kPlanMaxBlocks, "the plan must hold every block of a batch");
+
 // What the host knows of the FFN launch when the plan is built.
 struct PlanShape {
     int units_gu;    // gate/up work items per (expert, token block): 64-row units of the F rows; 0 = build no plan
@@ -116,6 +118,7 @@ __device__ __forceinline__ void plan_file_pair(const PlanShape &ps, const int *b
                                                int32_t *__restrict__ ws)
 {
     if (ps.units_gu <= 0 || te > kDirectMaxTokens) return;
+    if (blk0[e] >= kPlanMaxBlocks) return;   // (ranges of a caller that overlap: build_plan has no record for the block either)
     reinterpret_cast<uint16_t *>(ws + kWsPlanPairs)[blk0[e] * kDirectMaxTokens + i] = (uint16_t)p;
 }
 

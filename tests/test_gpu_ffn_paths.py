@@ -209,3 +209,28 @@ def test_k_slices_set_by_the_knob(L, fmt, slices, case):
         run_case(L, fmt, T, counts, H + dH, F + dF, S, Fs)
     finally:
         L.lynx_debug_set(B.DEBUG_DOWN_K_WAVES, 0)
+
+
+def test_overlapping_expert_ranges_stay_inside_the_plan(L):
+    """expert_offsets that lynx_permute cannot have written: every second expert claims all pairs, which makes more token
+    blocks than the work plan has records, and the last expert, behind them, a few (its pair ids would be filed).  What
+    the plan does not hold is not computed; nothing may be written past its tables."""
+    T, k, N, H, F = 64, 16, 140, 32, 4128             # F: two launches, no waits for blocks that the plan leaves out
+    P = T * k
+    print(f"ffn overlapping ranges T={T} k={k} N={N}", flush=True)
+    assert L.lynx_moe_ffn_launches(T, F) == 2
+    offsets = np.zeros(N + 1, np.int32)
+    offsets[1:138:2] = P                              # 69 experts of 16 blocks: 1104 blocks, the plan holds 512
+    offsets[138:] = [0, 0, 9]
+    W = [torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((N, F, H), (N, F, H), (N, H, F))]
+    idx = dev(np.tile(np.arange(k, dtype=np.int32), (T, 1)))
+    p = dict(offsets=dev(offsets), perm=dev(np.arange(P, dtype=np.int32)), active=dev(np.arange(N, dtype=np.int32)),
+             num_active=dev(np.array([N], np.int32)))
+    ws = L.new_workspace(T, H, F, N, k)
+    ws.fill_(0xFF)
+    gate = torch.ones((T, k), dtype=torch.float32, device="cuda")
+    L.lynx_moe_ffn(torch.ones((T, H), dtype=torch.bfloat16, device="cuda"), *L.lynx_pack_weights(*W), idx, gate, p, N, F,
+                   workspace=ws)
+    torch.cuda.synchronize()
+    # words 20032 to 22080: the counters of shared experts, of which there are none
+    assert np.all(host(ws.view(torch.int32))[20032:22080] == -1)
