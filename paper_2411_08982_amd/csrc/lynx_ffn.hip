@@ -1185,6 +1185,12 @@ __global__ __launch_bounds__(256) void plan_kernel(const int32_t *__restrict__ o
     }
 }
 
+// n values to an aligned place, from one that need not be (n a multiple of 32).
+__global__ __launch_bounds__(256) void realign_kernel(const uint16_t *__restrict__ x, uint16_t *__restrict__ out, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) out[i] = x[i];
+}
+
 // y[t] = sum_j gate[t,j] * o[t*k+j] + sum_s o[P + s*T + t].  If a workgroup of the expert kernel gave up a bounded wait
 // (flags != 0: some rows of o may then be computed from incomplete intermediate vectors) every element of y becomes NaN
 // and *status (if given) 1, else *status 0: a failed hand-over cannot pass for a result.
@@ -1712,7 +1718,17 @@ int moe_ffn_impl(const uint16_t *x_bf16, const uint16_t *Wgu_packed, const uint1
     float *obuf = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + ws.o_off);
     int32_t *rws = reinterpret_cast<int32_t *>(workspace);
     hipStream_t st = (hipStream_t)stream;
-    const FfnShape shape = ffn_shape(T, H, F, N, k, n_shared, q8 ? q8->format : 0);
+    FfnShape shape = ffn_shape(T, H, F, N, k, n_shared, q8 ? q8->format : 0);
+    if (reinterpret_cast<uintptr_t>(x_bf16) % 16 != 0) {
+        // Token rows of a tensor that starts at an odd place of its storage.  The loads into LDS take 16 bytes per lane and
+        // are not known to take them from everywhere, so the rows are copied first: to the place of the per-pair outputs,
+        // which the down projection writes, in a launch of its own then.
+        hipLaunchKernelGGL(realign_kernel, dim3(1024), dim3(256), 0, st, x_bf16, reinterpret_cast<uint16_t *>(obuf), (size_t)T * H);
+        rc = check_launch("lynx_moe_ffn(realign)");
+        if (rc != LYNX_OK) return rc;
+        x_bf16 = reinterpret_cast<const uint16_t *>(obuf);
+        shape.single = false;
+    }
     if (!plan_ready) {
         hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(256), 0, st, expert_offsets, perm, N, T * k, shape.plan, rws);
         rc = check_launch("lynx_moe_ffn(plan)");

@@ -234,3 +234,35 @@ def test_overlapping_expert_ranges_stay_inside_the_plan(L):
     torch.cuda.synchronize()
     # words 20032 to 22080: the counters of shared experts, of which there are none
     assert np.all(host(ws.view(torch.int32))[20032:22080] == -1)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "fp4"])
+@pytest.mark.parametrize("T,counts,S", [(40, (40, 33, 9, 1), 1), (130, (130, 100, 20), 0), (7, (7, 3), 1)])
+def test_token_rows_at_odd_places(L, fmt, T, counts, S):
+    """x is a contiguous tensor that starts one, two or four elements into its storage: the same result, bit for bit."""
+    H, F, N, k = 384, 256, len(counts), len(counts)
+    print(f"ffn odd places {fmt} T={T} counts={counts}", flush=True)
+    rng = np.random.default_rng([T, H, F])
+    idx = np.full((T, k), -1, np.int32)
+    for e, c in enumerate(counts):
+        idx[rng.permutation(T)[:c], e] = e
+    gate = dev(rng.uniform(0.1, 1.0, (T, k)).astype(np.float32))
+    mk = lambda *shape: to_bf16_dev(wl.f32_to_bf16_bits((rng.standard_normal(shape) * 0.05).astype(np.float32)))
+    pack, ffn = {"bf16": (L.lynx_pack_weights, L.lynx_moe_ffn), "fp8": (L.lynx_quantize_weights_fp8, L.lynx_moe_ffn_fp8),
+                 "fp4": (L.lynx_quantize_weights_fp4, L.lynx_moe_ffn_fp4)}[fmt]
+    W = pack(mk(N, F, H), mk(N, F, H), mk(N, H, F))
+    Sw = pack(mk(S, F, H), mk(S, F, H), mk(S, H, F)) if S else None
+    weights = lambda w: tuple(w) if fmt == "bf16" else (w,)
+    idx_d = dev(idx)
+    p = L.lynx_permute(idx_d, N)
+    shared = (weights(Sw) if S else weights(None if fmt != "bf16" else (None, None))) + (S, F if S else 0)
+    x = to_bf16_dev(wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32)))
+    want = host(ffn(x, *weights(W), idx_d, gate, p, N, F, *shared))
+    assert np.all(np.isfinite(want)) and np.any(want)
+    for off in (1, 2, 4):
+        room = torch.empty(T * H + 8, dtype=torch.bfloat16, device="cuda")
+        odd = room[off:off + T * H].view(T, H)
+        odd.copy_(x)
+        assert odd.is_contiguous() and odd.data_ptr() % 16 == 2 * off
+        got = host(ffn(odd, *weights(W), idx_d, gate, p, N, F, *shared))
+        assert np.array_equal(got, want), off
