@@ -183,8 +183,9 @@ constexpr int kWsTickets = 0;                              // 16 words
 constexpr int kWsOrder = 16;                               // LYNX_MAX_N words
 constexpr int kWsActive = kWsOrder + LYNX_MAX_N;           // LYNX_MAX_N words
 constexpr int kWsMember = kWsActive + LYNX_MAX_N;          // LYNX_MAX_N * LYNX_MAX_T/32 words
-constexpr int kWsOldDone = kWsMember + LYNX_MAX_N * (LYNX_MAX_T / 32);   // (1024 words free)
-constexpr int kWsFlags = kWsOldDone + 1024;               // FFN: bit 0 = a bounded wait ran out
+constexpr int kWsGap = kWsMember + LYNX_MAX_N * (LYNX_MAX_T / 32);   // 1024 words unused: the flags keep the place callers know
+constexpr int kWsFlags = kWsGap + 1024;                    // FFN: bit 0 = a bounded wait ran out
+static_assert(kWsFlags == 9744, "the binding's WAIT_FLAG_WORD");
 constexpr int kWsPlanHdr = kWsFlags + 16;                  // FFN work plan (lynx_plan.h): header, 16 words
 constexpr int kPlanMaxBlocks = 512;                        // most (expert, token block) pairs: one per expert and one per 64 pairs (lynx_plan.h checks it)
 constexpr int kWsPlanBlk = kWsPlanHdr + 16;                // one record of four words per (expert, token block) pair

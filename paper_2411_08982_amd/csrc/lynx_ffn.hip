@@ -35,10 +35,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kFfnThreads = 256;
 constexpr int kFfnWaves = kFfnThreads / kWave;
 constexpr int kPF = 8;                       // staged path: weight tiles in flight per wave and matrix
-#ifndef LYNX_PFD
-#define LYNX_PFD 8
-#endif
-constexpr int kPFD = LYNX_PFD;               // direct path: the same (most; see DirectDepth for the depth per format)
+constexpr int kPFD = 8;                      // direct path: the same (most; see DirectDepth for the depth per format)
 // Two LDS buffers for token rows.  They are two arrays, not halves of one: the compiler tells loads into the one from reads of
 // the other by that, and does not wait for them.  They have to lie in the first 64 KiB, which loads into LDS can address.
 // The compiler places them (by falling alignment, as it happens); the build compares the size of the kernel's LDS segment:
@@ -298,18 +295,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 }
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return (g / (1.0f + __expf(-g))) * u; }
-__device__ __forceinline__ uint4 zero4() { return make_uint4(0u, 0u, 0u, 0u); }
-__device__ __forceinline__ uint4 sel4(bool keep, uint4 v) { return keep ? v : zero4(); }
-
-template <int NT>
-__device__ __forceinline__ void clear_acc(f32x4 (&accg)[NT], f32x4 (&accu)[NT])
-{
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        accg[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        accu[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-}
 
 // D fragment of v_mfma_f32_16x16x32: lane holds token column (lane & 15) and output rows
 // 4*(lane >> 4) .. +3 of the wave's 16.  gate/up: h = silu(g) * u rounded to bf16; down: fp32.
@@ -355,15 +340,10 @@ __device__ __forceinline__ void epilogue(const f32x4 (&accg_in)[NT], const f32x4
 // draining the queue.
 // ---------------------------------------------------------------------------------------------------
 
-// The address passes through an empty asm so that the compiler treats every ring load as a distinct,
-// unmovable-by-value-numbering load: otherwise it merges the prefetch for the next turn of the ring
+// The offsets of the ring_load_* functions pass through an empty asm so that the compiler treats every ring load as a
+// distinct, unmovable-by-value-numbering load: otherwise it merges the prefetch for the next turn of the ring
 // with the loads of that turn and issues them only when they are needed.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 ring_load(const uint4 *__restrict__ base, int index)
-{
-    asm volatile("" : "+v"(index));
-    return base[index];
-}
 
 // B operand (token rows).  For the down projection these are the intermediate vectors that gate/up workgroups
 // of the same launch have written with device-coherent stores.  Plain (cached) loads are right for them: caches
@@ -418,8 +398,6 @@ __device__ __forceinline__ uint4 ring_load_weights(BufferRsrc rs, int index, boo
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Two weight streams share every B fragment: gate and up tiles (interleaved: second = 64, step = 128) or,
-// for the down projection, two consecutive row tiles (second = one row tile further, step = 64).
 // 16 E4M3 codes (one lane's piece of a 64-column tile) -> two MFMA operands of 8 bf16 (columns 0-7 and 8-15 of
 // the lane's group).  The hardware conversion gives fp32; an E4M3 value has 3 mantissa bits, so the upper half
 // of the fp32 IS the bf16, exactly.
@@ -486,7 +464,9 @@ struct DirectDepth {
     static constexpr int value = WF == 2 ? 4 : kPFD;
 };
 
-// Where a wave of the direct path streams from: needs the expert, not its tokens.
+// Where a wave of the direct path streams from: needs the expert, not its tokens.  Two weight streams share every token
+// fragment: gate and up tiles (interleaved: second = 64, step = 128) or, for the down projection, two consecutive row
+// tiles (second = one row tile further, step = 64).
 struct DirectPlan {
     const uint4 *Wb;     // the wave's first weight tile (the same for all lanes)
     const uint2 *Sl;     // MXFP4: this lane's scale dwords of the wave's row group, k-tile group 0
@@ -1106,13 +1086,12 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
     }
 }
 
-#ifndef LYNX_WGCU
-#define LYNX_WGCU 2
-#endif
-constexpr int kWgPerCuSmall = LYNX_WGCU;   // workgroups per CU of the kernels for batches of at most 64 tokens
+// Workgroups per CU: the registers (256 per wave) and the LDS buffers both come to two.  The dispatcher fills a CU up to its
+// occupancy limit before it moves on, so a third one would leave CUs idle in a grid that is small compared with the chip.
+constexpr int kWgPerCu = 2;
 
 template <int KWD, int BIG, int WF>
-__global__ __launch_bounds__(kFfnThreads, (BIG || WF != 0) ? 2 : kWgPerCuSmall) void ffn_kernel(FfnParams fp)
+__global__ __launch_bounds__(kFfnThreads, kWgPerCu) void ffn_kernel(FfnParams fp)
 {
     // staged token tile, or the K-slice partial sums
     constexpr int TB = staged_tokens(BIG, WF);
@@ -1121,6 +1100,9 @@ __global__ __launch_bounds__(kFfnThreads, (BIG || WF != 0) ? 2 : kWgPerCuSmall) 
     __shared__ int outrow[TB];   // staged path: output row of each token, -1 = none
     static_assert(2 * kStageBuffer <= 65536 && kStageBuffer % kStageAlign == 0 && sizeof(rowoff) + sizeof(outrow) < kStageAlign,
                   "loads into LDS address 64 KiB; the build checks the placement by the segment's size");
+    constexpr int kLdsPerCu = 160 * 1024;
+    static_assert(2 * kStageBuffer * kWgPerCu + kStageAlign <= kLdsPerCu && 2 * kStageBuffer * (kWgPerCu + 1) > kLdsPerCu,
+                  "workgroups per CU");
     const int b = blockIdx.x + fp.block0;
     if (b < fp.gu_blocks) {
         // Gate/up workgroups take four row tiles, one per wave, and the dispatcher hands workgroups to the CUs
@@ -1520,24 +1502,10 @@ static void set_tiles(GemmParams &p, int units_r, int rows_per_wg, int routed_it
 
 static unsigned grid_blocks(const GemmParams &p) { return (unsigned)(p.shared_blocks + p.routed_blocks); }
 
-// Workgroups per CU.  The dispatcher fills a CU up to its occupancy limit before it moves on, so a grid
-// that is small compared with the chip (few invoked experts) would leave CUs idle while others hold three
-// workgroups.  A dynamic-LDS pad makes exactly kWgPerCu workgroups fit a CU, which spreads such grids.
-constexpr int kLdsPerCu = 160 * 1024;
-
 template <int KWD, int BIG, int WF>
-static int launch_padded(const FfnParams &fp, unsigned blocks, hipStream_t st)
+static void launch_kernel(const FfnParams &fp, unsigned blocks, hipStream_t st)
 {
-    constexpr int kWgPerCu = (BIG || WF != 0) ? 2 : kWgPerCuSmall;
-    constexpr int kLdsTargetPerWg = kWgPerCu == 2 ? 56 * 1024 : kLdsPerCu / kWgPerCu / 1024 * 1024;   // (at most 64 KiB per workgroup)
-    static_assert(kLdsTargetPerWg * (kWgPerCu + 1) > kLdsPerCu && kLdsTargetPerWg * kWgPerCu <= kLdsPerCu, "LDS pad");
-    // what the kernel declares itself: the stage and the two token tables
-    constexpr int TB = staged_tokens(BIG, WF);
-    constexpr int kStatic = 2 * kStageBuffer + 2 * 4 * TB;
-    constexpr int pad = kLdsTargetPerWg > kStatic ? kLdsTargetPerWg - kStatic : 0;
-    static_assert((kStatic + pad) * kWgPerCu <= kLdsPerCu, "the workgroups must fit a CU");
-    hipLaunchKernelGGL((ffn_kernel<KWD, BIG, WF>), dim3(blocks), dim3(kFfnThreads), pad, st, fp);
-    return LYNX_OK;
+    hipLaunchKernelGGL((ffn_kernel<KWD, BIG, WF>), dim3(blocks), dim3(kFfnThreads), 0, st, fp);
 }
 
 // One launch for both projections, or one each (the same kernel over its gate/up and its down workgroups)?
@@ -1569,20 +1537,20 @@ static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
         fp.block0 = part == 0 ? 0 : fp.gu_blocks;
         const unsigned blocks = sh.single ? (unsigned)fp.gu_blocks + dn_blocks : part == 0 ? (unsigned)fp.gu_blocks : dn_blocks;
         if (sh.big == 2 && sh.kwd == 1)
-            rc = launch_padded<1, 2, WF>(fp, blocks, st);
+            launch_kernel<1, 2, WF>(fp, blocks, st);
         else if (sh.big == 2)
-            rc = launch_padded<2, 2, WF>(fp, blocks, st);
+            launch_kernel<2, 2, WF>(fp, blocks, st);
         else if (sh.big && sh.kwd == 1)
-            rc = launch_padded<1, 1, WF>(fp, blocks, st);
+            launch_kernel<1, 1, WF>(fp, blocks, st);
         else if (sh.big)
-            rc = launch_padded<2, 1, WF>(fp, blocks, st);
+            launch_kernel<2, 1, WF>(fp, blocks, st);
         else if (sh.kwd == 4)
-            rc = launch_padded<4, 0, WF>(fp, blocks, st);
+            launch_kernel<4, 0, WF>(fp, blocks, st);
         else if (sh.kwd == 2)
-            rc = launch_padded<2, 0, WF>(fp, blocks, st);
+            launch_kernel<2, 0, WF>(fp, blocks, st);
         else
-            rc = launch_padded<1, 0, WF>(fp, blocks, st);
-        if (rc == LYNX_OK) rc = check_launch("lynx_moe_ffn(gate/up, down)");
+            launch_kernel<1, 0, WF>(fp, blocks, st);
+        rc = check_launch("lynx_moe_ffn(gate/up, down)");
     }
     return rc;
 }
