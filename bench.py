@@ -4,7 +4,9 @@
 A step = one pass of the whole hot path (lynx_moe_layer = route -> affinity_bin -> permute -> moe_ffn, once per layer)
 over one decode batch, inputs already resident in HBM.  Prints ONE JSON line.
 
-Without --config (what the driver runs) the line covers every benchmark configuration:
+Without --config every benchmark configuration is measured.  The line on stdout holds the headline (and the microseconds
+of the other stack settings, `stack_us`), short enough to be kept whole where only the end of a program's output is kept; the
+report with every configuration in it goes to stderr as a JSON line of its own, and to a file with --report:
   * headline (`value`, `config`, `roofline`, `cpu_baseline`): the largest configuration that fits one GPU, the chained
     stack of 48 Qwen3-30B-A3B-shaped MoE layers (58 GB of bf16 expert weights resident, own router and weights per
     layer, x <- bf16(x + y) between layers), 512 decode tokens, remap aggressive, replayed as one HIP graph;
@@ -71,6 +73,7 @@ def parse():
                     help="with --config: time a chained stack of this many layers (own router and weights each, "
                          "x <- bf16(x + y) between them) as a whole, eagerly and as one HIP graph")
     ap.add_argument("--stack-layers", type=int, default=48, help="layers of the stack in the full report")
+    ap.add_argument("--report", default="", metavar="FILE", help="write the full report to this file as well")
     ap.add_argument("--pmc-calibration", action="store_true",
                     help="before the steps, run a plain 1 GiB read + 1 GiB write elementwise kernel three times: under "
                          "rocprofv3 --pmc its FETCH_SIZE / WRITE_SIZE readings give the counters' scale")
@@ -665,7 +668,7 @@ def single_layer_line(args, cfg, wl, torch, full=True):
 
 
 def full_report(args, wl, torch):
-    """Every benchmark configuration in one line; the stack is the headline."""
+    """Every benchmark configuration; the stack is the headline."""
     t_start = time.perf_counter()
     cfg4 = wl.CONFIGS["qwen3"]
     out = stack_line(args, cfg4, wl, torch, args.stack_layers, list(cfg4.batches), PRESET_NAMES,
@@ -696,6 +699,14 @@ def full_report(args, wl, torch):
     return out
 
 
+def headline_line(report):
+    """The part of the full report that goes to stdout."""
+    line = {k: v for k, v in report.items() if k not in ("stack", "configs", "mixtral_T8")}
+    line["stack_us"] = {name: v["us_graph_wall"] for name, v in report["stack"].items()}
+    line["mixtral_T8_us"] = report["mixtral_T8"]["value"]
+    return line
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -714,7 +725,12 @@ def main():
         L_.lynx_debug_set(B_.DEBUG_DOWN_ITEM_UNITS, args.down_item_units)
         L_.lynx_debug_set(B_.DEBUG_DOWN_K_WAVES, args.down_k_waves)
     if not args.config:
-        out = full_report(args, wl, torch)
+        report = full_report(args, wl, torch)
+        print(json.dumps(report), file=sys.stderr)
+        if args.report:
+            with open(args.report, "w") as fh:
+                json.dump(report, fh, indent=1)
+        out = headline_line(report)
     elif args.stack > 0:
         cfg = wl.CONFIGS[args.config]
         table = layer_policy(args.layer_policy, args.stack, args.preset) if args.layer_policy else None

@@ -39,3 +39,20 @@ def test_layer_policy_table():
     for bad in ("0-9:off", "1:sometimes", "3-1:off"):
         with pytest.raises(ValueError):
             bench.layer_policy(bad, 4, "off")
+
+
+def test_the_line_of_the_full_report_is_short():
+    """What goes to stdout keeps the agreed fields and stays below 4000 characters however many settings were measured."""
+    import json
+    sys.path.insert(0, ROOT)
+    import bench
+    agreed = dict(metric="MoE-stack decode us/batch (48 chained layers)", value=4000.1, unit="us/batch", n_gpus=1, steps=20,
+                  warmup=5, ms_per_step=4.0001, higher_is_better=False, scaling="weak", vs_baseline=None, dtype="bf16",
+                  data="synthetic", config={"workload": "w" * 600}, roofline={"kernel": "k" * 600}, cpu_baseline={"sample": "s" * 400})
+    entry = dict(us_graph_wall=12345.6, detail="d" * 400)
+    report = dict(agreed, stack={f"T{t}_{p}": entry for t in (32, 128, 256, 512) for p in bench.PRESET_NAMES},
+                  configs=[dict(us=100.0, detail="d" * 400)] * 45, mixtral_T8=dict(value=120.5, detail="d" * 2000))
+    line = bench.headline_line(report)
+    assert all(line[k] == v for k, v in agreed.items())
+    assert line["stack_us"]["T512_aggressive"] == 12345.6 and line["mixtral_T8_us"] == 120.5
+    assert len(json.dumps(line)) < 4000
