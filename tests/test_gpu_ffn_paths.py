@@ -81,13 +81,23 @@ LARGE = [
     (97, (97, 0, 81, 5, 49), 512, 256, 1, 768),            # an expert that is not invoked; a wide shared expert (K slices)
     (80, (3, 20, 0, 33, 65), 640, 384, 0, 0),
 ]
-# few tokens per expert on average (the unused experts count): units of 64 rows for bf16, or for every format
+# few tokens per expert on average (the unused experts count): units of 64 rows for every format
 SPARSE = [(130, (130, 20, 65, 5), 384, 640, 1, 128, 8), (90, (17, 90, 33, 64, 1), 256, 256, 0, 0, 20)]
+# More than eight experts: undivided K in the down projection for every format.  First with more than 64 tokens per expert on
+# average; then with 32 to 64, where 128-row gate/up units begin for MXFP4 (experts times F past 32768) and not yet for
+# bf16 and FP8, and just below each of the two lines.
+MANY = [
+    (90, (90, 88, 65, 64, 63, 33, 17, 16, 1), 384, 256, 1, 256, 0),
+    (130, (130, 129, 128, 70, 66, 65, 64, 5, 2), 256, 640, 0, 0, 0),
+    (130, (130, 20, 65, 5), 384, 2816, 1, 128, 8),        # 43 tokens per expert, 12 x 2816
+    (130, (130, 66, 17, 64), 256, 2688, 0, 0, 8),         # 12 x 2688: too few rows
+    (94, (94, 33, 64, 16), 256, 2816, 0, 0, 8),           # 31 tokens per expert
+]
 RAGGED = {"bf16": (32, 96), "fp8": (64, 64), "fp4": (0, 0)}   # added to H and F: the format's smallest steps
 
 
 @pytest.mark.parametrize("fmt", ["bf16", "fp8", "fp4"])
-@pytest.mark.parametrize("case", LARGE + SPARSE)
+@pytest.mark.parametrize("case", LARGE + SPARSE + MANY)
 def test_large_batches(L, fmt, case):
     T, counts, H, F, S, Fs, *spare = case
     dH, dF = RAGGED[fmt]
