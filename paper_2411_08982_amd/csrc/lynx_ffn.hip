@@ -1406,9 +1406,12 @@ static int pick_k_waves(int K, int R, bool dual, int T, int max_experts, int bit
     // do are expensive).
     // Beyond 64 tokens (passes of up to 128 tokens): 128-row workgroups, whose staged passes give every wave two row
     // tiles that share each token fragment read from LDS (measured 2-4 % faster on every shape).
-    // (not with quantised weights where 128-row workgroups are fewer than the CUs: 8 experts of 512 x 1024, FP8, 100 tokens
-    // 22.8 against 21.7 us.  With 8 experts of 4096 rows, 256 of them, MXFP4: 1000 tokens 727 against 820 us, 256 tokens 282
-    // against 307, 100 tokens 179 against 182; FP8 within 1 %.)
+    // (not with quantised weights of at most eight experts whose 128-row workgroups are fewer than the CUs.  us per FFN call,
+    // 128-row against 64-row workgroups, 100 tokens: 8 experts of 512 rows, F = 1024, FP8 17.5 against 16.5, MXFP4 16.6
+    // against 16.0; 8 experts of 4096 rows, 256 workgroups, F = 14336, FP8 245 against 251, MXFP4 150 against 161.  The
+    // limit of eight is part of the rule and not of the reason: with more experts and as few workgroups 64 rows are the
+    // better ones too (16 experts of 1024 rows, F = 2048, 300 tokens, FP8 57.1 against 52.3), towards 256 workgroups it
+    // goes either way (60 experts of 512 rows, FP8, 100 tokens 28.6 against 30.4, 600 tokens of F = 1408 55.6 against 53.0).)
     if (T > kTokBlock && !(bits_per_weight < 16 && max_experts <= 8 && (long)max_experts * R < 256 * 128)) return 1;
     if (T > kDirectMaxTokens) return 2;
     // Down, direct path only.  Measured: splitting K four ways pays when the batch can invoke so few experts
@@ -1515,8 +1518,8 @@ static void launch_kernel(const FfnParams &fp, unsigned blocks, hipStream_t st)
 // tokens: 81.7 -> 81.7, remap off 92.3 -> 87.5); with huge experts (hundreds of gate/up workgroups each, whose
 // completion reports then cost more than the overlap gains) it is equal or slower at every batch size.
 
-// Gate/up and down over all invoked and shared experts.  Batches of more than 64 tokens take the
-// kernels whose staged path makes passes of up to 128 tokens.
+// Gate/up and down over all invoked and shared experts.  Batches of more than 64 tokens take the large-batch kernels, whose
+// staged path makes passes of up to 128 tokens with bf16 weights, 64 with quantised ones.
 template <int WF>
 static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
 {

@@ -23,14 +23,14 @@
 namespace lynx {
 
 constexpr int kDirectMaxTokens = 16;         // experts with more tokens take the staged path
-constexpr int kTokBlock = 64;                // tokens per pass of the staged path (batches of up to 64 tokens)
-constexpr int kTokBlockBig = 128;            // the same in the bf16 kernels launched for larger batches
+constexpr int kTokBlock = 64;                // tokens per pass of the staged path (batches of up to 64 tokens, quantised weights)
+constexpr int kTokBlockBig = 128;            // the same for larger batches with bf16 weights
 
 static_assert(LYNX_MAX_N + LYNX_MAX_T * LYNX_MAX_K / kTokBlock <= kPlanMaxBlocks, "the plan must hold every block of a batch");
 
 // What the host knows of the FFN launch when the plan is built.
 struct PlanShape {
-    int units_gu;    // gate/up work items per (expert, token block): 64-row units of the F rows; 0 = build no plan
+    int units_gu;    // gate/up work items per (expert, token block): units of 64 or 128 of the F rows; 0 = build no plan
     int units_dn;    // down-projection row units per (expert, token block)
     int tok_block;   // tokens per block of an expert on the staged path
     int dn_cap;      // down items the grid is sized for: the device takes the fewest units per item that fit it
