@@ -52,7 +52,9 @@ const char *lynx_last_error(void);
 /* Bytes of device workspace that lynx_affinity_bin, lynx_moe_ffn and lynx_moe_layer need for these
  * sizes (one buffer serves all; contents need not be preserved between calls; calls that share a
  * workspace must not overlap in time).  lynx_affinity_bin alone uses only the first 64 KiB.  N does not
- * enter the size: the per-expert tables are reserved for LYNX_MAX_N experts in a part of fixed size. */
+ * enter the size: the per-expert tables are reserved for LYNX_MAX_N experts in a part of fixed size.  The
+ * workspace starts on 128 bytes, as every device allocation does (rows that one launch both writes and reads must
+ * not share a cache line). */
 size_t lynx_workspace_bytes(int T, int H, int F, int N, int k, int n_shared, int F_shared);
 
 /*
