@@ -14,7 +14,8 @@ extern "C" {
 
 /*
  * How many launches of the weight-streaming kernel lynx_moe_ffn issues for this batch size and expert width:
- * 1 (gate/up and down workgroups in one grid) or 2 (one grid each).  For measurement: per-launch figures of
+ * 1 (gate/up and down workgroups in one grid) or 2 (one grid each; always for an x that does not start on 16 bytes,
+ * whose rows are copied first).  For measurement: per-launch figures of
  * a profile are whole-FFN figures divided by this.
  */
 int lynx_moe_ffn_launches(int T, int F);

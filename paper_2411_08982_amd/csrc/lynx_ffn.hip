@@ -790,6 +790,8 @@ __device__ __forceinline__ void expert_staged(const WorkItem &w, const int *rowo
     // The wave's own pieces of the chunk requested last have landed, and then everybody's have, and nobody reads the other
     // buffer any more.  The count is of the loads that the wave has issued behind those pieces (`tiles` turns of load_w;
     // every load of the loop sits between scheduling fences).  The build counts them again in the machine code.
+    // (Left to the compiler, which waited before a read of the last piece, the counts were the same but for MXFP4's first
+    // chunks: nearly everything.  With the columns masked above, MXFP4 FFN of 100 tokens 173.6 -> 168.1 us.)
     constexpr int kLoadsPerTile = S + (WF == 2 ? SG : 0);
     auto chunk_ready = [&](auto tiles) {
         wait_loads<tiles.value * kLoadsPerTile>();
