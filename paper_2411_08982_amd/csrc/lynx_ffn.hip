@@ -1064,7 +1064,10 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
                 // unit and the expert: the sharing workgroups have consecutive indices, so a fixed choice would put all
                 // the staged work of the launch on the XCDs that the first of every four workgroups goes to (measured:
                 // two of the eight XCDs ended their gate/up work at 44 us, the others at 31 us).
-                if (!shared && (tile % kShare) != ((tile / kShare + w.e) % kShare)) continue;
+                // (Of the last unit's sharers some may not exist: R / 32 need not be even.)
+                int owner = tile / kShare * kShare + (tile / kShare + w.e) % kShare;
+                if (!DUAL && kShare > 1) owner = min(owner, p.tiles_r - 1);
+                if (!shared && tile != owner) continue;
                 const int s0 = shared ? tile : (tile / kShare) * kUnits;
                 const int sn = shared ? 1 : kUnits;
                 for (int su = 0; su < sn; ++su) {
