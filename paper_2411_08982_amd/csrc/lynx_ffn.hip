@@ -941,7 +941,8 @@ struct FfnParams {
     int32_t *flags;
 };
 
-constexpr int kSplitRound = 256;     // CUs: workgroups per round of the dispatcher
+constexpr int kCus = 256;
+constexpr int kSplitRound = kCus;    // workgroups per round of the dispatcher
 constexpr int kSplitMaxRem = 128;    // largest partial round that is cut into single row tiles
 constexpr int kSplitMaxTokens = 32;  // largest batch for which it is done
 constexpr int kSpinLimit = 1 << 17;   // polls of a counter (about a microsecond each) before giving up
@@ -1454,6 +1455,20 @@ struct FfnShape {
 
 static bool single_launch(int T, int F) { return T >= 1 && (F + 63) / 64 <= 64; }   // (any batch size: see below)
 
+// Quantised weights, huge experts: one launch all the same where the batch is between 8 and 64 tokens and can fill every slot
+// of the chip with down workgroups (two per CU).  They start in the slots that the last, partial round of gate/up workgroups
+// leaves empty.  us per FFN call, two launches against one: 8 experts of 4096 x 14336, FP8, 8 tokens 205 -> 195, 16 tokens
+// 230 -> 224, 48 tokens 246 -> 242; MXFP4 118 -> 109, 127 -> 122, 143 -> 141; 16 experts of 4096 x 8192, 20 tokens, FP8
+// 231 -> 220, MXFP4 128 -> 121.  Fewer down workgroups than slots lose: they go two to a CU as its slots come free, where a
+// launch of their own spreads them, one to a CU (4 experts of 2048 x 8192, FP8, 8 tokens 45 against 49; the first shapes, 2
+// tokens, 107 against 116, 100 tokens and 128-row workgroups, 277 against 309).  bf16 weights gain 0 to 1.5 % and keep two.
+// (Expert ranges of a caller that overlap can make more token blocks than the plan has records; their gate/up workgroups
+// would never report.  Batches that could do that keep two launches, which wait for nothing.)
+static bool fill_tail(int T, int N, int k, long down_items)
+{
+    return T >= 8 && T <= kTokBlock && down_items >= 2 * kCus && (long)N * ((T * k + kTokBlock - 1) / kTokBlock) <= kPlanMaxBlocks;
+}
+
 static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int format)
 {
     FfnShape s;
@@ -1472,7 +1487,6 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     const bool sooner = format == 2 && (long)N * F >= 256L * 128 && (long)T * k >= 32L * N;
     const bool many = sooner || (long)T * k > (long)kTokBlock * N;
     s.big = T <= kTokBlock ? 0 : many ? 2 : 1;
-    s.single = single_launch(T, F);
     s.tok_block = staged_tokens(s.big, format);
     s.max_blocks = plan_max_blocks(T, N, k, s.tok_block);
     s.plan.shared_pairs = n_shared * (T > kDirectMaxTokens ? (T + s.tok_block - 1) / s.tok_block : 1);
@@ -1480,6 +1494,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     const int rows_gu = 64 * staged_row_tiles(true, 1, s.big);
     s.plan.units_gu = (F + rows_gu - 1) / rows_gu;
     s.plan.units_dn = (H + rows_dn - 1) / rows_dn;
+    s.single = single_launch(T, F) || (format != 0 && fill_tail(T, N, k, (long)s.plan.units_dn * max_experts));
     s.plan.tok_block = s.tok_block;
     // Longer down items only where the staged unit and the direct workgroup are the same 64 rows (two K slices).
     // (not in the large-batch kernels, whose items are single passes)
@@ -1520,8 +1535,9 @@ static void launch_kernel(const FfnParams &fp, unsigned blocks, hipStream_t st)
 // Measured over the benchmark configurations: with experts of moderate size the single launch is 3-12 % faster beyond
 // 16 tokens (the down projection fills the tail of gate/up and there is one start-up less) and 0-5 % faster up to 16
 // (DeepSeek-V2-Lite shapes, 16 tokens: 87.6 -> 84.7 us per layer, remap off 150.0 -> 146.5; Qwen1.5-MoE shapes, 8
-// tokens: 81.7 -> 81.7, remap off 92.3 -> 87.5); with huge experts (hundreds of gate/up workgroups each, whose
-// completion reports then cost more than the overlap gains) it is equal or slower at every batch size.
+// tokens: 81.7 -> 81.7, remap off 92.3 -> 87.5); with huge experts it is
+// equal or slower with bf16 weights (Mixtral shapes, 1 token 129 -> 140 us, 64 tokens equal, 200 tokens 505 -> 555: down
+// workgroups that are few come to lie two to a CU) and faster with quantised ones between 8 and 64 tokens (fill_tail).
 
 // Gate/up and down over all invoked and shared experts.  Batches of more than 64 tokens take the large-batch kernels, whose
 // staged path makes passes of up to 128 tokens with bf16 weights, 64 with quantised ones.

@@ -226,6 +226,14 @@ def test_k_slices_set_by_the_knob(L, fmt, slices, case):
         L.lynx_debug_set(B.DEBUG_DOWN_K_WAVES, 0)
 
 
+# One launch for quantised experts past 4096 columns from 8 to 64 tokens, where 512 down workgroups exist: both edges of the
+# batch size, direct and staged experts, and just too few workgroups (H = 1920: 480), two launches, beside it.
+@pytest.mark.parametrize("fmt,T,H,F", [("fp8", 7, 2048, 4160), ("fp8", 8, 1920, 4160), ("fp8", 8, 2048, 4160), ("fp4", 8, 2048, 4224),
+                                       ("fp8", 64, 4096, 4160)])
+def test_huge_quantised_experts_in_one_launch(L, fmt, T, H, F):
+    run_case(L, fmt, T, tuple(min(T, c) for c in (64, 20, 8, 7, 5, 3, 2, 1)), H, F, 0, 0)
+
+
 def test_overlapping_expert_ranges_stay_inside_the_plan(L):
     """expert_offsets that lynx_permute cannot have written: every second expert claims all pairs, which makes more token
     blocks than the work plan has records, and the last expert, behind them, a few (its pair ids would be filed).  What
