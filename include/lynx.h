@@ -159,7 +159,7 @@ int lynx_moe_ffn(const uint16_t *x_bf16, const uint16_t *Wgu_packed, const uint1
 /*
  * The whole decode step of one MoE layer: the work of lynx_route, lynx_affinity_bin, lynx_permute and
  * lynx_moe_ffn chained on `stream` with the argument meanings above and identical results (the routing
- * side is issued as two launches up to 16 tokens and four beyond).  All intermediate arrays are outputs; new_psum and
+ * side is issued as one or two launches up to 16 tokens and four beyond).  All intermediate arrays are outputs; new_psum and
  * status may be NULL.  Every argument check of the four calls is made before anything is enqueued.  stage_events: HOST
  * array of four hipEvent_t (entries may be NULL) or NULL: [0] is recorded on `stream` before the weight-streaming
  * launch(es), [1] and [2] after them, [3] after the combine (for measurement; see lynx_bench.h).

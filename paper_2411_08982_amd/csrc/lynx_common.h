@@ -80,6 +80,16 @@ __device__ __forceinline__ int wave_prefix_sum_i32(int v)
     return v;
 }
 
+// Sum over each row of 16 lanes: lane 15 of the row holds it.
+__device__ __forceinline__ int row_sum_i32(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    return v;
+}
+
 // Floats as integers that compare the same way (finite values and infinities; -0 is first made +0, so that the two
 // stay equal), and back.
 __device__ __forceinline__ int order_key(float f)

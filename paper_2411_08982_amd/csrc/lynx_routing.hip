@@ -8,11 +8,12 @@
 // minimises dependent launches and dependent memory round trips inside them:
 //   logits_kernel         (token tile x expert group)  fp32 dot products: the router row is prefetched
 //                         into registers while the 4 tokens are staged in LDS; lanes split H; transposing
-//                         butterfly reduction.  Always its own launch (it needs the whole chip).  Above
+//                         butterfly reduction.  Its own launch (it needs the whole chip).  Above
 //                         128 tokens logits_mfma_kernel does the same on the fp32 matrix cores.
 //   T <= 16:  routing_small_kernel  ONE workgroup does everything else with all state in LDS: top-k,
 //                         bins + histogram, scores + score order, nominations, fill, remap, gates, counts
-//                         and (fused path) the token assignment.  Two launches for the whole routing side.
+//                         and (fused path) the token assignment.  Two launches for the whole routing side, one
+//                         where the router is so small that this workgroup computes the logits as well.
 //   T  > 16:  token_kernel -> nominate_kernel -> remap_kernel, one wave per token over many workgroups, one
 //                         launch per batch-level dependency (finished histogram; finished active set).
 //                         Scores/order and the fill are recomputed by every workgroup in its prologue
@@ -35,6 +36,7 @@ constexpr int kTokWaves = kTokThreads / kWave;
 constexpr int kRemapWideMinT = 256;   // batches from which remap_kernel runs with 1024 threads per workgroup
 constexpr int kSmallThreads = 1024;   // single-workgroup path: 16 waves = 16 tokens
 constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kSmallFusedN = 64;      // most experts whose logits the single workgroup computes itself (small_logits_pays)
 constexpr int kLogitsMfmaMinT = 128;   // larger batches compute the logits on the fp32 matrix cores (measured crossover)
 
 struct ZeroList {
@@ -56,6 +58,40 @@ __global__ __launch_bounds__(256) void zero_kernel(ZeroList z)
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Eight columns of one token and expert.
+__device__ __forceinline__ float logits_dot8(uint4 xv, float4 w0, float4 w1, float a)
+{
+    a = fmaf(bf16_lo(xv.x), w0.x, a);
+    a = fmaf(bf16_hi(xv.x), w0.y, a);
+    a = fmaf(bf16_lo(xv.y), w0.z, a);
+    a = fmaf(bf16_hi(xv.y), w0.w, a);
+    a = fmaf(bf16_lo(xv.z), w1.x, a);
+    a = fmaf(bf16_hi(xv.z), w1.y, a);
+    a = fmaf(bf16_lo(xv.w), w1.z, a);
+    a = fmaf(bf16_hi(xv.w), w1.w, a);
+    return a;
+}
+
+// Sums of four tokens over the lanes: a transposing butterfly, after whose two exchange steps each quarter of the wave owns
+// one token's sum.  Lane 16 q returns the sum of token tok (one of the four).
+__device__ __forceinline__ float logits_reduce(const float (&acc)[kRouteTT], int &tok)
+{
+    const int lane = lane_id();
+    const bool hi32 = (lane & 32) != 0;
+    float a0 = hi32 ? acc[2] : acc[0], a1 = hi32 ? acc[3] : acc[1];
+    const float s0 = hi32 ? acc[0] : acc[2], s1 = hi32 ? acc[1] : acc[3];
+    a0 += __shfl_xor(s0, 32, kWave);
+    a1 += __shfl_xor(s1, 32, kWave);
+    const bool hi16 = (lane & 16) != 0;
+    float keep = hi16 ? a1 : a0;
+    const float send = hi16 ? a0 : a1;
+    keep += __shfl_xor(send, 16, kWave);
+#pragma unroll
+    for (int m = 8; m > 0; m >>= 1) keep += __shfl_xor(keep, m, kWave);
+    tok = (hi32 ? 2 : 0) + (hi16 ? 1 : 0);
+    return keep;
+}
 
 // logits[t,e] = sum_h x[t,h] * Wr[e,h] + bias[e].  Grid (ceil(T/4), ceil(N/4)); wave w owns expert
 // 4*blockIdx.y + w for the workgroup's 4 tokens.  Also clears the scratch of the kernels that follow.
@@ -105,34 +141,12 @@ __global__ __launch_bounds__(256) void logits_kernel(const uint16_t *__restrict_
         for (int i = 0; i < kIter; ++i) {
             const int h = min(lane * 8 + i * kWave * 8, hc - 8);
 #pragma unroll
-            for (int tt = 0; tt < kRouteTT; ++tt) {
-                const uint4 xv = *reinterpret_cast<const uint4 *>(xs + tt * kRouteHC + h);
-                float a = acc[tt];
-                a = fmaf(bf16_lo(xv.x), w0[i].x, a);
-                a = fmaf(bf16_hi(xv.x), w0[i].y, a);
-                a = fmaf(bf16_lo(xv.y), w0[i].z, a);
-                a = fmaf(bf16_hi(xv.y), w0[i].w, a);
-                a = fmaf(bf16_lo(xv.z), w1[i].x, a);
-                a = fmaf(bf16_hi(xv.z), w1[i].y, a);
-                a = fmaf(bf16_lo(xv.w), w1[i].z, a);
-                a = fmaf(bf16_hi(xv.w), w1[i].w, a);
-                acc[tt] = a;
-            }
+            for (int tt = 0; tt < kRouteTT; ++tt)
+                acc[tt] = logits_dot8(*reinterpret_cast<const uint4 *>(xs + tt * kRouteHC + h), w0[i], w1[i], acc[tt]);
         }
     }
-    // transposing butterfly: after two exchange steps each quarter of the wave owns one token's sum
-    const bool hi32 = (lane & 32) != 0;
-    float a0 = hi32 ? acc[2] : acc[0], a1 = hi32 ? acc[3] : acc[1];
-    const float s0 = hi32 ? acc[0] : acc[2], s1 = hi32 ? acc[1] : acc[3];
-    a0 += __shfl_xor(s0, 32, kWave);
-    a1 += __shfl_xor(s1, 32, kWave);
-    const bool hi16 = (lane & 16) != 0;
-    float keep = hi16 ? a1 : a0;
-    const float send = hi16 ? a0 : a1;
-    keep += __shfl_xor(send, 16, kWave);
-#pragma unroll
-    for (int m = 8; m > 0; m >>= 1) keep += __shfl_xor(keep, m, kWave);
-    const int tok = (hi32 ? 2 : 0) + (hi16 ? 1 : 0);
+    int tok;
+    const float keep = logits_reduce(acc, tok);
     if ((lane & 15) == 0 && tok < ntok && e < N) {
         float zv = keep;
         if (bias) zv += bias[e];
@@ -313,15 +327,21 @@ __device__ __forceinline__ float selection_gate(int k, int mye, float myz, int g
 // The "top-k weight sum" of a selection (paper Sec. 4): with num = sum over the selected experts of exp(z - zref) it is
 // num over the same sum taken over all N experts; for a sigmoid-gated router the sum of the selected scores itself.
 template <int NS>
-__device__ __forceinline__ void selection_mass(const TokenLogits<NS> &raw, int t, int gate_fn, float num, float zref,
-                                               float *__restrict__ out)
+__device__ __forceinline__ float selection_mass_of(const TokenLogits<NS> &raw, int gate_fn, float num, float zref)
 {
     float part = 0.f;
 #pragma unroll
     for (int i = 0; i < NS; ++i)
         if ((raw.have >> i) & 1u) part += expf(raw.v[i] - zref);
     const float den = wave_sum(part);
-    if (lane_id() == 0) out[t] = gate_fn == kGateSigmoid ? num : num / den;
+    return gate_fn == kGateSigmoid ? num : num / den;
+}
+template <int NS>
+__device__ __forceinline__ void selection_mass(const TokenLogits<NS> &raw, int t, int gate_fn, float num, float zref,
+                                               float *__restrict__ out)
+{
+    const float m = selection_mass_of(raw, gate_fn, num, zref);
+    if (lane_id() == 0) out[t] = m;
 }
 
 // Softmax + top-k (Sec. 2.1): lane j < k returns the j-th pick in mye; writes idx / gate / psum (softmax: the
@@ -380,14 +400,14 @@ __device__ __forceinline__ float logit_of(const TokenLogits<NS> &tl, int e)
 }
 
 // Nominations of one token (Sec. 3.3.1 under the stated reading).  order[r] = expert with the r-th best
-// score, inU[e] = the batch invokes e, sel = the token's own picks in rank order; sets inA[e] = 1.
+// score, inU[e] > 0 = the batch invokes e, myq = the bins of the token's own picks, one per lane in rank order (beta = none);
+// zmax = its largest logit; sets inA[e] = 1.
 // The logits stay in registers: the experts are brought into score order with lane permutations.
 template <int NS>
-__device__ __forceinline__ void token_nominate(const TokenLogits<NS> &tl, int N, int k, float alpha, int beta,
-                                               const int *order, const int *inU, const int32_t *sel, int *inA)
+__device__ __forceinline__ void nominate_by_bins(const TokenLogits<NS> &tl, float zmax, int myq, int N, int k, float alpha, int beta,
+                                                 const int *order, const int *inU, int *inA)
 {
     const int lane = lane_id();
-    const float zmax = token_max(tl);
     int er[NS], qr[NS];
     unsigned avail = 0;   // bit i: the expert at score rank lane+64*i is invoked by the batch and not used yet
 #pragma unroll
@@ -398,15 +418,7 @@ __device__ __forceinline__ void token_nominate(const TokenLogits<NS> &tl, int N,
         // be read by the others, and the expert at this lane's rank may live in any lane
         const float zr = logit_of(tl, er[i]);
         qr[i] = (r < N && zr != -INFINITY) ? bin_of(zmax, zr, alpha, beta) : INT_MAX;   // -inf: not one of the token's groups
-        if (r < N && inU[er[i]]) avail |= 1u << i;
-    }
-    // bins of the token's own picks, one per lane
-    int myq = beta;
-    {
-        const int es = (lane < k) ? sel[lane] : -1;
-        const bool ok = es >= 0 && es < N;
-        const float zs = logit_of(tl, ok ? es : 0);
-        if (ok) myq = bin_of(zmax, zs, alpha, beta);
+        if (r < N && inU[er[i]] > 0) avail |= 1u << i;
     }
     for (int s = 0; s < k; ++s) {
         const int qs = __builtin_amdgcn_readlane(myq, s);
@@ -426,6 +438,19 @@ __device__ __forceinline__ void token_nominate(const TokenLogits<NS> &tl, int N,
             }
         }
     }
+}
+
+// The same, the token's own picks given in rank order.
+template <int NS>
+__device__ __forceinline__ void token_nominate(const TokenLogits<NS> &tl, int N, int k, float alpha, int beta,
+                                               const int *order, const int *inU, const int32_t *sel, int *inA)
+{
+    const int lane = lane_id();
+    const float zmax = token_max(tl);
+    const int es = (lane < k) ? sel[lane] : -1;
+    const bool ok = es >= 0 && es < N;
+    const float zs = logit_of(tl, ok ? es : 0);
+    nominate_by_bins(tl, zmax, ok ? bin_of(zmax, zs, alpha, beta) : beta, N, k, alpha, beta, order, inU, inA);
 }
 
 // Fill of the active set up to k from the invoked experts in score order (one wave; inA / inU in LDS).
@@ -451,8 +476,48 @@ __device__ __forceinline__ int wave_fill_active(int N, int k, const int *order, 
     return nU;
 }
 
-// Selection of one token inside the active set (or its unchanged selection when bypassed) and its gates
-// (Secs. 3.4, 4).  Lane j < k returns the j-th expert; writes new_idx / new_gate.
+// Selection of one token inside the active set (Secs. 3.4, 4): lane j < k holds its j-th expert in mye (-1 = none) and that
+// expert's logit in myz.  active(e) = e is in the active set; ownz(own, zs): fetches the token's own picks, one per lane in
+// rank order (-1 = none or invalid), and their logits, if they are needed.
+template <int NS, typename Active, typename Own>
+__device__ __forceinline__ void select_active(const TokenLogits<NS> &tl, int k, Active &&active, Own &&ownz, int &mye, float &myz)
+{
+    const int lane = lane_id();
+    mye = -1;
+    myz = -INFINITY;
+    unsigned cand = 0;
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+        if (((tl.have >> i) & 1u) && active(lane + kWave * i)) cand |= 1u << i;
+    wave_topk(tl.v, cand, k, [&](int j, int e, float zz) {
+        put_lane(mye, j, (e == INT_MAX) ? -1 : e);
+        put_lane(myz, j, zz);
+    });
+    // A group-limited token can find fewer than k members of the active set among its experts (without groups
+    // the active set holds at least k for everybody).  Then all of them were taken, and the slots left keep the
+    // token's own picks that are not in the active set, in rank order.
+    int slot = __popcll(__ballot(lane < k && mye >= 0));
+    if (slot < k) {
+        int es;
+        float zs;
+        ownz(es, zs);
+        unsigned long long rest = __ballot(es >= 0 && !active(es >= 0 ? es : 0));
+        while (rest != 0ull && slot < k) {
+            const int src = __ffsll((long long)rest) - 1;
+            rest &= rest - 1ull;
+            const int e = __shfl(es, src, kWave);
+            const float zz = __shfl(zs, src, kWave);
+            if (lane == slot) {
+                mye = e;
+                myz = zz;
+            }
+            ++slot;
+        }
+    }
+}
+
+// The same (or the token's unchanged selection when bypassed) from its picks in memory, and the gates.
+// Lane j < k returns the j-th expert; writes new_idx / new_gate.
 // new_psum (may be null): what token_topk writes as topk_psum, for the new selection: its share of the softmax over all
 // N experts (raw), or the sum of its sigmoid scores.  Same arithmetic as there, so an unchanged selection gives the
 // same bits.
@@ -464,45 +529,19 @@ __device__ __forceinline__ int token_remap(const TokenLogits<NS> &tl, const Toke
     const int lane = lane_id();
     int mye = -1;
     float myz = -INFINITY;
+    auto own = [&](int &es, float &zs) {
+        es = (lane < k) ? sel[lane] : -1;
+        if (es >= N) es = -1;
+        zs = logit_of(tl, max(es, 0));
+    };
     if (bypass) {
-        const int es = (lane < k) ? sel[lane] : -1;
-        const bool ok = es >= 0 && es < N;
-        const float zs = logit_of(tl, ok ? es : 0);
-        if (ok) {
-            mye = es;
-            myz = zs;
-        }
+        float zs;
+        own(mye, zs);
+        if (mye >= 0) myz = zs;
     } else {
-        unsigned cand = 0;
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-            if (((tl.have >> i) & 1u) && inA[lane + kWave * i]) cand |= 1u << i;
-        wave_topk(tl.v, cand, k, [&](int j, int e, float zz) {
-            put_lane(mye, j, (e == INT_MAX) ? -1 : e);
-            put_lane(myz, j, zz);
-        });
-        // A group-limited token can find fewer than k members of the active set among its experts (without groups
-        // the active set holds at least k for everybody).  Then all of them were taken, and the slots left keep the
-        // token's own picks that are not in the active set, in rank order.
-        int slot = __popcll(__ballot(lane < k && mye >= 0));
-        if (slot < k) {
-            const int es = (lane < k) ? sel[lane] : -1;
-            const bool ok = es >= 0 && es < N;
-            const float zs = logit_of(tl, ok ? es : 0);
-            unsigned long long rest = __ballot(ok && !inA[ok ? es : 0]);
-            while (rest != 0ull && slot < k) {
-                const int src = __ffsll((long long)rest) - 1;
-                rest &= rest - 1ull;
-                const int e = __shfl(es, src, kWave);
-                const float zz = __shfl(zs, src, kWave);
-                if (lane == slot) {
-                    mye = e;
-                    myz = zz;
-                }
-                ++slot;
-            }
-        }
+        select_active(tl, k, [&](int e) { return inA[e] != 0; }, own, mye, myz);
     }
+    mye = max(mye, -1);
     float num, zref;
     const float g = selection_gate(k, mye, myz, gate_fn, num, zref);
     if (lane < k) {
@@ -574,98 +613,293 @@ __device__ __forceinline__ bool last_workgroup(int32_t *ticket, int *flag_lds)
 constexpr int kSmallT = 16;   // one token per wave; beyond that one CU's ALUs are the bottleneck (measured)
 
 struct SmallShared {
-    PermuteSharedT<1> perm;
     int hist[LYNX_MAX_N * LYNX_MAX_BETA];
-    unsigned long long score[LYNX_MAX_N];
-    int cntb[LYNX_MAX_N], cnta[LYNX_MAX_N], order[LYNX_MAX_N], inU[LYNX_MAX_N], inA[LYNX_MAX_N];
-    unsigned key[LYNX_MAX_N];
-    int32_t sel[kSmallT * LYNX_MAX_K];      // the tokens' own picks
-    int32_t newsel[kSmallT * LYNX_MAX_K];   // the remapped picks
-    int n_before, n_after;
+    int cntb[LYNX_MAX_N], cnta[LYNX_MAX_N], order[LYNX_MAX_N];
+    int nominated[LYNX_MAX_N], filled[LYNX_MAX_N];   // the two parts of the active set
+    unsigned member[LYNX_MAX_N];                     // bit t: token t uses the expert after the remap
+    float logits[kSmallT * kSmallFusedN];            // (with the logits in this kernel)
 };
 static_assert(kSmallT <= kSmallWaves && kSmallT <= 32, "one wave per token, one 32-token word per expert");
 
-// One workgroup, wave t owns token t and keeps its logits in registers from the first step to the last.
-template <int NS, bool DO_TOPK, bool DO_PERMUTE>
+// Logits of the whole batch in one workgroup: a wave takes an expert and four tokens at a time, with the arithmetic and the
+// order of logits_kernel (the same bits).  Also clears the scratch of the kernels that follow.
+template <int MAXT>
+__device__ __forceinline__ void small_logits(const uint16_t *__restrict__ x, const float *__restrict__ Wr, const float *__restrict__ bias,
+                                             int T, int H, int N, float *__restrict__ logits, float *lds, const ZeroList &z)
+{
+    const int lane = lane_id();
+    const int tasks = N * ((T + kRouteTT - 1) / kRouteTT);
+    bool first = true;
+    for (int task = wave_id(); task < tasks; task += kSmallWaves) {
+        const int e = task % N, t0 = task / N * kRouteTT;
+        const int ntok = min(kRouteTT, T - t0);
+        float acc[kRouteTT] = {0.f, 0.f, 0.f, 0.f};
+        constexpr int kStep = kWave * 8, U = MAXT == 1 ? 8 : 2;   // columns of a wave-wide load; loads in flight (4: no better)
+        for (int h0 = 0; h0 < H; h0 += U * kStep) {
+            float4 w0[U], w1[U];
+            uint4 xv[U][MAXT];
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                if (h0 + i * kStep >= H) break;
+                const int h = h0 + i * kStep + lane * 8, hcl = min(h, H - 8);   // (past the end: see logits_kernel)
+                w0[i] = *reinterpret_cast<const float4 *>(Wr + (size_t)e * H + hcl);
+                w1[i] = *reinterpret_cast<const float4 *>(Wr + (size_t)e * H + hcl + 4);
+#pragma unroll
+                for (int tt = 0; tt < MAXT; ++tt)
+                    xv[i][tt] = *reinterpret_cast<const uint4 *>(x + (size_t)(t0 + min(tt, ntok - 1)) * H + hcl);
+            }
+            if (first) zero_slices(z, 0, 1, threadIdx.x, kSmallThreads);
+            first = false;
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                if (h0 + i * kStep >= H) break;
+                if (h0 + i * kStep + lane * 8 >= H) w0[i] = w1[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int tt = 0; tt < MAXT; ++tt) acc[tt] = logits_dot8(xv[i][tt], w0[i], w1[i], acc[tt]);
+            }
+        }
+        int tok;
+        const float keep = logits_reduce(acc, tok);
+        if ((lane & 15) == 0 && tok < ntok) {
+            const float zv = bias ? keep + bias[e] : keep;
+            logits[(size_t)(t0 + tok) * N + e] = zv;
+            lds[(t0 + tok) * N + e] = zv;
+        }
+    }
+    if (first) zero_slices(z, 0, 1, threadIdx.x, kSmallThreads);
+}
+
+// One workgroup, wave t owns token t and keeps its logits and its picks in registers from the first step to the last.
+// LOGITS: 0 = the logits are given; 1, 4 = this kernel computes them, for one token or for up to four at a time.
+// Bound by the latency of a chain of short steps (16 waves on one CU; a step is a few hundred cycles, most of them latencies of
+// LDS, lane exchanges and dependent instructions), so it holds as few of them as it can: five barriers; what only the results
+// need (gates, masses, counts) comes last, beside the token assignment; every wave makes the fill of the active set and the
+// prefix sums of the assignment for itself instead of waiting for one that does.
+// (As twelve steps with a barrier each, us per layer: 512 x 1024, 8 experts, 16 tokens 28.6 -> 27.2, and 25.2 with the logits in
+// it; Qwen1.5-MoE shapes, 8 tokens 61.3 -> 58.8; DeepSeek-V2-Lite shapes, MXFP4, 16 tokens 43.7 -> 42.1; 128 experts, 16 tokens,
+// small experts 41.8 -> 39.5.)
+template <int NS, bool DO_TOPK, bool DO_PERMUTE, int LOGITS>
 __global__ __launch_bounds__(kSmallThreads) void routing_small_kernel(
-    const float *__restrict__ logits, int T, int N, int k, float alpha, int beta, int bypass, RouterKind rk,
+    float *__restrict__ logits, int T, int N, int k, float alpha, int beta, int bypass, RouterKind rk,
     int32_t *__restrict__ topk_idx, float *__restrict__ topk_gate, float *__restrict__ topk_psum,
     int32_t *__restrict__ new_idx, float *__restrict__ new_gate, float *__restrict__ new_psum,
     int32_t *__restrict__ cnt_before, int32_t *__restrict__ cnt_after, int32_t *__restrict__ bin_hist,
     int32_t *__restrict__ num_active, int32_t *__restrict__ expert_offsets, int32_t *__restrict__ perm,
-    int32_t *__restrict__ active_experts, int32_t *__restrict__ num_active_perm, PlanShape ps, int32_t *__restrict__ ws)
+    int32_t *__restrict__ active_experts, int32_t *__restrict__ num_active_perm, PlanShape ps, int32_t *__restrict__ ws,
+    const uint16_t *__restrict__ x, const float *__restrict__ Wr, const float *__restrict__ bias, int H, ZeroList z)
 {
     __shared__ SmallShared sh;
     const int tid = threadIdx.x, lane = lane_id(), t = wave_id();
     const bool has_token = t < T;
-    // the token's logits (and, if given, its picks) are requested first; everything below overlaps the loads
-    const TokenLogits<NS> raw = load_token<NS>(logits + (size_t)(has_token ? t : 0) * N, N);
-    int given = -1;
-    if (!DO_TOPK && has_token && lane < k) given = topk_idx[(size_t)t * k + lane];
     for (int i = tid; i < N * beta; i += kSmallThreads) sh.hist[i] = 0;
     for (int i = tid; i < N; i += kSmallThreads) {
         sh.cntb[i] = 0;
         sh.cnta[i] = 0;
-        sh.inA[i] = 0;
-        if (DO_PERMUTE) sh.perm.member[i] = 0u;
+        sh.nominated[i] = 0;
+        sh.filled[i] = 0;
+        sh.member[i] = 0u;
     }
-    if (DO_PERMUTE)
-        for (int p = tid; p < T * k; p += kSmallThreads) perm[p] = -1;
-    if (tid == 0) sh.n_after = 0;
-    const TokenLogits<NS> tl = limit_groups(raw, N, rk);
-    __syncthreads();
-    // top-k (or the given picks), bins, histogram
-    if (has_token) {
-        int mye = -1;
-        if (DO_TOPK) {
-            mye = token_topk(tl, raw, t, k, rk.gate_fn, topk_idx, topk_gate, topk_psum);
-        } else if (lane < k) {
-            mye = (given < 0 || given >= N) ? -1 : given;
-        }
-        if (lane < k) sh.sel[t * k + lane] = mye;
-        token_bins(tl, k, mye, alpha, beta, sh.hist, sh.cntb);
-    }
-    __syncthreads();
-    score_of(tid, N, T, beta, sh.hist, sh.score);
-    if (tid < N) sh.inU[tid] = sh.cntb[tid] > 0;
-    __syncthreads();
-    rank_of(tid, N, T, beta, sh.score, sh.key, sh.order);
-    __syncthreads();
-    if (!bypass) {
-        if (has_token) token_nominate(tl, N, k, alpha, beta, sh.order, sh.inU, sh.sel + t * k, sh.inA);
+    if constexpr (LOGITS != 0) {
+        small_logits<LOGITS>(x, Wr, bias, T, H, N, logits, sh.logits, z);
         __syncthreads();
     }
-    if (t == 0) {
-        const int nU = wave_fill_active(N, k, sh.order, sh.inU, sh.inA, !bypass);
-        if (lane == 0) sh.n_before = nU;
+    const TokenLogits<NS> raw = load_token<NS>((LOGITS != 0 ? sh.logits : logits) + (size_t)(has_token ? t : 0) * N, N);
+    // the token's picks, top-k or given: lane j < k holds the j-th and its logit
+    int mye = -1;
+    if (!DO_TOPK && has_token && lane < k) mye = topk_idx[(size_t)t * k + lane];
+    float myz = -INFINITY;
+    const TokenLogits<NS> tl = limit_groups(raw, N, rk);
+    if (has_token) {
+        if (DO_TOPK) {
+            wave_topk(tl.v, tl.have, k, [&](int j, int e, float zz) {
+                put_lane(mye, j, (e == INT_MAX) ? -1 : e);
+                put_lane(myz, j, zz);
+            });
+        } else {
+            if (mye < 0 || mye >= N) mye = -1;
+            const float zs = logit_of(tl, max(mye, 0));
+            if (mye >= 0) myz = zs;
+        }
+    }
+    const float zmax = token_max(tl);
+    if (LOGITS == 0) __syncthreads();   // (LDS has been cleared)
+    // bins into the histogram, pairs per expert
+    int newe = mye;
+    float newz = myz;
+    if (has_token) {
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if ((tl.have >> i) & 1u) {
+                const int q = bin_of(zmax, tl.v[i], alpha, beta);
+                if (q >= 0 && q < beta) atomicAdd(&sh.hist[(lane + kWave * i) * beta + q], 1);
+            }
+        if (lane < k && mye >= 0) atomicAdd(&sh.cntb[mye], 1);
+    }
+    if (!bypass) {
+        __syncthreads();
+        // Score order: the rank of an expert is the number of experts with a larger key, counted by sixteen lanes per expert.
+        // The score has T for its base and is at most T^beta <= 2^24; only a histogram with all tokens in bin 0 reaches 2^24,
+        // and none has 2^24 - 1.  So score and index fit one word.
+        {
+            constexpr int KF = 4 * NS;
+            auto key_of = [&](int e) {
+                unsigned sc = 0;
+                for (int j = 0; j < beta; ++j) sc = sc * (unsigned)T + (unsigned)sh.hist[e * beta + j];
+                return min(sc, 0xffffffu) << 8 | (unsigned)(LYNX_MAX_N - 1 - e);
+            };
+            unsigned kf[KF];
+#pragma unroll
+            for (int j = 0; j < KF; ++j) {
+                const int f = (lane & 15) + 16 * j;
+                kf[j] = f < N ? key_of(f) : 0u;   // (below or equal to every key)
+            }
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                const int e = (tid >> 4) + kWave * i;
+                const unsigned mine = key_of(min(e, N - 1));
+                int r = 0;
+#pragma unroll
+                for (int j = 0; j < KF; ++j) r += kf[j] > mine ? 1 : 0;
+                r = row_sum_i32(r);   // lane 15 of the row
+                if ((lane & 15) == 15 && e < N) sh.order[r] = e;
+            }
+        }
+        __syncthreads();
+        if (has_token)
+            nominate_by_bins(tl, zmax, mye >= 0 ? bin_of(zmax, myz, alpha, beta) : beta, N, k, alpha, beta, sh.order, sh.cntb,
+                             sh.nominated);
+        __syncthreads();
+        if (has_token) {
+            // the fill of the active set up to k from the invoked experts in score order: every wave makes the same one
+            int er[NS], nA = 0;
+            bool u[NS];
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                const int r = lane + kWave * i;
+                er[i] = r < N ? sh.order[r] : 0;
+                const bool in = r < N && sh.nominated[er[i]] != 0;
+                u[i] = r < N && !in && sh.cntb[er[i]] > 0;
+                nA += __popcll(__ballot(in));
+            }
+            int need = k - nA;
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                if (need <= 0) break;
+                const unsigned long long b = __ballot(u[i]);
+                if (u[i] && __popcll(b & ((1ull << lane) - 1ull)) < need) sh.filled[er[i]] = 1;
+                need -= __popcll(b);
+            }
+            __builtin_amdgcn_wave_barrier();   // (the wave's own writes are read below; LDS serves a wave in order)
+            select_active(tl, k, [&](int e) { return (sh.nominated[e] | sh.filled[e]) != 0; },
+                          [&](int &es, float &zs) { es = mye; zs = myz; }, newe, newz);
+        }
+    }
+    if (has_token && lane < k && newe >= 0) {
+        if (DO_PERMUTE)
+            atomicOr(&sh.member[newe], 1u << t);
+        else
+            atomicAdd(&sh.cnta[newe], 1);   // (given picks may name an expert twice)
     }
     __syncthreads();
-    if (has_token) {
-        const int mye = token_remap(tl, raw, t, N, k, bypass != 0, rk.gate_fn, sh.inA, sh.sel + t * k, new_idx, new_gate,
-                                    new_psum);
-        if (lane < k) {
-            sh.newsel[t * k + lane] = mye;
-            if (mye >= 0) {
-                atomicAdd(&sh.cnta[mye], 1);
-                if (DO_PERMUTE) atomicOr(&sh.perm.member[mye], 1u << t);
+    // ---- results
+    if constexpr (DO_PERMUTE) {
+        // The token assignment.  An expert has at most 16 tokens, so it is one block of the FFN's plan and its rank among the
+        // invoked experts is the block.  Prefix sums over the experts, pairs in the low half and invoked experts in the high one.
+        if (has_token || t == kSmallWaves - 1) {
+            unsigned mem[NS];
+            int pre[NS], carry = 0;
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                const int e = lane + kWave * i;
+                mem[i] = e < N ? sh.member[e] : 0u;
+                const int v = __popc(mem[i]) | (mem[i] != 0u ? 1 << 16 : 0);
+                const int incl = wave_prefix_sum_i32(v);
+                pre[i] = carry + incl - v;
+                carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+            }
+            const int pairs = carry & 0xffff, na = carry >> 16;
+            if (has_token) {
+                unsigned m = 0;
+                int at = 0;
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    const int src = max(newe, 0) & (kWave - 1);
+                    const unsigned mi = (unsigned)__shfl((int)mem[i], src, kWave);
+                    const int pi = __shfl(pre[i], src, kWave);
+                    if ((max(newe, 0) >> 6) == i) {
+                        m = mi;
+                        at = pi;
+                    }
+                }
+                if (lane < k && newe >= 0) {
+                    const int p = t * k + lane, i = __popc(m & ((1u << t) - 1u));
+                    perm[(at & 0xffff) + i] = p;
+                    if (ps.units_gu > 0) reinterpret_cast<uint16_t *>(ws + kWsPlanPairs)[(at >> 16) * kDirectMaxTokens + i] = (uint16_t)p;
+                }
+            }
+            if (t == kSmallWaves - 1) {
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    const int e = lane + kWave * i, c = __popc(mem[i]), q = pre[i] >> 16;
+                    if (e < N) expert_offsets[e] = pre[i] & 0xffff;
+                    if (c > 0) {
+                        active_experts[q] = e;
+                        if (ps.units_gu > 0)
+                            *reinterpret_cast<int4 *>(ws + kWsPlanBlk + 4 * q) = make_int4(e | (c << 16), pre[i] & 0xffff, 0, 0);
+                    }
+                    if (e < N && e >= na) active_experts[e] = -1;
+                }
+                for (int p = pairs + lane; p < T * k; p += kWave) perm[p] = -1;   // pairs without a valid expert
+                if (lane == 0) {
+                    expert_offsets[N] = pairs;
+                    num_active_perm[0] = na;
+                    if (ps.units_gu > 0) {
+                        ws[kWsPlanHdr + kPlanB] = na;
+                        ws[kWsPlanHdr + kPlanM] = plan_down_units_per_item(ps, na);
+                        ws[kWsPlanHdr + kPlanNa] = na;
+                    }
+                }
             }
         }
     }
-    __syncthreads();
+    if (has_token) {
+        // gates and masses of both selections (one chain each, side by side); an unchanged selection has the same bits
+        float num, zref, num2, zref2;
+        const float g2 = selection_gate(k, newe, newz, rk.gate_fn, num2, zref2);
+        const float m2 = new_psum ? selection_mass_of(raw, rk.gate_fn, num2, zref2) : 0.f;
+        if (DO_TOPK) {
+            const float g = selection_gate(k, mye, myz, rk.gate_fn, num, zref);
+            const float m = selection_mass_of(raw, rk.gate_fn, num, zref);
+            if (lane < k) {
+                topk_idx[(size_t)t * k + lane] = mye;
+                topk_gate[(size_t)t * k + lane] = g;
+            }
+            if (lane == 0) topk_psum[t] = m;
+        }
+        if (lane < k) {
+            new_idx[(size_t)t * k + lane] = newe;
+            new_gate[(size_t)t * k + lane] = g2;
+        }
+        if (new_psum && lane == 0) new_psum[t] = m2;
+    }
     for (int i = tid; i < N * beta; i += kSmallThreads) bin_hist[i] = sh.hist[i];
     for (int i = tid; i < N; i += kSmallThreads) {
         cnt_before[i] = sh.cntb[i];
-        cnt_after[i] = sh.cnta[i];
-        if (sh.cnta[i] > 0) atomicAdd(&sh.n_after, 1);
+        cnt_after[i] = DO_PERMUTE ? __popc(sh.member[i]) : sh.cnta[i];
     }
-    __syncthreads();
-    if (tid == 0) {
-        num_active[0] = sh.n_before;
-        num_active[1] = sh.n_after;
+    if (t == kSmallWaves - 2) {
+        int nU = 0, nA = 0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int e = lane + kWave * i;
+            nU += __popcll(__ballot(e < N && sh.cntb[e] > 0));
+            nA += __popcll(__ballot(e < N && (DO_PERMUTE ? sh.member[e] != 0u : sh.cnta[e] > 0)));
+        }
+        if (lane == 0) {
+            num_active[0] = nU;
+            num_active[1] = nA;
+        }
     }
-    if constexpr (DO_PERMUTE)
-        permute_from_bitsets<kSmallThreads>(sh.perm, sh.newsel, T, N, k, expert_offsets, perm, active_experts,
-                                            num_active_perm, ps, ws);
 }
 
 // ---- large batches: one wave per token over many workgroups, one launch per batch-level dependency ----------
@@ -974,6 +1208,18 @@ static void launch_logits(const uint16_t *x, const float *Wr, const float *bias,
                            T, H, N, logits, z);
 }
 
+// Small batches with a small router: the workgroup that does the rest of the routing computes the logits too, which saves a
+// launch (2.2 to 2.8 us).  One CU reads the router's rows at some 60 GB/s and a wave goes through its experts one after another, so
+// it pays up to 32768 products of four tokens (128 KiB of router) and three experts per wave.  us per layer of small
+// experts, two launches against one: H = 4096, 8 experts, 1 token 23.7 -> 21.4, 4 tokens 27.6 -> 25.5, but 8 tokens
+// 29.6 -> 30.2; H = 2048, 8 experts, 8 tokens 24.7 -> 23.6; H = 512, 8 experts, 16 tokens 23.3 -> 21.2; 32 experts, 4 tokens
+// 21.8 -> 20.1, 8 tokens 23.0 -> 23.1.  A single token is a quarter of the work: 60 experts, H = 512, 19.3 -> 17.9.
+static bool small_logits_pays(int T, int H, int N)
+{
+    const long groups = (T + kRouteTT - 1) / kRouteTT;
+    return T <= kSmallT && N <= kSmallFusedN && groups * N * H <= 32768 && (T == 1 || groups * N <= 3 * kSmallWaves);
+}
+
 // Everything after the logits.  DO_TOPK: compute the top-k (else topk_idx is an input); DO_PERMUTE: also
 // assign the tokens.  clear_first: the multi-workgroup path accumulates into zeroed arrays; true = clear them
 // with a launch of their own, false = the caller already had them cleared (by the logits kernel).
@@ -986,9 +1232,12 @@ static int launch_after_logits_ns(const char *who, const float *logits, int T, i
 {
     const int bypass = (!enable || T <= 1) ? 1 : 0;
     if (T <= kSmallT) {
-        hipLaunchKernelGGL((routing_small_kernel<NS, DO_TOPK, DO_PERMUTE>), dim3(1), dim3(kSmallThreads), 0, st, logits, T, N, k,
-                           alpha, beta, bypass, rk, topk_idx, topk_gate, topk_psum, new_idx, new_gate, new_psum, cnt_before,
-                           cnt_after, bin_hist, num_active, expert_offsets, perm, active_experts, num_active_perm, ps, ws);
+        ZeroList none;
+        none.n = 0;
+        hipLaunchKernelGGL((routing_small_kernel<NS, DO_TOPK, DO_PERMUTE, 0>), dim3(1), dim3(kSmallThreads), 0, st,
+                           const_cast<float *>(logits), T, N, k, alpha, beta, bypass, rk, topk_idx, topk_gate, topk_psum, new_idx,
+                           new_gate, new_psum, cnt_before, cnt_after, bin_hist, num_active, expert_offsets, perm, active_experts,
+                           num_active_perm, ps, ws, nullptr, nullptr, nullptr, 0, none);
         return check_launch(who);
     }
     int rc;
@@ -1048,7 +1297,7 @@ static int launch_after_logits(const char *who, const float *logits, int T, int 
 #undef LYNX_ROUTING_ARGS
 }
 
-// The whole routing side of lynx_moe_layer: two launches for T <= kSmallT, four otherwise.  T >= 1, arguments checked.
+// The whole routing side of lynx_moe_layer: one or two launches for T <= kSmallT, four otherwise.  T >= 1, arguments checked.
 int routing_fused(const uint16_t *x, const float *Wr, const float *bias, int T, int H, int N, int k, float alpha,
                   int beta, int enable, RouterKind rk, float *logits, int32_t *topk_idx, float *topk_gate, float *topk_psum,
                   int32_t *new_idx, float *new_gate, float *new_psum, int32_t *cnt_before, int32_t *cnt_after, int32_t *bin_hist,
@@ -1067,6 +1316,14 @@ int routing_fused(const uint16_t *x, const float *Wr, const float *bias, int T, 
         add_zero(z, bin_hist, N * beta);
         add_zero(z, cnt_before, N);
         add_zero(z, cnt_after, N);
+    }
+    if (small_logits_pays(T, H, N)) {
+        const int bypass = (!enable || T <= 1) ? 1 : 0;
+        auto *kernel = T == 1 ? routing_small_kernel<1, true, true, 1> : routing_small_kernel<1, true, true, kRouteTT>;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), 0, st, logits, T, N, k, alpha, beta, bypass, rk, topk_idx, topk_gate,
+                           topk_psum, new_idx, new_gate, new_psum, cnt_before, cnt_after, bin_hist, num_active, expert_offsets, perm,
+                           active_experts, num_active_perm, ps, ws, x, Wr, bias, H, z);
+        return check_launch("lynx_moe_layer(routing)");
     }
     launch_logits(x, Wr, bias, T, H, N, logits, z, st);
     int rc = check_launch("lynx_moe_layer(logits)");

@@ -579,6 +579,43 @@ def test_fused_layer_equals_separate_calls(L, name, T, preset):
         assert torch.equal(u, v), i
 
 
+# At most 16 tokens: the single routing workgroup, with the logits in it on one side of its line and without on the other
+# (products of four tokens 32768, experts per wave, 64 experts, one token), several tasks per wave, hidden sizes that leave
+# lanes and whole column groups idle, experts past 64 and 128, as many picks as experts, group-limited and sigmoid-gated.
+@pytest.mark.parametrize("H,N,k,T,gate_fn,groups", [
+    (4096, 8, 2, 1, 0, (1, 1)), (4096, 8, 2, 4, 1, (4, 2)), (4096, 8, 2, 5, 0, (1, 1)), (4128, 8, 8, 3, 0, (1, 1)), (32, 5, 5, 16, 0, (1, 1)),
+    (544, 60, 4, 1, 0, (1, 1)), (96, 64, 16, 1, 1, (1, 1)), (512, 12, 3, 16, 0, (3, 2)), (640, 12, 3, 13, 1, (3, 1)), (672, 13, 2, 16, 0, (1, 1)),
+    (1056, 24, 6, 8, 0, (1, 1)), (64, 65, 7, 2, 0, (5, 3)), (128, 97, 9, 11, 0, (1, 1)), (64, 256, 8, 16, 1, (8, 4)), (64, 256, 16, 9, 0, (1, 1))])
+@pytest.mark.parametrize("alpha,beta,enable", [(4.0, 1, 1), (1.5, 6, 1), (0.0, 6, 1), (2.0, 2, 0)])   # alpha = 0: all in bin 0
+def test_small_layer_equals_separate_calls(L, H, N, k, T, gate_fn, groups, alpha, beta, enable):
+    cfg = wl.MoEConfig("small", H, 64, N, k, 0, 0, 1.0, 0.5, 0.2, (T,), 7)
+    d = wl.make_layer(cfg, T)
+    x, Wr, bias = to_bf16_dev(d["x"]), dev(d["Wr"]), dev(d["bias"])
+    Wgu, Wdp = L.lynx_pack_weights(to_bf16_dev(d["Wg"]), to_bf16_dev(d["Wu"]), to_bf16_dev(d["Wd"]))
+    buf = L.LayerBuffers(T, H, cfg.F, N, k, beta)
+    buf.workspace.fill_(0xFF)
+    b = L.lynx_moe_layer_grouped(x, Wr, bias, Wgu, Wdp, cfg.F, k, *groups, alpha, beta, gate_fn, enable, buffers=buf)
+    r = L.lynx_route_grouped(x, Wr, bias, k, *groups, gate_fn)
+    if groups[0] == 1:
+        a = (L.lynx_affinity_bin_sigmoid if gate_fn else L.lynx_affinity_bin)(r["logits"], r["idx"], alpha, beta, enable)
+    else:
+        a = L.lynx_affinity_bin_grouped(r["logits"], k, *groups, alpha, beta, gate_fn, enable)
+    p = L.lynx_permute(a["new_idx"], N)
+    y = L.lynx_moe_ffn(x, Wgu, Wdp, a["new_idx"], a["new_gate"], p, N, cfg.F)
+    torch.cuda.synchronize()
+    names = ["logits", "topk_idx", "topk_gate", "topk_psum", "new_idx", "new_gate", "new_psum", "cnt_before", "cnt_after", "bin_hist",
+             "num_active", "offsets", "perm", "active", "num_active_perm", "y"]
+    other = [r["logits"], r["idx"], r["gate"], r["psum"], a["new_idx"], a["new_gate"], a["new_psum"], a["cnt_before"], a["cnt_after"],
+             a["bin_hist"], a["num_active"], p["offsets"], p["perm"], p["active"], p["num_active"], y]
+    for n, v in zip(names, other):
+        assert torch.equal(getattr(b, n), v), n
+    if groups[0] == 1:   # the remap itself against the oracle (the separate calls share its kernel up to 16 tokens)
+        z = host(r["logits"])
+        ref = oracle.affinity_bin(z, host(r["idx"]), alpha, beta, enable)
+        for n in ("new_idx", "cnt_before", "cnt_after", "bin_hist", "num_active"):
+            assert np.array_equal(host(getattr(b, n)).ravel(), np.asarray(ref[n]).ravel()), n
+
+
 def test_layer_zero_tokens(L):
     cfg = wl.CONFIGS["tiny"]
     d = wl.make_layer(cfg, 0)
