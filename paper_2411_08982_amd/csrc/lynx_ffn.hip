@@ -1161,7 +1161,7 @@ __global__ __launch_bounds__(256) void plan_kernel(const int32_t *__restrict__ o
         offs[tid] = ok ? o0 : 0;
     }
     __syncthreads();
-    build_plan<256>(ps, N, count, offs, blk0, ws);
+    build_plan(ps, N, count, offs, blk0, ws);
     __syncthreads();
     // the pair ids of the experts on the direct path, 16 threads per expert
     for (int e = tid / kDirectMaxTokens; e < N; e += 256 / kDirectMaxTokens) {

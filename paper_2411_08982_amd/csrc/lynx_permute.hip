@@ -18,7 +18,6 @@ __global__ __launch_bounds__(kPermThreads) void permute_kernel(const int32_t *__
     const int W = (T + 31) / 32;
     const int P = T * k;
     for (int i = tid; i < N * W; i += kPermThreads) sh.member[i] = 0u;
-    for (int p = tid; p < P; p += kPermThreads) perm[p] = -1;
     __syncthreads();
     for (int p = tid; p < P; p += kPermThreads) {
         const int e = idx[p];

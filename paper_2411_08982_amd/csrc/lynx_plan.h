@@ -76,11 +76,23 @@ inline int plan_down_grid(const PlanShape &ps, int max_blocks)
     return (int)worst;
 }
 
-// Builds the header and the block records.  Every thread of the workgroup calls it (one wave does the work); count[e] /
-// offs[e] (pairs of expert e and where they start in the permutation) are in LDS and complete (barrier before).
-// blk0[e] (LDS) receives the first block of expert e, for the caller to file the pair ids under (barrier after).
+// The records of an expert with c > 0 pairs from offset off, blocks [q0, q0 + nb), and the header.
+__device__ __forceinline__ void plan_write_records(int e, int c, int off, int q0, int nb, int32_t *__restrict__ ws)
+{
+    for (int j = 0; j < nb && q0 + j < kPlanMaxBlocks; ++j)
+        *reinterpret_cast<int4 *>(ws + kWsPlanBlk + 4 * (q0 + j)) = make_int4(e | (c << 16), off, j, 0);
+}
+__device__ __forceinline__ void plan_write_header(const PlanShape &ps, int blocks, int invoked, int32_t *__restrict__ ws)
+{
+    ws[kWsPlanHdr + kPlanB] = min(blocks, kPlanMaxBlocks);
+    ws[kWsPlanHdr + kPlanM] = plan_down_units_per_item(ps, blocks);
+    ws[kWsPlanHdr + kPlanNa] = invoked;
+}
+
+// Builds the header and the block records from a caller's ranges.  Every thread of the workgroup calls it (one wave does the
+// work); count[e] / offs[e] (pairs of expert e and where they start in the permutation) are in LDS and complete (barrier
+// before).  blk0[e] (LDS) receives the first block of expert e, for the caller to file the pair ids under (barrier after).
 // ws = the routing part of the workspace.
-template <int THREADS>
 __device__ __forceinline__ void build_plan(const PlanShape &ps, int N, const int *count, const int *offs, int *blk0,
                                            int32_t *__restrict__ ws)
 {
@@ -96,21 +108,14 @@ __device__ __forceinline__ void build_plan(const PlanShape &ps, int N, const int
         const int a = c > 0 ? 1 : 0;
         const int nb = c > 0 ? plan_token_blocks(c, ps.tok_block) : 0;
         const int s = wave_prefix_sum_i32(a | (nb << 16));
-        if (e < N) blk0[e] = carry_b + (s >> 16) - nb;
-        if (a) {
-            const int q0 = carry_b + (s >> 16) - nb;
-            for (int j = 0; j < nb && q0 + j < kPlanMaxBlocks; ++j)
-                *reinterpret_cast<int4 *>(ws + kWsPlanBlk + 4 * (q0 + j)) = make_int4(e | (c << 16), offs[e], j, 0);
-        }
+        const int q0 = carry_b + (s >> 16) - nb;
+        if (e < N) blk0[e] = q0;
+        if (a) plan_write_records(e, c, offs[e], q0, nb, ws);
         const int total = __builtin_amdgcn_readlane(s, kWave - 1);
         carry_r += total & 0xffff;
         carry_b += total >> 16;
     }
-    if (tid == 0) {
-        ws[kWsPlanHdr + kPlanB] = min(carry_b, kPlanMaxBlocks);
-        ws[kWsPlanHdr + kPlanM] = plan_down_units_per_item(ps, carry_b);
-        ws[kWsPlanHdr + kPlanNa] = carry_r;
-    }
+    if (tid == 0) plan_write_header(ps, carry_b, carry_r, ws);
 }
 
 // Files pair id p, the i-th of expert e's te pairs, under the expert's block (experts on the direct path only).

@@ -336,47 +336,37 @@ __device__ __forceinline__ float selection_mass_of(const TokenLogits<NS> &raw, i
     const float den = wave_sum(part);
     return gate_fn == kGateSigmoid ? num : num / den;
 }
+// Top-k (Sec. 2.1): lane j < k returns the j-th pick in mye (-1 = none) and its logit in myz.
 template <int NS>
-__device__ __forceinline__ void selection_mass(const TokenLogits<NS> &raw, int t, int gate_fn, float num, float zref,
-                                               float *__restrict__ out)
+__device__ __forceinline__ void token_topk(const TokenLogits<NS> &tl, int k, int &mye, float &myz)
 {
-    const float m = selection_mass_of(raw, gate_fn, num, zref);
-    if (lane_id() == 0) out[t] = m;
-}
-
-// Softmax + top-k (Sec. 2.1): lane j < k returns the j-th pick in mye; writes idx / gate / psum (softmax: the
-// selected probability mass; sigmoid-gated: the sum of the selected scores).
-// tl = the experts the token may use, raw = all of them (the same unless the router is group-limited): the softmax
-// denominator runs over all.
-template <int NS>
-__device__ __forceinline__ int token_topk(const TokenLogits<NS> &tl, const TokenLogits<NS> &raw, int t, int k, int gate_fn,
-                                          int32_t *__restrict__ topk_idx, float *__restrict__ topk_gate,
-                                          float *__restrict__ topk_psum)
-{
-    const int lane = lane_id();
-    int mye = -1;
-    float myz = -INFINITY;
+    mye = -1;
+    myz = -INFINITY;
     wave_topk(tl.v, tl.have, k, [&](int j, int e, float z) {
         put_lane(mye, j, (e == INT_MAX) ? -1 : e);
         put_lane(myz, j, z);
     });
+}
+
+// Gates of a selection and its mass (softmax: the selected probability mass, whose denominator runs over all experts, raw, also
+// of a group-limited router; sigmoid-gated: the sum of the selected scores).  mass may be null.
+template <int NS>
+__device__ __forceinline__ void write_gates(const TokenLogits<NS> &raw, int t, int k, int mye, float myz, int gate_fn,
+                                            float *__restrict__ gate, float *__restrict__ mass)
+{
     float num, zref;
     const float g = selection_gate(k, mye, myz, gate_fn, num, zref);
-    if (lane < k) {
-        topk_idx[(size_t)t * k + lane] = mye;
-        topk_gate[(size_t)t * k + lane] = g;
-    }
-    selection_mass(raw, t, gate_fn, num, zref, topk_psum);
-    return mye;
+    const float m = mass ? selection_mass_of(raw, gate_fn, num, zref) : 0.f;
+    if (lane_id() < k) gate[(size_t)t * k + lane_id()] = g;
+    if (mass && lane_id() == 0) mass[t] = m;
 }
 
 // Bins of every expert for this token into the (LDS) histogram, and the token's pairs per expert.
 template <int NS>
-__device__ __forceinline__ void token_bins(const TokenLogits<NS> &tl, int k, int mye, float alpha, int beta, int *hist,
+__device__ __forceinline__ void token_bins(const TokenLogits<NS> &tl, float zmax, int k, int mye, float alpha, int beta, int *hist,
                                            int *cntb)
 {
     const int lane = lane_id();
-    const float zmax = token_max(tl);
 #pragma unroll
     for (int i = 0; i < NS; ++i)
         if ((tl.have >> i) & 1u) {
@@ -440,40 +430,31 @@ __device__ __forceinline__ void nominate_by_bins(const TokenLogits<NS> &tl, floa
     }
 }
 
-// The same, the token's own picks given in rank order.
+// Fill of the active set up to k from the invoked experts in score order.  Every wave of the workgroup makes the same one for
+// itself (filled, all zero before, is written with the same ones by all of them; nominated stays as it is): no barrier behind it.
 template <int NS>
-__device__ __forceinline__ void token_nominate(const TokenLogits<NS> &tl, int N, int k, float alpha, int beta,
-                                               const int *order, const int *inU, const int32_t *sel, int *inA)
+__device__ __forceinline__ void wave_fill_active(int N, int k, const int *order, const int *inU, const int *nominated, int *filled)
 {
     const int lane = lane_id();
-    const float zmax = token_max(tl);
-    const int es = (lane < k) ? sel[lane] : -1;
-    const bool ok = es >= 0 && es < N;
-    const float zs = logit_of(tl, ok ? es : 0);
-    nominate_by_bins(tl, zmax, ok ? bin_of(zmax, zs, alpha, beta) : beta, N, k, alpha, beta, order, inU, inA);
-}
-
-// Fill of the active set up to k from the invoked experts in score order (one wave; inA / inU in LDS).
-// Returns the number of invoked experts |U|.
-__device__ __forceinline__ int wave_fill_active(int N, int k, const int *order, const int *inU, int *inA, bool do_fill)
-{
-    const int lane = lane_id();
-    int nA = 0, nU = 0;
-    for (int base = 0; base < N; base += kWave) {
-        const int e = base + lane;
-        nA += __popcll(__ballot(e < N && inA[e] != 0));
-        nU += __popcll(__ballot(e < N && inU[e] != 0));
+    int er[NS], nA = 0;
+    bool u[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int r = lane + kWave * i;
+        er[i] = r < N ? order[r] : 0;
+        const bool in = r < N && nominated[er[i]] != 0;
+        u[i] = r < N && !in && inU[er[i]] > 0;
+        nA += __popcll(__ballot(in));
     }
-    int need = do_fill ? k - nA : 0;
-    for (int base = 0; base < N && need > 0; base += kWave) {
-        const int r = base + lane;
-        const int e = (r < N) ? order[r] : 0;
-        const bool c = r < N && inU[e] && !inA[e];
-        const unsigned long long b = __ballot(c);
-        if (c && __popcll(b & ((1ull << lane) - 1ull)) < need) inA[e] = 1;
+    int need = k - nA;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        if (need <= 0) break;
+        const unsigned long long b = __ballot(u[i]);
+        if (u[i] && __popcll(b & ((1ull << lane) - 1ull)) < need) filled[er[i]] = 1;
         need -= __popcll(b);
     }
-    return nU;
+    __builtin_amdgcn_wave_barrier();   // (the wave reads its own writes behind this; LDS serves a wave in order)
 }
 
 // Selection of one token inside the active set (Secs. 3.4, 4): lane j < k holds its j-th expert in mye (-1 = none) and that
@@ -516,42 +497,6 @@ __device__ __forceinline__ void select_active(const TokenLogits<NS> &tl, int k, 
     }
 }
 
-// The same (or the token's unchanged selection when bypassed) from its picks in memory, and the gates.
-// Lane j < k returns the j-th expert; writes new_idx / new_gate.
-// new_psum (may be null): what token_topk writes as topk_psum, for the new selection: its share of the softmax over all
-// N experts (raw), or the sum of its sigmoid scores.  Same arithmetic as there, so an unchanged selection gives the
-// same bits.
-template <int NS>
-__device__ __forceinline__ int token_remap(const TokenLogits<NS> &tl, const TokenLogits<NS> &raw, int t, int N, int k, bool bypass,
-                                           int gate_fn, const int *inA, const int32_t *sel, int32_t *__restrict__ new_idx,
-                                           float *__restrict__ new_gate, float *__restrict__ new_psum)
-{
-    const int lane = lane_id();
-    int mye = -1;
-    float myz = -INFINITY;
-    auto own = [&](int &es, float &zs) {
-        es = (lane < k) ? sel[lane] : -1;
-        if (es >= N) es = -1;
-        zs = logit_of(tl, max(es, 0));
-    };
-    if (bypass) {
-        float zs;
-        own(mye, zs);
-        if (mye >= 0) myz = zs;
-    } else {
-        select_active(tl, k, [&](int e) { return inA[e] != 0; }, own, mye, myz);
-    }
-    mye = max(mye, -1);
-    float num, zref;
-    const float g = selection_gate(k, mye, myz, gate_fn, num, zref);
-    if (lane < k) {
-        store_coherent(&new_idx[(size_t)t * k + lane], mye);   // read by the workgroup that assigns the tokens
-        new_gate[(size_t)t * k + lane] = g;
-    }
-    if (new_psum) selection_mass(raw, t, gate_fn, num, zref, new_psum);
-    return mye;
-}
-
 // Scores as base-T integers (most significant digit = bin 0) from a histogram, and the score order:
 // order[r] = expert with the r-th best score, equal scores to the lower index.  Threads tid < N take part;
 // the caller puts barriers around it.
@@ -563,11 +508,12 @@ __device__ __forceinline__ void score_of(int tid, int N, int T, int beta, const 
         score[tid] = s;
     }
 }
-// The rank of an expert is the number of experts that come before it: N comparisons per thread.  A turn of that loop
-// on 64-bit scores with the index as tie-break costs 64 cycles (measured: 6.8 us at N = 256, 3.6 us at N = 128): the
-// 64-bit compares run at a quarter of the rate.  Whenever score * N + (N - 1 - index) fits 32 bits (always for
-// beta <= 2, T <= 1024) that one key orders the experts the same way, and a turn is one 32-bit compare.  Every
-// thread of the workgroup must call this (it holds a barrier); key is LDS scratch of N words.
+// The rank of an expert is the number of experts that come before it, counted by the sixteen lanes of a row, each of which
+// compares N / 16 of them.  64-bit compares run at a quarter of the rate: whenever score * N + (N - 1 - index) fits 32 bits
+// (always for beta <= 2, T <= 1024) that one key orders the experts the same way.  Every thread of the workgroup must call
+// this (it holds a barrier); key is LDS scratch of N words.
+// (One thread per expert and N compares: nominate_kernel at 128 experts 5.0 -> 4.6 us, 32 tokens, and 6.0 -> 5.5, 512 tokens.)
+template <int NS, int THREADS>
 __device__ __forceinline__ void rank_of(int tid, int N, int T, int beta, const unsigned long long *score, unsigned *key,
                                         int *order)
 {
@@ -577,11 +523,21 @@ __device__ __forceinline__ void rank_of(int tid, int N, int T, int beta, const u
     if (lim + (unsigned long long)N <= (1ull << 32)) {
         if (tid < N) key[tid] = (unsigned)score[tid] * (unsigned)N + (unsigned)(N - 1 - tid);
         __syncthreads();
-        if (tid < N) {
-            const unsigned s = key[tid];
+        constexpr int KF = 4 * NS, kPerPass = THREADS / 16;
+        unsigned kf[KF];
+#pragma unroll
+        for (int j = 0; j < KF; ++j) {
+            const int f = (tid & 15) + 16 * j;
+            kf[j] = f < N ? key[f] : 0u;   // (below or equal to every key)
+        }
+        for (int e0 = 0; e0 < N; e0 += kPerPass) {
+            const int e = e0 + (tid >> 4);
+            const unsigned mine = key[min(e, N - 1)];
             int r = 0;
-            for (int e = 0; e < N; ++e) r += key[e] > s ? 1 : 0;
-            order[r] = tid;
+#pragma unroll
+            for (int j = 0; j < KF; ++j) r += kf[j] > mine ? 1 : 0;
+            r = row_sum_i32(r);   // lane 15 of the row
+            if ((tid & 15) == 15 && e < N) order[r] = e;
         }
         return;
     }
@@ -711,10 +667,7 @@ __global__ __launch_bounds__(kSmallThreads) void routing_small_kernel(
     const TokenLogits<NS> tl = limit_groups(raw, N, rk);
     if (has_token) {
         if (DO_TOPK) {
-            wave_topk(tl.v, tl.have, k, [&](int j, int e, float zz) {
-                put_lane(mye, j, (e == INT_MAX) ? -1 : e);
-                put_lane(myz, j, zz);
-            });
+            token_topk(tl, k, mye, myz);
         } else {
             if (mye < 0 || mye >= N) mye = -1;
             const float zs = logit_of(tl, max(mye, 0));
@@ -726,15 +679,7 @@ __global__ __launch_bounds__(kSmallThreads) void routing_small_kernel(
     // bins into the histogram, pairs per expert
     int newe = mye;
     float newz = myz;
-    if (has_token) {
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-            if ((tl.have >> i) & 1u) {
-                const int q = bin_of(zmax, tl.v[i], alpha, beta);
-                if (q >= 0 && q < beta) atomicAdd(&sh.hist[(lane + kWave * i) * beta + q], 1);
-            }
-        if (lane < k && mye >= 0) atomicAdd(&sh.cntb[mye], 1);
-    }
+    if (has_token) token_bins(tl, zmax, k, mye, alpha, beta, sh.hist, sh.cntb);
     if (!bypass) {
         __syncthreads();
         // Score order: the rank of an expert is the number of experts with a larger key, counted by sixteen lanes per expert.
@@ -770,26 +715,7 @@ __global__ __launch_bounds__(kSmallThreads) void routing_small_kernel(
                              sh.nominated);
         __syncthreads();
         if (has_token) {
-            // the fill of the active set up to k from the invoked experts in score order: every wave makes the same one
-            int er[NS], nA = 0;
-            bool u[NS];
-#pragma unroll
-            for (int i = 0; i < NS; ++i) {
-                const int r = lane + kWave * i;
-                er[i] = r < N ? sh.order[r] : 0;
-                const bool in = r < N && sh.nominated[er[i]] != 0;
-                u[i] = r < N && !in && sh.cntb[er[i]] > 0;
-                nA += __popcll(__ballot(in));
-            }
-            int need = k - nA;
-#pragma unroll
-            for (int i = 0; i < NS; ++i) {
-                if (need <= 0) break;
-                const unsigned long long b = __ballot(u[i]);
-                if (u[i] && __popcll(b & ((1ull << lane) - 1ull)) < need) sh.filled[er[i]] = 1;
-                need -= __popcll(b);
-            }
-            __builtin_amdgcn_wave_barrier();   // (the wave's own writes are read below; LDS serves a wave in order)
+            wave_fill_active<NS>(N, k, sh.order, sh.cntb, sh.nominated, sh.filled);
             select_active(tl, k, [&](int e) { return (sh.nominated[e] | sh.filled[e]) != 0; },
                           [&](int &es, float &zs) { es = mye; zs = myz; }, newe, newz);
         }
@@ -844,8 +770,7 @@ __global__ __launch_bounds__(kSmallThreads) void routing_small_kernel(
                     if (e < N) expert_offsets[e] = pre[i] & 0xffff;
                     if (c > 0) {
                         active_experts[q] = e;
-                        if (ps.units_gu > 0)
-                            *reinterpret_cast<int4 *>(ws + kWsPlanBlk + 4 * q) = make_int4(e | (c << 16), pre[i] & 0xffff, 0, 0);
+                        if (ps.units_gu > 0) plan_write_records(e, c, pre[i] & 0xffff, q, 1, ws);
                     }
                     if (e < N && e >= na) active_experts[e] = -1;
                 }
@@ -853,11 +778,7 @@ __global__ __launch_bounds__(kSmallThreads) void routing_small_kernel(
                 if (lane == 0) {
                     expert_offsets[N] = pairs;
                     num_active_perm[0] = na;
-                    if (ps.units_gu > 0) {
-                        ws[kWsPlanHdr + kPlanB] = na;
-                        ws[kWsPlanHdr + kPlanM] = plan_down_units_per_item(ps, na);
-                        ws[kWsPlanHdr + kPlanNa] = na;
-                    }
+                    if (ps.units_gu > 0) plan_write_header(ps, na, na, ws);
                 }
             }
         }
@@ -924,24 +845,29 @@ __global__ __launch_bounds__(kTokThreads) void token_kernel(const float *__restr
         __syncthreads();
     }
     const int t = blockIdx.x * kTokWaves + wave;
+    const TokenLogits<NS> raw = load_token<NS>(logits + (size_t)(t < T ? t : 0) * N, N);
+    int mye = -1;
+    float myz = -INFINITY;
     if (t < T) {
-        const TokenLogits<NS> raw = load_token<NS>(logits + (size_t)t * N, N);
         const TokenLogits<NS> tl = limit_groups(raw, N, rk);
-        int mye = -1;
         if (DO_TOPK) {
-            mye = token_topk(tl, raw, t, k, rk.gate_fn, topk_idx, topk_gate, topk_psum);
+            token_topk(tl, k, mye, myz);
+            if (lane < k) topk_idx[(size_t)t * k + lane] = mye;
         } else if (lane < k) {
             mye = topk_idx[(size_t)t * k + lane];
             if (mye < 0 || mye >= N) mye = -1;
         }
-        if (DO_BINS) token_bins(tl, k, mye, alpha, beta, hist, cntb);
+        if (DO_BINS) token_bins(tl, token_max(tl), k, mye, alpha, beta, hist, cntb);
     }
-    if (!DO_BINS) return;
-    __syncthreads();
-    for (int i = tid; i < N * beta; i += kTokThreads)
-        if (hist[i]) atomicAdd(&bin_hist[i], hist[i]);
-    for (int i = tid; i < N; i += kTokThreads)
-        if (cntb[i]) atomicAdd(&cnt_before[i], cntb[i]);
+    if (DO_BINS) {
+        __syncthreads();
+        for (int i = tid; i < N * beta; i += kTokThreads)
+            if (hist[i]) atomicAdd(&bin_hist[i], hist[i]);
+        for (int i = tid; i < N; i += kTokThreads)
+            if (cntb[i]) atomicAdd(&cnt_before[i], cntb[i]);
+    }
+    // (last: what the other workgroups' results need is on its way by then)
+    if (DO_TOPK && t < T) write_gates(raw, t, k, mye, myz, rk.gate_fn, topk_gate, topk_psum);
 }
 
 // Every workgroup first turns the finished histogram into scores and the score order (cheap, and it saves a
@@ -957,36 +883,39 @@ __global__ __launch_bounds__(kTokThreads) void nominate_kernel(const float *__re
     __shared__ unsigned long long score[LYNX_MAX_N];
     __shared__ int order[LYNX_MAX_N], inU[LYNX_MAX_N], inA[LYNX_MAX_N];
     __shared__ unsigned key[LYNX_MAX_N];
-    __shared__ int32_t sel[kTokWaves * LYNX_MAX_K];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
     const int t = blockIdx.x * kTokWaves + wave;
     // the token's logits and picks are requested first; the score prologue overlaps the loads
     const TokenLogits<NS> raw = load_token<NS>(logits + (size_t)(t < T ? t : 0) * N, N);
-    if (lane < k) sel[wave * k + lane] = (t < T) ? topk_idx[(size_t)t * k + lane] : -1;
+    const int es = (lane < k && t < T) ? topk_idx[(size_t)t * k + lane] : -1;
     score_of(tid, N, T, beta, bin_hist, score);
     if (tid < N) {
         inU[tid] = cnt_before[tid] > 0;
         inA[tid] = 0;
     }
     const TokenLogits<NS> tl = limit_groups(raw, N, rk);
+    const float zmax = token_max(tl);
+    const bool ok = es >= 0 && es < N;
+    const float zs = logit_of(tl, ok ? es : 0);
+    const int myq = ok ? bin_of(zmax, zs, alpha, beta) : beta;   // the bins of the token's own picks
     __syncthreads();
-    rank_of(tid, N, T, beta, score, key, order);
+    rank_of<NS, kTokThreads>(tid, N, T, beta, score, key, order);
     __syncthreads();
     if (blockIdx.x == 0 && tid < N) ws[kWsOrder + tid] = order[tid];
-    if (t < T) token_nominate(tl, N, k, alpha, beta, order, inU, sel + wave * k, inA);
+    if (t < T) nominate_by_bins(tl, zmax, myq, N, k, alpha, beta, order, inU, inA);
     __syncthreads();
     if (tid < N && inA[tid]) ws[kWsActive + tid] = 1;
 }
 
 template <bool DO_PERMUTE>
 struct RemapShared {
-    int inA[LYNX_MAX_N], inU[LYNX_MAX_N], order[LYNX_MAX_N], cnta[LYNX_MAX_N];
+    int nominated[LYNX_MAX_N], filled[LYNX_MAX_N], inU[LYNX_MAX_N], order[LYNX_MAX_N], cnta[LYNX_MAX_N];
     int flag, n_after;
 };
 template <>
 struct RemapShared<true> {
     PermuteShared perm;
-    int inA[LYNX_MAX_N], inU[LYNX_MAX_N], order[LYNX_MAX_N], cnta[LYNX_MAX_N];
+    int nominated[LYNX_MAX_N], filled[LYNX_MAX_N], inU[LYNX_MAX_N], order[LYNX_MAX_N], cnta[LYNX_MAX_N];
     int flag, n_after;
 };
 
@@ -1008,41 +937,53 @@ __global__ __launch_bounds__(TT) void remap_kernel(const float *__restrict__ log
                                                             int32_t *__restrict__ num_active_perm, PlanShape ps)
 {
     __shared__ RemapShared<DO_PERMUTE> sh;
-    __shared__ int32_t sel[(TT / kWave) * LYNX_MAX_K];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
     const int W = (T + 31) / 32;
     const int t = blockIdx.x * (TT / kWave) + wave;
     // the token's logits and picks are requested first; the prologue overlaps the loads
     const TokenLogits<NS> raw = load_token<NS>(logits + (size_t)(t < T ? t : 0) * N, N);
-    if (lane < k) sel[wave * k + lane] = (t < T) ? topk_idx[(size_t)t * k + lane] : -1;
+    int own = (lane < k && t < T) ? topk_idx[(size_t)t * k + lane] : -1;   // the token's own picks, in rank order
     if (tid < N) {
-        sh.inA[tid] = bypass ? 0 : ws[kWsActive + tid];
+        sh.nominated[tid] = bypass ? 0 : ws[kWsActive + tid];
         sh.inU[tid] = cnt_before[tid] > 0;
         sh.order[tid] = bypass ? tid : ws[kWsOrder + tid];
+        sh.filled[tid] = 0;
         sh.cnta[tid] = 0;
     }
     if (tid == 0) sh.n_after = 0;
     const TokenLogits<NS> tl = limit_groups(raw, N, rk);
-    if (DO_PERMUTE) {   // pairs whose expert is invalid stay unassigned
-        const int p0 = blockIdx.x * (TT / kWave) * k, p1 = min(T * k, p0 + (TT / kWave) * k);
-        for (int p = p0 + tid; p < p1; p += TT) store_coherent(&perm[p], -1);   // overwritten by the last workgroup
-    }
+    if (own < 0 || own >= N) own = -1;
+    const float ownz = logit_of(tl, max(own, 0));
     __syncthreads();
-    if (wave == 0) {
-        const int nU = wave_fill_active(N, k, sh.order, sh.inU, sh.inA, !bypass);
-        if (blockIdx.x == 0 && lane == 0) num_active[0] = nU;
-    }
-    __syncthreads();
+    int mye = -1;
+    float myz = -INFINITY;
     if (t < T) {
-        const int mye = token_remap(tl, raw, t, N, k, bypass != 0, rk.gate_fn, sh.inA, sel + wave * k, new_idx, new_gate,
-                                    new_psum);
-        if (lane < k && mye >= 0) {
-            atomicAdd(&sh.cnta[mye], 1);
-            if (DO_PERMUTE) atomicOr(reinterpret_cast<unsigned *>(ws + kWsMember) + mye * W + (t >> 5), 1u << (t & 31));
+        if (bypass) {
+            mye = own;
+            if (own >= 0) myz = ownz;
+        } else {
+            wave_fill_active<NS>(N, k, sh.order, sh.inU, sh.nominated, sh.filled);
+            select_active(tl, k, [&](int e) { return (sh.nominated[e] | sh.filled[e]) != 0; }, [&](int &es, float &zs) { es = own; zs = ownz; },
+                          mye, myz);
+        }
+        if (lane < k) {
+            store_coherent(&new_idx[(size_t)t * k + lane], mye);   // read by the workgroup that assigns the tokens
+            if (mye >= 0) {
+                atomicAdd(&sh.cnta[mye], 1);
+                if (DO_PERMUTE) atomicOr(reinterpret_cast<unsigned *>(ws + kWsMember) + mye * W + (t >> 5), 1u << (t & 31));
+            }
         }
     }
     __syncthreads();
     if (tid < N && sh.cnta[tid]) atomicAdd(&cnt_after[tid], sh.cnta[tid]);
+    // (behind the stores and atomics that the last workgroup waits for: the two overlap)
+    if (t < T) write_gates(raw, t, k, mye, myz, rk.gate_fn, new_gate, new_psum);
+    if (blockIdx.x == 0 && wave == 0) {
+        int nU = 0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) nU += __popcll(__ballot(lane + kWave * i < N && sh.inU[lane + kWave * i] != 0));
+        if (lane == 0) num_active[0] = nU;
+    }
     if (!last_workgroup(ws + kWsTickets + 2, &sh.flag)) return;
     if (tid < N && load_coherent(&cnt_after[tid]) > 0) atomicAdd(&sh.n_after, 1);
     if constexpr (DO_PERMUTE) {
@@ -1135,14 +1076,11 @@ __global__ __launch_bounds__(kTokThreads) void biased_remap_kernel(const float *
             const float zo = logit_of(tl, mye >= 0 ? mye : 0);   // gates come from the original logits
             if (lane > 0 && mye >= 0) myz = zo;
         }
-        float num, zref;
-        const float g = selection_gate(k, mye, myz, kGateSoftmax, num, zref);
         if (lane < k) {
             new_idx[(size_t)t * k + lane] = mye;
-            new_gate[(size_t)t * k + lane] = g;
             if (mye >= 0) atomicAdd(&cnta[mye], 1);
         }
-        if (new_psum) selection_mass(tl, t, kGateSoftmax, num, zref, new_psum);
+        write_gates(tl, t, k, mye, myz, kGateSoftmax, new_gate, new_psum);
     }
     __syncthreads();
     if (tid < N && cnta[tid]) atomicAdd(&cnt_after[tid], cnta[tid]);

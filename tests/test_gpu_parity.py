@@ -230,6 +230,28 @@ def test_biased_selection_through_the_ffn(L):
 
 # ------------------------------------------------------------------------------------------------ permute
 
+@pytest.mark.parametrize("T,N,k", [(1, 1, 1), (1024, 1, 1), (33, 3, 3), (1023, 256, 7), (1024, 255, 16), (17, 129, 13), (700, 64, 11)])
+def test_permute_with_skipped_pairs(L, T, N, k):
+    """Every number of picks divides pair ids into tokens; pairs without an expert leave -1 at the end of the permutation."""
+    _say(f"permute with skipped pairs T={T} N={N} k={k}")
+    rng = np.random.default_rng([T, N, k])
+    idx = np.stack([rng.permutation(N)[:k] for _ in range(T)]).astype(np.int32)
+    idx[rng.random(idx.shape) < 0.2] = -1
+    idx[rng.random(idx.shape) < 0.05] = N
+    flat = idx.ravel()
+    valid = np.flatnonzero((flat >= 0) & (flat < N))
+    want = np.full(T * k, -1, np.int32)
+    want[:valid.size] = valid[np.argsort(flat[valid], kind="stable")]
+    counts = np.bincount(flat[valid], minlength=N)
+    out = L.lynx_permute(dev(idx), N)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(out["perm"]), want)
+    assert np.array_equal(host(out["offsets"]), np.concatenate([[0], np.cumsum(counts)]))
+    used = np.flatnonzero(counts)
+    assert host(out["num_active"])[0] == used.size
+    assert np.array_equal(host(out["active"]), np.concatenate([used, np.full(N - used.size, -1)]))
+
+
 @pytest.mark.parametrize("T,N,k,seed", [(1, 4, 2, 0), (16, 8, 2, 1), (37, 60, 4, 2), (128, 128, 8, 3), (512, 128, 8, 4),
                                         (1024, 256, 16, 5), (100, 8, 8, 6), (65, 3, 1, 7)])
 def test_permute(L, T, N, k, seed):
