@@ -125,16 +125,43 @@ def new_workspace(T, H, F, N, k, n_shared=0, F_shared=0, device="cuda"):
     return torch.empty(max(workspace_bytes(T, H, F, N, k, n_shared, F_shared), 256), dtype=torch.uint8, device=device)
 
 
+# The routing calls take 4 to 11 tensors of their own each, and on a small batch the host spends longer on them than the GPU on
+# the kernels: sizes go to torch.empty as plain integers (1.3 us against 1.65 with a tuple), and tensors that were just allocated
+# are not checked again (0.26 us each).
+def _outputs(out, made, dtypes):
+    """The call's output dict and the addresses of its entries in the order of dtypes (None: absent from a caller's dict)."""
+    if not out:
+        return made, [t.data_ptr() for t in made.values()]
+    return out, [_ptr(out.get(n) if n == "new_psum" else out[n], dt, n) for n, dt in dtypes.items()]
+
+
+_ROUTE_OUT = dict(logits=F32, idx=I32, gate=F32, psum=F32)
+_REMAP_OUT = dict(new_idx=I32, new_gate=F32, new_psum=F32, cnt_before=I32, cnt_after=I32, bin_hist=I32, num_active=I32)
+_GROUPED_OUT = dict(idx=I32, gate=F32, psum=F32, **_REMAP_OUT)
+_PERMUTE_OUT = dict(offsets=I32, perm=I32, active=I32, num_active=I32)
+
+
+def _route_outputs(out, T, N, k, dev):
+    empty = torch.empty
+    return _outputs(out, None if out else dict(logits=empty(T, N, dtype=F32, device=dev), idx=empty(T, k, dtype=I32, device=dev),
+                                               gate=empty(T, k, dtype=F32, device=dev), psum=empty(T, dtype=F32, device=dev)),
+                    _ROUTE_OUT)
+
+
+def _new_remap(T, N, k, nb, dev):
+    empty = torch.empty
+    return dict(new_idx=empty(T, k, dtype=I32, device=dev), new_gate=empty(T, k, dtype=F32, device=dev),
+                new_psum=empty(T, dtype=F32, device=dev), cnt_before=empty(N, dtype=I32, device=dev),
+                cnt_after=empty(N, dtype=I32, device=dev), bin_hist=empty(N, nb, dtype=I32, device=dev),
+                num_active=empty(2, dtype=I32, device=dev))
+
+
 def lynx_route(x, Wr, bias, k, out=None, _entry="lynx_route"):
     """x [T,H] bf16, Wr [N,H] f32, bias [N] f32 or None -> dict(logits, idx, gate, psum)."""
     T, H = x.shape
     N = Wr.shape[0]
-    dev = x.device
-    o = out or dict(logits=torch.empty((T, N), dtype=F32, device=dev), idx=torch.empty((T, k), dtype=I32, device=dev),
-                    gate=torch.empty((T, k), dtype=F32, device=dev), psum=torch.empty((T,), dtype=F32, device=dev))
-    _check(getattr(lib(), _entry)(_ptr(x, BF16, "x"), _ptr(Wr, F32, "Wr"), _ptr(bias, F32, "bias"), T, H, N, k,
-                                  _ptr(o["logits"], F32, "logits"), _ptr(o["idx"], I32, "idx"),
-                                  _ptr(o["gate"], F32, "gate"), _ptr(o["psum"], F32, "psum"), _stream()))
+    o, p = _route_outputs(out, T, N, k, x.device)
+    _check(getattr(lib(), _entry)(_ptr(x, BF16, "x"), _ptr(Wr, F32, "Wr"), _ptr(bias, F32, "bias"), T, H, N, k, *p, _stream()))
     return o
 
 
@@ -147,13 +174,9 @@ def lynx_route_grouped(x, Wr, bias, k, n_group, topk_group, gate_fn=0, out=None)
     """lynx_route for a group-limited router (gate_fn 0 softmax, 1 sigmoid); "psum" holds the third output."""
     T, H = x.shape
     N = Wr.shape[0]
-    dev = x.device
-    o = out or dict(logits=torch.empty((T, N), dtype=F32, device=dev), idx=torch.empty((T, k), dtype=I32, device=dev),
-                    gate=torch.empty((T, k), dtype=F32, device=dev), psum=torch.empty((T,), dtype=F32, device=dev))
+    o, p = _route_outputs(out, T, N, k, x.device)
     _check(lib().lynx_route_grouped(_ptr(x, BF16, "x"), _ptr(Wr, F32, "Wr"), _ptr(bias, F32, "bias"), T, H, N, k,
-                                    int(n_group), int(topk_group), int(gate_fn), _ptr(o["logits"], F32, "logits"),
-                                    _ptr(o["idx"], I32, "idx"), _ptr(o["gate"], F32, "gate"), _ptr(o["psum"], F32, "psum"),
-                                    _stream()))
+                                    int(n_group), int(topk_group), int(gate_fn), *p, _stream()))
     return o
 
 
@@ -162,23 +185,14 @@ def lynx_affinity_bin_grouped(logits, k, n_group, topk_group, alpha, beta, gate_
     cnt_after, bin_hist, num_active)."""
     T, N = logits.shape
     dev = logits.device
-    nb = max(int(beta), 1)
-    o = out or dict(idx=torch.empty((T, k), dtype=I32, device=dev), gate=torch.empty((T, k), dtype=F32, device=dev),
-                    psum=torch.empty((T,), dtype=F32, device=dev),
-                    new_idx=torch.empty((T, k), dtype=I32, device=dev), new_gate=torch.empty((T, k), dtype=F32, device=dev),
-                    new_psum=torch.empty((T,), dtype=F32, device=dev),
-                    cnt_before=torch.empty((N,), dtype=I32, device=dev), cnt_after=torch.empty((N,), dtype=I32, device=dev),
-                    bin_hist=torch.empty((N, nb), dtype=I32, device=dev), num_active=torch.empty((2,), dtype=I32, device=dev))
+    empty = torch.empty
+    o, p = _outputs(out, None if out else dict(idx=empty(T, k, dtype=I32, device=dev), gate=empty(T, k, dtype=F32, device=dev),
+                                               psum=empty(T, dtype=F32, device=dev), **_new_remap(T, N, k, max(int(beta), 1), dev)),
+                    _GROUPED_OUT)
     if workspace is None:
-        workspace = torch.empty(65536, dtype=torch.uint8, device=dev)
+        workspace = empty(65536, dtype=torch.uint8, device=dev)
     _check(lib().lynx_affinity_bin_grouped(_ptr(logits, F32, "logits"), T, N, int(k), int(n_group), int(topk_group),
-                                           int(gate_fn), float(alpha), int(beta), int(enable), _ptr(o["idx"], I32, "idx"),
-                                           _ptr(o["gate"], F32, "gate"), _ptr(o["psum"], F32, "psum"),
-                                           _ptr(o["new_idx"], I32, "new_idx"), _ptr(o["new_gate"], F32, "new_gate"),
-                                           _ptr(o.get("new_psum"), F32, "new_psum"),
-                                           _ptr(o["cnt_before"], I32, "cnt_before"), _ptr(o["cnt_after"], I32, "cnt_after"),
-                                           _ptr(o["bin_hist"], I32, "bin_hist"), _ptr(o["num_active"], I32, "num_active"),
-                                           workspace.data_ptr(), _stream()))
+                                           int(gate_fn), float(alpha), int(beta), int(enable), *p, workspace.data_ptr(), _stream()))
     return o
 
 
@@ -187,20 +201,11 @@ def lynx_affinity_bin(logits, topk_idx, alpha, beta, enable=1, workspace=None, o
     T, N = logits.shape
     k = topk_idx.shape[1]
     dev = logits.device
-    nb = max(int(beta), 1)
-    o = out or dict(new_idx=torch.empty((T, k), dtype=I32, device=dev), new_gate=torch.empty((T, k), dtype=F32, device=dev),
-                    new_psum=torch.empty((T,), dtype=F32, device=dev),
-                    cnt_before=torch.empty((N,), dtype=I32, device=dev), cnt_after=torch.empty((N,), dtype=I32, device=dev),
-                    bin_hist=torch.empty((N, nb), dtype=I32, device=dev), num_active=torch.empty((2,), dtype=I32, device=dev))
+    o, p = _outputs(out, None if out else _new_remap(T, N, k, max(int(beta), 1), dev), _REMAP_OUT)
     if workspace is None:
         workspace = torch.empty(65536, dtype=torch.uint8, device=dev)
-    ws = workspace.data_ptr()
     _check(getattr(lib(), _entry)(_ptr(logits, F32, "logits"), _ptr(topk_idx, I32, "topk_idx"), T, N, k, float(alpha),
-                                  int(beta), int(enable), _ptr(o["new_idx"], I32, "new_idx"),
-                                  _ptr(o["new_gate"], F32, "new_gate"), _ptr(o.get("new_psum"), F32, "new_psum"),
-                                  _ptr(o["cnt_before"], I32, "cnt_before"),
-                                  _ptr(o["cnt_after"], I32, "cnt_after"), _ptr(o["bin_hist"], I32, "bin_hist"),
-                                  _ptr(o["num_active"], I32, "num_active"), ws, _stream()))
+                                  int(beta), int(enable), *p, workspace.data_ptr(), _stream()))
     return o
 
 
@@ -214,20 +219,11 @@ def lynx_affinity_bin_biased(logits, topk_idx, alpha, beta, gamma, enable=1, wor
     T, N = logits.shape
     k = topk_idx.shape[1]
     dev = logits.device
-    nb = max(int(beta), 1)
-    o = out or dict(new_idx=torch.empty((T, k), dtype=I32, device=dev), new_gate=torch.empty((T, k), dtype=F32, device=dev),
-                    new_psum=torch.empty((T,), dtype=F32, device=dev),
-                    cnt_before=torch.empty((N,), dtype=I32, device=dev), cnt_after=torch.empty((N,), dtype=I32, device=dev),
-                    bin_hist=torch.empty((N, nb), dtype=I32, device=dev), num_active=torch.empty((2,), dtype=I32, device=dev))
+    o, p = _outputs(out, None if out else _new_remap(T, N, k, max(int(beta), 1), dev), _REMAP_OUT)
     if workspace is None:
         workspace = torch.empty(65536, dtype=torch.uint8, device=dev)
     _check(lib().lynx_affinity_bin_biased(_ptr(logits, F32, "logits"), _ptr(topk_idx, I32, "topk_idx"), T, N, k,
-                                          float(alpha), int(beta), float(gamma), int(enable),
-                                          _ptr(o["new_idx"], I32, "new_idx"), _ptr(o["new_gate"], F32, "new_gate"),
-                                          _ptr(o.get("new_psum"), F32, "new_psum"),
-                                          _ptr(o["cnt_before"], I32, "cnt_before"), _ptr(o["cnt_after"], I32, "cnt_after"),
-                                          _ptr(o["bin_hist"], I32, "bin_hist"), _ptr(o["num_active"], I32, "num_active"),
-                                          workspace.data_ptr(), _stream()))
+                                          float(alpha), int(beta), float(gamma), int(enable), *p, workspace.data_ptr(), _stream()))
     return o
 
 
@@ -235,11 +231,11 @@ def lynx_permute(idx, N, out=None):
     """idx [T,k] i32 -> dict(offsets [N+1], perm [T*k], active [N], num_active [1])."""
     T, k = idx.shape
     dev = idx.device
-    o = out or dict(offsets=torch.empty((N + 1,), dtype=I32, device=dev), perm=torch.empty((T * k,), dtype=I32, device=dev),
-                    active=torch.empty((N,), dtype=I32, device=dev), num_active=torch.empty((1,), dtype=I32, device=dev))
-    _check(lib().lynx_permute(_ptr(idx, I32, "idx"), T, N, k, _ptr(o["offsets"], I32, "offsets"),
-                              _ptr(o["perm"], I32, "perm"), _ptr(o["active"], I32, "active"),
-                              _ptr(o["num_active"], I32, "num_active"), _stream()))
+    empty = torch.empty
+    o, p = _outputs(out, None if out else dict(offsets=empty(N + 1, dtype=I32, device=dev), perm=empty(T * k, dtype=I32, device=dev),
+                                               active=empty(N, dtype=I32, device=dev), num_active=empty(1, dtype=I32, device=dev)),
+                    _PERMUTE_OUT)
+    _check(lib().lynx_permute(_ptr(idx, I32, "idx"), T, N, k, *p, _stream()))
     return o
 
 
