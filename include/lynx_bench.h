@@ -63,12 +63,15 @@ int lynx_read_probe(const void *buf, size_t bytes, int non_temporal, uint32_t *s
  *                               at most 64 tokens)
  *   LYNX_DEBUG_DOWN_K_WAVES     K slices that the four waves of a down-projection workgroup form (1, 2, or 4 for batches
  *                               of at most 16 tokens; default 0 = the library's rule)
+ *   LYNX_DEBUG_WIDE_KERNEL      1: batches of more than 64 tokens with bf16 weights take the kernel for token blocks of 256 at
+ *                               any size (default 0 = the library's rule)
  */
 #define LYNX_DEBUG_SPIN_LIMIT 1
 #define LYNX_DEBUG_TARGET_BIAS 2
 #define LYNX_DEBUG_DOWN_ITEM_CAP 3
 #define LYNX_DEBUG_DOWN_ITEM_UNITS 4
 #define LYNX_DEBUG_DOWN_K_WAVES 5
+#define LYNX_DEBUG_WIDE_KERNEL 6
 int lynx_debug_set(int what, int value);
 
 #ifdef __cplusplus

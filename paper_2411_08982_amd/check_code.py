@@ -9,6 +9,10 @@ Waits: a wave reports its pieces of a chunk of token rows at a barrier, before w
 until at most as many loads are outstanding as it has issued behind them, a number that follows from its source as long as
 the compiler neither drops nor merges loads.  They are counted again in the machine code, ahead of every barrier behind a
 direct-to-LDS load, in the order of the listing (the kernel's loops around them are laid out straight).
+
+Operands: the wide kernel's matrix instructions are written out, so the compiler does not keep the two wait states between a VALU
+instruction that writes an operand of theirs and its use.  Their operands come from loads; that no VALU instruction writes one
+so late is checked in the machine code.
 """
 from __future__ import annotations
 
@@ -19,6 +23,7 @@ import tempfile
 
 LLVM = os.environ.get("ROCM_LLVM_BIN", "/opt/rocm/llvm/bin")
 KERNEL = "ffn_kernel"
+WIDE = "ffn_wide_kernel"
 STAGE_END = 65536     # 2 * kStageBuffer
 STAGE_ALIGN = 4096    # kStageAlign
 
@@ -82,10 +87,48 @@ def check_waits(listing: str) -> int:
     return barriers
 
 
+def _vector_registers(operand: str) -> set:
+    m = re.fullmatch(r"v(?:\[(\d+):(\d+)\]|(\d+))", operand)
+    if not m:
+        return set()
+    lo = int(m.group(1) or m.group(3))
+    return set(range(lo, int(m.group(2) or lo) + 1))
+
+
+def check_operands(listing: str) -> int:
+    """Raises if a VALU instruction of the wide kernel writes an operand of a matrix instruction within two wait states of its
+    use; the number of matrix instructions."""
+    products = 0
+    name = ""
+    recent = []           # (wait states it stands for, vector registers that a VALU instruction writes)
+    for line in listing.splitlines():
+        head = re.match(r"[0-9a-f]+ <(\S+)>:", line)
+        if head:
+            name, recent = head.group(1), []
+            continue
+        words = line.split("//")[0].replace(",", " ").split()
+        if not words or WIDE not in name:
+            continue
+        op = words[0]
+        if op.startswith("v_mfma"):
+            products += 1
+            states = 0
+            for n, written in reversed(recent):
+                if states >= 2:
+                    break
+                if written & (_vector_registers(words[2]) | _vector_registers(words[3])):
+                    raise RuntimeError(f"{name}: {line.strip()} uses a register that was written {states} states before")
+                states += n
+        valu = op.startswith("v_") and not op.startswith(("v_mfma", "v_cmp", "v_readlane", "v_readfirstlane"))
+        recent = recent[-3:] + [(int(words[1]) + 1 if op == "s_nop" else 1, _vector_registers(words[1]) if valu else set())]
+    return products
+
+
 def check(lib_path: str) -> None:
-    kernels = barriers = 0
+    kernels = barriers = products = 0
     for notes, listing in code_object_texts(lib_path):
         kernels += check_placement(notes)
         barriers += check_waits(listing)
-    if kernels == 0 or barriers < kernels:
-        raise RuntimeError(f"{lib_path}: {kernels} kernels and {barriers} barriers found: the checks do not read this library")
+        products += check_operands(listing)
+    if kernels == 0 or barriers < kernels or products == 0:
+        raise RuntimeError(f"{lib_path}: {kernels} kernels, {barriers} barriers and {products} products found: the checks do not read this library")

@@ -953,6 +953,34 @@ __device__ __forceinline__ int done_slot(const GemmParams &p, const WorkItem &w)
                           : kWsDoneWords + done_shared_slot(w.shared_s * p.shared_tblocks + w.tok0 / p.tok_block);
 }
 
+// Waits for this expert's (this token block's) intermediate vectors (down projection in the same launch as
+// gate/up; gate/up workgroups report row tiles: four each, or one for a workgroup of a single tile).
+__device__ __forceinline__ void wait_for_gate_up(const GemmParams &p, const WorkItem &w, const FfnParams &fp, const int32_t *counter)
+{
+    if (!fp.wait) return;
+    const int items = w.shared_s < 0 ? fp.gu.tiles_r * plan_token_blocks(w.te_all, p.tok_block) : fp.gu.tiles_s;
+    const int target = kFfnWaves * items + fp.target_bias;
+    if (threadIdx.x == 0) {
+        int polls = 0;
+        while (load_coherent(counter) < target) {
+            if (++polls > fp.spin_limit) {
+                atomicOr(fp.flags, 1);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+    }
+    __syncthreads();
+}
+
+// Reports that this workgroup's part of h is complete in memory.
+__device__ __forceinline__ void report_gate_up(int32_t *counter, int row_tiles)
+{
+    wait_memory_complete();
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(counter, row_tiles);
+}
+
 // 16-row tiles per wave on the staged path.  Two in the large-batch kernels (gate/up, and down with undivided K): a token
 // fragment read from LDS then feeds four MFMAs (gate/up) or two (down), and a unit of 128 rows stages the tokens half as
 // often as two of 64.
@@ -976,23 +1004,8 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
     }
     const int unit0 = w.tile;
     LYNX_TS(1);
-    // Waits for this expert's (this token block's) intermediate vectors (down projection in the same launch as
-    // gate/up; gate/up workgroups report row tiles: four each, or one for a workgroup of a single tile).
     auto wait_for_h = [&]() {
-        if (DUAL || !fp.wait) return;
-        const int items = w.shared_s < 0 ? fp.gu.tiles_r * plan_token_blocks(w.te_all, p.tok_block) : fp.gu.tiles_s;
-        const int target = kFfnWaves * items + fp.target_bias;
-        if (threadIdx.x == 0) {
-            int polls = 0;
-            while (load_coherent(counter) < target) {
-                if (++polls > fp.spin_limit) {
-                    atomicOr(fp.flags, 1);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(8);
-            }
-        }
-        __syncthreads();
+        if (!DUAL) wait_for_gate_up(p, w, fp, counter);
     };
     // (With K in four slices a chunk of sixteen rows holds half a turn of the ring of the quantised formats.  Such kernels are
     // for at most eight tokens, but an assignment that sends a token to one expert twice can still give it more rows.)
@@ -1085,11 +1098,7 @@ __device__ __forceinline__ void expert_work(const GemmParams &p, int b, const Ff
         }
     }
     LYNX_TS(3);
-    if (DUAL && fp.wait) {   // report: this workgroup's part of h is complete in memory
-        wait_memory_complete();
-        __syncthreads();
-        if (threadIdx.x == 0) atomicAdd(counter, KW == 1 ? kFfnWaves : 1);
-    }
+    if (DUAL && fp.wait) report_gate_up(counter, KW == 1 ? kFfnWaves : 1);
 }
 
 // Workgroups per CU: the registers (256 per wave) and the LDS buffers both come to two.  The dispatcher fills a CU up to its
@@ -1142,6 +1151,234 @@ __global__ __launch_bounds__(kFfnThreads, kWgPerCu) void ffn_kernel(FfnParams fp
     } else {
         expert_work<false, KWD, BIG, WF>(fp.dn, b - fp.gu_blocks, fp, stage0, stage1, rowoff, outrow);
     }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Wide kernel (bf16 weights, batches whose experts hold more than 128 tokens on average): token blocks of 256, units of 128
+// gate/up rows or 256 down rows, one workgroup of four waves per CU with 512 registers each.
+// With blocks of 128 tokens such a batch is bound by what passes the L2: every block of an expert streams its weights again
+// (Mixtral shapes, 1000 tokens: 6.6 GB, at the 7.2 TB/s that memory and the memory-side cache both deliver; with the weights read
+// from one place, 1106 -> 740 us).  Twice the tokens per weight byte need 256 sums per lane, all of the accumulator registers,
+// and leave one wave per SIMD, so nothing but the order of the instructions hides a latency:
+//   * every token fragment read from LDS feeds four products (64 cycles of matrix work), BQ fragments ahead, also across
+//     the end of a chunk, and everything that is not a product is issued between two products, one thing at a time;
+//   * token rows travel through registers, requested two chunks (128 columns) before they are written to LDS, as far ahead as the
+//     weights: loads return in order, so whatever is waited for earlier shortens the way of everything behind it;
+//   * three LDS buffers and one barrier per chunk, in the middle of its products: a wave that is past it may write the
+//     buffer after next while another still reads the last one.
+// Mixtral shapes, 1000 tokens, us per layer 1107 -> 880 (gate/up 670 -> 510, down 417 -> 330): matrix cores busy half of the
+// time a wave is there (8 of 10 states with the weights in the caches), gate/up 5.2 rounds of workgroups, down 208 of them, one
+// to a CU.  On the way: products in fours with the rest behind them 1008, dealt out between them 957; a turn of two chunks without
+// a way out in the middle 915; loads further apart, 866 to 881.
+// ---------------------------------------------------------------------------------------------------
+constexpr int kWideTokens = 256;             // tokens per block
+constexpr int kWideCols = 64;                // columns of a chunk: whole 128-byte lines of a token row
+constexpr int kWideBuffer = kWideTokens * kWideCols * 2;
+
+// One product.  Written out, because the compiler (left alone it keeps the sums in the other half of the registers, where they do
+// not fit beside the operands, and spills hundreds) has to be told that they live in accumulator registers.  It does not know what
+// is inside and inserts no waits between this and VALU instructions: settle_sums() stands between the sums and ordinary code, no
+// sum is used again for 4 * NT products, and the operands come from loads (the build checks that no VALU instruction writes one
+// in the two states before its use).
+__device__ __forceinline__ void mfma_acc(f32x4 &c, bf16x8 a, bf16x8 b)
+{
+    asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+// Between the products and ordinary instructions on the sums, in both directions: more states than the longest wait.
+template <int S, int NT>
+__device__ __forceinline__ void settle_sums(f32x4 (&acc)[S][NT])
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < S; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+a"(acc[j][nt]));
+    asm volatile("s_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <bool DUAL, int NT>
+__device__ __forceinline__ void expert_wide(const WorkItem &w, const int *rowoff, const int *outrow, char *stage)
+{
+    constexpr int MATS = DUAL ? 2 : 1, S = 4, RT = S / MATS;   // weight streams of a wave: RT row tiles of MATS matrices
+    constexpr int D = 4;                         // k-steps (32 columns) in the weight ring: two chunks
+    constexpr int LPT = NT / 2;                  // token loads per thread and chunk: 32 rows x 128 bytes each
+    constexpr int BQ = NT < 8 ? 3 : 7;           // token fragments read ahead: 64 cycles of products each
+    constexpr int WS = NT < 8 ? 1 : NT < 12 ? 2 : 3;   // fragments between the weight loads of a k-step
+    constexpr int WSTEP = MATS * kWave;
+    static_assert(NT % 2 == 0 && NT * 16 * kWideCols * 2 <= kWideBuffer, "a chunk must fit its buffer");
+
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int KTrow = w.K / 32, KT = w.ksteps, K = KT * 32, last = KT - 1;
+    const int rt = (w.tile * kFfnWaves + wv) * RT;
+    const bool wave_active = rt * 16 < w.R;      // idle waves read tile 0 (in bounds) and store nothing
+    const int rtc = wave_active ? rt : 0;
+    int tile_at[RT];                             // row tiles past the last row re-read the wave's first
+#pragma unroll
+    for (int r = 0; r < RT; ++r) tile_at[r] = (rtc + r) * 16 < w.R ? r * KTrow * WSTEP : 0;
+
+    const BufferRsrc rb = token_rows_resource(w.B + (size_t)w.kbeg * 32);
+    const int piece = tid & 7;                   // 16-byte piece of a row's 128
+    unsigned ro[LPT];                            // byte offset of this thread's piece in its rows, out of range = no token
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+        const int o = rowoff[(tid >> 3) + 32 * i];
+        ro[i] = o >= 0 ? 2u * (unsigned)o + (unsigned)piece * 16u : kNoToken;
+    }
+    u32x4 xr[2][LPT];
+    auto load_x1 = [&](int set, int i, int c) {  // (columns past the end, and chunks, arrive as zeros)
+        const bool in = c * kWideCols + piece * 8 < K;
+        asm volatile("" : "+s"(c));
+        xr[set][i] = __builtin_amdgcn_raw_buffer_load_b128(rb, in ? ro[i] : kNoToken, c * (kWideCols * 2), 0);
+    };
+    // A row's eight pieces lie in the order piece ^ (row % 8): eight rows of a fragment, and the row that eight lanes write, lie in
+    // different banks.
+    const int xst = (tid >> 3) * 128 + (piece ^ ((tid >> 3) & 7)) * 16;
+    auto store_x1 = [&](int set, int i, char *buf) { *reinterpret_cast<u32x4 *>(buf + xst + i * 4096) = xr[set][i]; };
+    int xaddr[2];                                // this lane's place in a fragment, for each of a chunk's two k-steps
+#pragma unroll
+    for (int q = 0; q < 2; ++q) xaddr[q] = (lane & 15) * 128 + ((q * 4 + (lane >> 4)) ^ (lane & 7)) * 16;
+
+    const BufferRsrc rw = weights_resource(w.W + ((size_t)rtc * KTrow + w.kbeg) * WSTEP);
+    uint4 wr[D][S];
+    auto load_w1 = [&](int slot, int j, int s) {   // stream m + MATS * r: matrix m of row tile r; past the end nothing is fetched
+        wr[slot][j] = ring_load_weights<true>(rw, s * WSTEP + (j % MATS) * kWave + tile_at[j / MATS], s <= last);
+    };
+    f32x4 acc[S][NT];
+#pragma unroll
+    for (int j = 0; j < S; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto barrier = [&]() {                       // this wave's writes to LDS are done; everybody's are behind it
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(15 | 3 << 14 | 7 << 4 | 0 << 8);   // LDS only
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // (the order of the loop below, so that the compiler counts the same loads behind each one on both ways into it)
+    auto load_wx = [&](int s, int set, int c) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if (nt % WS == 0 && nt / WS < S) load_w1(s, nt / WS, s);
+            if (nt % 2 == 1) load_x1(set, nt / 2, c);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) load_x1(0, i, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_wx(0, 1, 1);
+#pragma unroll
+    for (int j = 0; j < S; ++j) load_w1(1, j, 1);
+    settle_sums(acc);
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) store_x1(0, i, stage);
+    load_wx(2, 0, 2);
+    barrier();
+
+    constexpr int G = 2 * NT;                    // fragments of a chunk: k-step i / NT, column tile i % NT
+    constexpr int NB = BQ + 1;                   // fragment i lies in bq[i % NB]
+    constexpr bool kEarly = NT / 2 <= BQ;        // the reads that run into the next chunk begin before half of the second k-step
+    static_assert(G % NB == 0 && (kEarly ? BQ <= NT : NT / 2 - 1 + BQ < NT), "nothing of the next chunk is read ahead of the barrier");
+    char *cur = stage, *nxt = stage + kWideBuffer, *far = stage + 2 * kWideBuffer;
+    auto read_b = [&](int i) {
+        const char *buf = i < G ? cur : nxt;
+        const int j = i < G ? i : i - G;
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(buf + xaddr[j / NT] + (j % NT) * 2048));
+    };
+    bf16x8 bq[NB];
+#pragma unroll
+    for (int i = 0; i < BQ; ++i) bq[i] = read_b(i);
+    // (Two chunks a turn, also where the second one is all zeros: with a way out between them the compiler takes the loads of the
+    // first for the newest at the top of the loop and waits for nearly all of them.)
+    for (int c0 = 0; c0 < KT; c0 += 2 * 2) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int c = c0 / 2 + half;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int slot = half * 2 + q;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    // A wave is alone on its SIMD, and what it issues between two products costs nothing while the first one
+                    // runs; behind four products in a row it does.  So everything else is dealt out between them.
+                    const int i = q * NT + nt;
+                    const bf16x8 b = bq[i % NB];
+#pragma unroll
+                    for (int j = 0; j < S; ++j) {
+                        mfma_acc(acc[j][nt], __builtin_bit_cast(bf16x8, wr[slot][j]), b);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (j == 0) bq[(i + BQ) % NB] = read_b(i + BQ);
+                        if (j == 1 && nt % WS == 0 && nt / WS < S) load_w1((slot + 3) % D, nt / WS, 2 * c + q + 3);   // the slot of the last k-step
+                        if (q == 0 && j == 2 && nt >= NT / 2) store_x1(1 - half, nt - NT / 2, nxt);    // chunk c + 1
+                        if (q == 1 && j == 2 && nt % 2 == 1) load_x1(1 - half, nt / 2, c + 3);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (kEarly ? q == 0 && nt == NT - 1 : q == 1 && nt == NT / 2 - 1) barrier();
+                }
+            }
+            char *t = cur;
+            cur = nxt;
+            nxt = far;
+            far = t;
+        }
+    }
+    settle_sums(acc);
+    if (!wave_active) return;
+    int orow[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) orow[nt] = outrow[nt * 16 + (lane & 15)];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        if ((rt + r) * 16 >= w.R) break;
+        epilogue<DUAL, NT, 0>(acc[r * MATS], acc[r * MATS + MATS - 1], w.out, w.ldo, (rt + r) * 16, orow, w.sc, w.R);
+    }
+}
+
+template <bool DUAL>
+__device__ __forceinline__ void wide_work(const GemmParams &p, int b, const FfnParams &fp, char *stage, int *rowoff, int *outrow)
+{
+    int units;
+    LYNX_TS_BEGIN(DUAL ? 1 : 0, b);
+    const WorkItem w = resolve_item<DUAL, 0>(p, b, units);
+    if (!w.valid) return;
+    int32_t *counter = fp.done + done_slot(p, w);
+    LYNX_TS(1);
+    if (!DUAL) wait_for_gate_up(p, w, fp, counter);
+    LYNX_TS(2);
+    const int nb = w.Te - w.tok0;
+    if ((int)threadIdx.x < kWideTokens) {
+        int ro, orow;
+        token_rows<DUAL>(p, w, (int)threadIdx.x < nb ? w.tok0 + (int)threadIdx.x : w.Te, ro, orow);
+        rowoff[threadIdx.x] = ro;
+        outrow[threadIdx.x] = orow;
+    }
+    __syncthreads();
+    if (nb <= 64)
+        expert_wide<DUAL, 4>(w, rowoff, outrow, stage);
+    else if (nb <= 128)
+        expert_wide<DUAL, 8>(w, rowoff, outrow, stage);
+    else if (nb <= 192)
+        expert_wide<DUAL, 12>(w, rowoff, outrow, stage);
+    else
+        expert_wide<DUAL, 16>(w, rowoff, outrow, stage);
+    LYNX_TS(3);
+    if (DUAL && fp.wait) report_gate_up(counter, kFfnWaves);
+}
+
+__global__ __launch_bounds__(kFfnThreads, 1) void ffn_wide_kernel(FfnParams fp)
+{
+    static_assert(kWideTokens <= kFfnThreads, "a thread per token of the tables");
+    __shared__ __attribute__((aligned(128))) char stage[3 * kWideBuffer];
+    __shared__ int rowoff[kWideTokens], outrow[kWideTokens];
+    const int b = blockIdx.x + fp.block0;
+    if (b < fp.gu_blocks)
+        wide_work<true>(fp.gu, b, fp, stage, rowoff, outrow);
+    else
+        wide_work<false>(fp.dn, b - fp.gu_blocks, fp, stage, rowoff, outrow);
 }
 
 // The plan from a caller's token assignment (lynx_moe_ffn after lynx_permute): the experts with a valid, non-empty
@@ -1440,15 +1677,17 @@ struct Tunables {
     std::atomic<int> dn_cap{768};      // down items the grid aims at (two per CU are resident: 512)
     std::atomic<int> dn_m_max{1};      // most row units per down item
     std::atomic<int> dn_kw{0};         // 0 = the rule of pick_k_waves, else the K slices of a down workgroup's waves
+    std::atomic<int> wide{0};          // 1 = the wide kernel for every batch that it can take
 };
 static Tunables g_tune;
 
 // Everything the host decides from the sizes alone.
 struct FfnShape {
     int kwd;            // K slices of a down workgroup's waves
-    int big;            // 0 = at most 64 tokens; 1, 2 = larger batches, gate/up units of 64 or of 128 rows
+    int big;            // 0 = at most 64 tokens; 1, 2 = larger batches, gate/up units of 64 or of 128 rows; 3 = the wide kernel
     bool single;        // one launch for both projections
     int tok_block;
+    int rows_gu, rows_dn;   // rows of a gate/up unit, of a down workgroup
     int max_blocks;     // most (expert, token block) pairs of a batch
     PlanShape plan;
 };
@@ -1469,6 +1708,18 @@ static bool fill_tail(int T, int N, int k, long down_items)
     return T >= 8 && T <= kTokBlock && down_items >= 2 * kCus && (long)N * ((T * k + kTokBlock - 1) / kTokBlock) <= kPlanMaxBlocks;
 }
 
+// The wide kernel pays with more than 128 tokens per expert on average, where its workgroups are long (a quarter of a wave's time
+// is start and end at H = 2048) and several per CU.  us, ffn_kernel against the wide one: Mixtral shapes, 400 tokens 674 against
+// 685, 520 tokens 744 -> 724, 700 tokens 823 -> 759, 1000 tokens 1085 -> 870; 12 experts of 4096 x 4096, 400 tokens 256 against
+// 281, 1000 tokens 363 -> 328; 16 experts of 2048 x 2048 (four picks), 1000 tokens 191 against 193; 8 of them (two picks) 107
+// against 114; 8 experts of 2048 x 4096, 600 tokens 192 against 204.
+static bool wide_pays(int T, int H, int F, int N, int k, int format)
+{
+    if (format != 0 || T <= kTokBlock) return false;
+    if (g_tune.wide.load()) return true;
+    return H >= 4096 && (long)T * k > 128L * N && (long)F * T * k >= 240L * 128 * kWideTokens;
+}
+
 static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int format)
 {
     FfnShape s;
@@ -1487,11 +1738,17 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     const bool sooner = format == 2 && (long)N * F >= 256L * 128 && (long)T * k >= 32L * N;
     const bool many = sooner || (long)T * k > (long)kTokBlock * N;
     s.big = T <= kTokBlock ? 0 : many ? 2 : 1;
-    s.tok_block = staged_tokens(s.big, format);
+    if (wide_pays(T, H, F, N, k, format)) {
+        s.big = 3;
+        s.kwd = 1;
+    }
+    s.tok_block = s.big == 3 ? kWideTokens : staged_tokens(s.big, format);
     s.max_blocks = plan_max_blocks(T, N, k, s.tok_block);
     s.plan.shared_pairs = n_shared * (T > kDirectMaxTokens ? (T + s.tok_block - 1) / s.tok_block : 1);
-    const int rows_dn = 16 * (kFfnWaves / s.kwd) * 2;
-    const int rows_gu = 64 * staged_row_tiles(true, 1, s.big);
+    const int rows_dn = s.big == 3 ? 256 : 16 * (kFfnWaves / s.kwd) * 2;
+    const int rows_gu = s.big == 3 ? 128 : 64 * staged_row_tiles(true, 1, s.big);
+    s.rows_gu = rows_gu;
+    s.rows_dn = rows_dn;
     s.plan.units_gu = (F + rows_gu - 1) / rows_gu;
     s.plan.units_dn = (H + rows_dn - 1) / rows_dn;
     s.single = single_launch(T, F) || (format != 0 && fill_tail(T, N, k, (long)s.plan.units_dn * max_experts));
@@ -1545,8 +1802,8 @@ template <int WF>
 static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
 {
     const GemmParams &d = fp.dn;
-    set_tiles(fp.gu, sh.plan.units_gu, 64 * staged_row_tiles(true, 1, sh.big), sh.plan.units_gu * sh.max_blocks, sh.tok_block);   // gate/up: four row tiles per workgroup
-    set_tiles(fp.dn, sh.plan.units_dn, 16 * (kFfnWaves / sh.kwd) * 2, plan_down_grid(sh.plan, sh.max_blocks), sh.tok_block);
+    set_tiles(fp.gu, sh.plan.units_gu, sh.rows_gu, sh.plan.units_gu * sh.max_blocks, sh.tok_block);
+    set_tiles(fp.dn, sh.plan.units_dn, sh.rows_dn, plan_down_grid(sh.plan, sh.max_blocks), sh.tok_block);
     fp.gu.dn_m_max = fp.dn.dn_m_max = sh.plan.dn_m_max;
     // the split of the last round needs up to three more workgroups per workgroup it replaces
     // (not for batches of more than 32 tokens: more and more experts are then on the staged path, whose unit is the
@@ -1560,7 +1817,9 @@ static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
         fp.wait = sh.single ? 1 : 0;
         fp.block0 = part == 0 ? 0 : fp.gu_blocks;
         const unsigned blocks = sh.single ? (unsigned)fp.gu_blocks + dn_blocks : part == 0 ? (unsigned)fp.gu_blocks : dn_blocks;
-        if (sh.big == 2 && sh.kwd == 1)
+        if (WF == 0 && sh.big == 3)
+            hipLaunchKernelGGL(ffn_wide_kernel, dim3(blocks), dim3(kFfnThreads), 0, st, fp);
+        else if (sh.big == 2 && sh.kwd == 1)
             launch_kernel<1, 2, WF>(fp, blocks, st);
         else if (sh.big == 2)
             launch_kernel<2, 2, WF>(fp, blocks, st);
@@ -1600,6 +1859,7 @@ extern "C" int lynx_debug_set(int what, int value)
     case LYNX_DEBUG_DOWN_ITEM_CAP: g_tune.dn_cap.store(value <= 0 ? 768 : value); return LYNX_OK;
     case LYNX_DEBUG_DOWN_ITEM_UNITS: g_tune.dn_m_max.store(value <= 0 ? 1 : value); return LYNX_OK;
     case LYNX_DEBUG_DOWN_K_WAVES: g_tune.dn_kw.store(value <= 0 ? 0 : value); return LYNX_OK;
+    case LYNX_DEBUG_WIDE_KERNEL: g_tune.wide.store(value <= 0 ? 0 : 1); return LYNX_OK;
     default: return fail(LYNX_ERR_INVALID_ARG, "lynx_debug_set: unknown knob %d", what);
     }
 }

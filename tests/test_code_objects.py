@@ -52,3 +52,21 @@ def test_a_missing_wait_is_refused(between, wait, ok):
         with pytest.raises(RuntimeError, match="nothing waits"):
             check_code.check_waits(listing)
     assert check_code.check_waits(listing.replace("ffn_kernel", "other_kernel")) == 0
+
+
+def test_operands_of_written_out_products_come_from_loads(texts):
+    assert sum(check_code.check_operands(listing) for _, listing in texts) >= 8 * 256   # two projections, four sizes of pass
+
+
+@pytest.mark.parametrize("before,ok", [(["v_mov_b32_e32 v9, v1"], False), (["v_mov_b32_e32 v20, v1", "s_nop 0"], False),
+                                       (["v_mov_b32_e32 v9, v1", "s_nop 1"], True), (["v_mov_b32_e32 v12, v1"], True),
+                                       (["v_add_u32_e32 v8, v1, v2", "ds_read_b128 v[30:33], v4", "s_waitcnt lgkmcnt(4)"], True),
+                                       (["ds_read_b128 v[8:11], v4"], True), (["v_cmp_gt_i32_e32 vcc, v8, v1"], True)])
+def test_a_late_write_of_an_operand_is_refused(before, ok):
+    body = before + ["v_mfma_f32_16x16x32_bf16 a[0:3], v[8:11], v[20:23], a[0:3]  // 000000008320: D3B580FC"]
+    listing = "0000000000006700 <_ZN4lynx15ffn_wide_kernelENS_9FfnParamsE>:\n" + "\n".join("\t" + l for l in body)
+    if ok:
+        assert check_code.check_operands(listing) == 1
+    else:
+        with pytest.raises(RuntimeError, match="written"):
+            check_code.check_operands(listing)

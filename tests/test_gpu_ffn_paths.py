@@ -226,6 +226,30 @@ def test_k_slices_set_by_the_knob(L, fmt, slices, case):
         L.lynx_debug_set(B.DEBUG_DOWN_K_WAVES, 0)
 
 
+# The kernel for token blocks of 256, set by its knob: passes of up to 64, 128, 192 and 256 tokens at their edges, several blocks, one
+# token, an expert that is not invoked; contractions of one k-step, an odd number of them, and ends inside a turn of four; rows that
+# leave waves and row tiles without work; shared experts with K slices; one launch with waits and (F past 4096) two.
+WIDE = [
+    (257, (257, 256, 255, 193, 1), 256, 512, 0, 0),
+    (192, (192, 129, 128, 65, 64), 288, 352, 1, 384),
+    (66, (66, 0, 1, 33), 32, 64, 0, 0),
+    (600, (600, 513, 512, 31), 160, 96, 1, 1024),
+    (130, (130, 97), 1056, 4128, 0, 0),
+    (65, (17, 16), 64, 4384, 1, 4384),
+    (1024, (1024, 700), 512, 640, 2, 320),
+]
+
+
+@pytest.mark.parametrize("case", WIDE)
+def test_wide_kernel(L, case):
+    from paper_2411_08982_amd import binding as B
+    L.lynx_debug_set(B.DEBUG_WIDE_KERNEL, 1)
+    try:
+        run_case(L, "bf16", *case)
+    finally:
+        L.lynx_debug_set(B.DEBUG_WIDE_KERNEL, 0)
+
+
 # One launch for quantised experts past 4096 columns from 8 to 64 tokens, where 512 down workgroups exist: both edges of the
 # batch size, direct and staged experts, and just too few workgroups (H = 1920: 480), two launches, beside it.
 @pytest.mark.parametrize("fmt,T,H,F", [("fp8", 7, 2048, 4160), ("fp8", 8, 1920, 4160), ("fp8", 8, 2048, 4160), ("fp4", 8, 2048, 4224),
