@@ -55,7 +55,8 @@ def test_a_missing_wait_is_refused(between, wait, ok):
 
 
 def test_operands_of_written_out_products_come_from_loads(texts):
-    assert sum(check_code.check_operands(listing) for _, listing in texts) >= 8 * 256   # two projections, four sizes of pass
+    # two projections, passes of 4, 8, 12 and 16 column tiles, four streams, four k-steps a turn
+    assert sum(check_code.check_operands(listing) for _, listing in texts) >= 2 * (4 + 8 + 12 + 16) * 4 * 4
 
 
 @pytest.mark.parametrize("before,ok", [(["v_mov_b32_e32 v9, v1"], False), (["v_mov_b32_e32 v20, v1", "s_nop 0"], False),
