@@ -8,8 +8,8 @@
 // minimises dependent launches and dependent memory round trips inside them:
 //   logits_kernel         (token tile x expert group)  fp32 dot products: the router row is prefetched
 //                         into registers while the 4 tokens are staged in LDS; lanes split H; transposing
-//                         butterfly reduction.  Its own launch (it needs the whole chip).  Above
-//                         128 tokens logits_mfma_kernel does the same on the fp32 matrix cores.
+//                         butterfly reduction.  Its own launch (it needs the whole chip).  Larger
+//                         batches: logits_mfma_kernel does the same on the fp32 matrix cores.
 //   T <= 16:  routing_small_kernel  ONE workgroup does everything else with all state in LDS: top-k,
 //                         bins + histogram, scores + score order, nominations, fill, remap, gates, counts
 //                         and (fused path) the token assignment.  Two launches for the whole routing side, one
@@ -37,7 +37,6 @@ constexpr int kRemapWideMinT = 256;   // batches from which remap_kernel runs wi
 constexpr int kSmallThreads = 1024;   // single-workgroup path: 16 waves = 16 tokens
 constexpr int kSmallWaves = kSmallThreads / kWave;
 constexpr int kSmallFusedN = 64;      // most experts whose logits the single workgroup computes itself (small_logits_pays)
-constexpr int kLogitsMfmaMinT = 128;   // larger batches compute the logits on the fp32 matrix cores (measured crossover)
 
 struct ZeroList {
     int32_t *ptr[8];
@@ -154,69 +153,83 @@ __global__ __launch_bounds__(256) void logits_kernel(const uint16_t *__restrict_
     }
 }
 
-// The same for larger batches on the fp32 matrix cores: one workgroup per 16 tokens x 16 experts, its four
+// The same for larger batches on the fp32 matrix cores: one workgroup per 16 tokens x 16 experts, its eight
 // waves split H and are summed in a fixed order through LDS.  v_mfma_f32_16x16x4_f32 takes fp32 operands
 // (x is exact in fp32) and accumulates in fp32.  A = x (lane l: token l%16, k group l/16), B = Wr (lane l:
-// expert l%16, k group l/16), D: lane l holds expert l%16 for tokens 4*(l/16) .. +3.  A k-step is 32 columns:
-// a lane loads the 8 consecutive columns of its k group (16 bytes of x, 32 bytes of Wr) and the j-th of its
-// 8 values goes into the j-th of 8 MFMAs (any assignment of columns to MFMAs is right as long as A and B
-// agree).  Against the 4 x 4 output tiles of logits_kernel this reads 4 times less through L2; its lanes read 16
-// rows at once, which costs latency, so it only pays for large batches (about 10 us at any size; logits_kernel:
-// 6 us at 32 tokens, 26 us at 512).
+// expert l%16, k group l/16), D: lane l holds expert l%16 for tokens 4*(l/16) .. +3.  A k-step is 32 columns: a lane holds the
+// 8 consecutive columns of its k group, and the j-th of its 8 values goes into the j-th of 8 MFMAs (any assignment of columns
+// to MFMAs is right as long as A and B agree).
+// Loads in operand order gather 16 bytes of sixteen rows side by side, 47 cycles of the load path each, and bound the kernel
+// (neither more waves nor a deeper ring, nor leaving the products out, made it faster).  So a wave loads chunks of 64 columns in
+// whole rows (128 bytes of x, 256 of Wr per row), one chunk ahead, and turns them over in an LDS region of its own: no barrier.
+// us per launch, operand-order gathers by four waves against this: 200 tokens, H = 7168, 256 experts 23.7 -> 17.6, 1000 tokens
+// 84.4 -> 51.3; 512 tokens, H = 2048, 128 experts 10.0 -> 7.7; 1000 tokens, H = 4096, 8 experts 11.7 -> 10.7; 200 tokens, H = 2048, 60
+// experts 9.0 -> 7.0.  (Four waves 21.9 at the first shape, sixteen 16.6 but 58 at the second; chunks further ahead: equal or slower.)
 typedef float logits_f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kLogitsRing = 4;    // k-steps in flight per wave
-constexpr int kLogitsWaves = 4;   // waves of a workgroup, splitting H
-
-struct LogitsStep {
-    uint4 xv;
-    float4 w0, w1;
-};
-
-__device__ __forceinline__ LogitsStep logits_load(const uint16_t *__restrict__ xrow, const float *__restrict__ wrow, int step)
-{
-    asm volatile("" : "+v"(step));   // keeps the prefetch ring: see the weight ring of the expert kernels
-    LogitsStep r;
-    r.xv = *reinterpret_cast<const uint4 *>(xrow + step * 32);
-    r.w0 = *reinterpret_cast<const float4 *>(wrow + step * 32);
-    r.w1 = *reinterpret_cast<const float4 *>(wrow + step * 32 + 4);
-    return r;
-}
+typedef unsigned logits_u32x4 __attribute__((ext_vector_type(4)));
+constexpr int kLogitsWaves = 8;   // waves of a workgroup, splitting H
+constexpr int kLogitsCols = 64;   // columns of a chunk: two k-steps
 
 __global__ __launch_bounds__(kLogitsWaves * kWave) void logits_mfma_kernel(const uint16_t *__restrict__ x, const float *__restrict__ Wr,
                                                           const float *__restrict__ bias, int T, int H, int N,
                                                           float *__restrict__ logits, ZeroList z)
 {
     __shared__ logits_f32x4 part[kLogitsWaves - 1][kWave];
+    // x: 16 rows of 8 pieces of 16 bytes, in the order piece ^ (row % 8); Wr: 16 rows of 16 pieces, piece ^ row: rows that are read or
+    // written together lie in different banks
+    __shared__ logits_u32x4 xt[kLogitsWaves][128];
+    __shared__ logits_f32x4 wt[kLogitsWaves][256];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16;
+    const int t0 = blockIdx.y * 16, e0 = blockIdx.x * 16;    // (the token tiles of an expert tile on few XCDs)
     const int KT = H / 32;                                   // k-steps; wave w takes [kb, kb + n)
     const int per = (KT + kLogitsWaves - 1) / kLogitsWaves;
     const int kb = min(wave * per, KT), n = min(KT, kb + per) - kb;
-    const int kbc = n > 0 ? kb : 0, last = max(n, 1) - 1;
+    const int chunks = (n + 1) / 2;
     // rows past the end re-read the last row; their results are not stored
-    const uint16_t *xrow = x + (size_t)min(t0 + (lane & 15), T - 1) * H + kbc * 32 + (lane >> 4) * 8;
-    const float *wrow = Wr + (size_t)min(e0 + (lane & 15), N - 1) * H + kbc * 32 + (lane >> 4) * 8;
+    const int xp = lane & 7, wp = lane & 15;                 // this lane's pieces
+    const uint16_t *xrow[2];
+    const float *wrow[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) xrow[i] = x + (size_t)min(t0 + (lane >> 3) + 8 * i, T - 1) * H;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) wrow[i] = Wr + (size_t)min(e0 + (lane >> 4) + 4 * i, N - 1) * H;
+    logits_u32x4 xr[2];
+    logits_f32x4 wr[4];
+    auto load = [&](int c) {   // columns past the end re-read the row's last ones
+        const int col = kb * 32 + c * kLogitsCols;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) xr[i] = *reinterpret_cast<const logits_u32x4 *>(xrow[i] + min(col + xp * 8, H - 8));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wr[i] = *reinterpret_cast<const logits_f32x4 *>(wrow[i] + min(col + wp * 4, H - 4));
+    };
+    const int xs = (lane >> 3) * 8 + (xp ^ (lane >> 3));     // (rows 8 apart share row % 8)
+    const int row = lane & 15, g = lane >> 4;
     logits_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    LogitsStep ring[kLogitsRing];
-#pragma unroll
-    for (int j = 0; j < kLogitsRing; ++j) ring[j] = logits_load(xrow, wrow, min(j, last));
+    load(0);
     zero_slices(z, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid, kLogitsWaves * kWave);
-    for (int s0 = 0; s0 < n; s0 += kLogitsRing) {
+    for (int c = 0; c < chunks; ++c) {
+        // (LDS serves a wave in order: the region may be written while the last chunk's reads are still on their way)
 #pragma unroll
-        for (int u = 0; u < kLogitsRing; ++u) {
-            const int s = s0 + u;
-            const bool live = s < n;
-            const LogitsStep c = ring[u];
-            const float a[8] = {bf16_lo(c.xv.x), bf16_hi(c.xv.x), bf16_lo(c.xv.y), bf16_hi(c.xv.y),
-                                bf16_lo(c.xv.z), bf16_hi(c.xv.z), bf16_lo(c.xv.w), bf16_hi(c.xv.w)};
-            const float b[8] = {c.w0.x, c.w0.y, c.w0.z, c.w0.w, c.w1.x, c.w1.y, c.w1.z, c.w1.w};
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? a[j] : 0.f, b[j], acc, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            ring[u] = logits_load(xrow, wrow, min(s + kLogitsRing, last));
-            __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < 2; ++i) {
+            const bool in = c * kLogitsCols + xp * 8 < n * 32;   // past the wave's slice x counts as zero
+            xt[wave][xs + i * 64] = in ? xr[i] : logits_u32x4{0u, 0u, 0u, 0u};
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wt[wave][((lane >> 4) + 4 * i) * 16 + (wp ^ ((lane >> 4) + 4 * i))] = wr[i];
+        load(min(c + 1, chunks - 1));   // (the last chunk again at the end, from the cache)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const logits_u32x4 xv = xt[wave][row * 8 + ((q * 4 + g) ^ (row & 7))];
+            const logits_f32x4 w0 = wt[wave][row * 16 + ((q * 8 + g * 2) ^ row)];
+            const logits_f32x4 w1 = wt[wave][row * 16 + ((q * 8 + g * 2 + 1) ^ row)];
+            const float a[8] = {bf16_lo(xv.x), bf16_hi(xv.x), bf16_lo(xv.y), bf16_hi(xv.y),
+                                bf16_lo(xv.z), bf16_hi(xv.z), bf16_lo(xv.w), bf16_hi(xv.w)};
+            const float b[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
     if (wave > 0) part[wave - 1][lane] = acc;
     __syncthreads();
@@ -1135,11 +1148,16 @@ static void add_zero(ZeroList &z, int32_t *p, int count)
     ++z.n;
 }
 
+// Larger batches on the matrix cores.  Below 129 tokens it depends on the experts too (us, logits_kernel against the matrix cores,
+// H = 2048: 32 tokens x 128 experts 5.8 and 6.4, 61 x 64 5.7 and 6.5, 100 x 128 8.6 and 6.6; H = 7168: 32 x 256 17.6 and 14.7;
+// H = 4096: 128 x 8 5.9 and 9.9).
+static bool logits_on_matrix_cores(int T, int N) { return T > 128 || (long)T * N >= 8192; }
+
 static void launch_logits(const uint16_t *x, const float *Wr, const float *bias, int T, int H, int N, float *logits,
                           const ZeroList &z, hipStream_t st)
 {
-    if (T > kLogitsMfmaMinT)
-        hipLaunchKernelGGL(logits_mfma_kernel, dim3((T + 15) / 16, (N + 15) / 16), dim3(kLogitsWaves * kWave), 0, st, x, Wr, bias, T, H, N,
+    if (logits_on_matrix_cores(T, N))
+        hipLaunchKernelGGL(logits_mfma_kernel, dim3((N + 15) / 16, (T + 15) / 16), dim3(kLogitsWaves * kWave), 0, st, x, Wr, bias, T, H, N,
                            logits, z);
     else
         hipLaunchKernelGGL(logits_kernel, dim3((T + kRouteTT - 1) / kRouteTT, (N + 3) / 4), dim3(256), 0, st, x, Wr, bias,

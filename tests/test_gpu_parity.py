@@ -230,6 +230,21 @@ def test_biased_selection_through_the_ffn(L):
 
 # ------------------------------------------------------------------------------------------------ permute
 
+# The logits on the matrix cores: hidden sizes that leave waves without a k-step, with an odd number of them and with the last one
+# short; token and expert tiles that are partly filled; both sides of the line at T * N = 8192 and of 128 tokens.
+@pytest.mark.parametrize("T,H,N", [(129, 32, 3), (130, 96, 17), (200, 288, 16), (129, 544, 60), (32, 256, 256), (31, 256, 256), (65, 2080, 127),
+                                   (145, 800, 33), (1024, 64, 8), (128, 7168, 63)])
+def test_logits_of_large_batches(L, T, H, N):
+    _say(f"logits T={T} H={H} N={N}")
+    rng = np.random.default_rng([T, H, N])
+    x = wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
+    Wr = (rng.standard_normal((N, H)) / np.sqrt(H)).astype(np.float32)
+    b = rng.standard_normal(N).astype(np.float32)
+    out = L.lynx_route(to_bf16_dev(x), dev(Wr), dev(b), min(4, N))
+    want = wl.bf16_bits_to_f32(x).astype(np.float64) @ Wr.astype(np.float64).T + b
+    assert np.all(np.abs(host(out["logits"]) - want) <= 1e-5 * np.maximum(1.0, np.abs(want)))
+
+
 @pytest.mark.parametrize("T,N,k", [(1, 1, 1), (1024, 1, 1), (33, 3, 3), (1023, 256, 7), (1024, 255, 16), (17, 129, 13), (700, 64, 11)])
 def test_permute_with_skipped_pairs(L, T, N, k):
     """Every number of picks divides pair ids into tokens; pairs without an expert leave -1 at the end of the permutation."""
