@@ -1701,8 +1701,6 @@ static bool single_launch(int T, int F) { return T >= 1 && (F + 63) / 64 <= 64; 
 // 231 -> 220, MXFP4 128 -> 121.  Fewer down workgroups than slots lose: they go two to a CU as its slots come free, where a
 // launch of their own spreads them, one to a CU (4 experts of 2048 x 8192, FP8, 8 tokens 45 against 49; the first shapes, 2
 // tokens, 107 against 116, 100 tokens and 128-row workgroups, 277 against 309).  bf16 weights gain 0 to 1.5 % and keep two.
-// (Expert ranges of a caller that overlap can make more token blocks than the plan has records; their gate/up workgroups
-// would never report.  Batches that could do that keep two launches, which wait for nothing.)
 static bool fill_tail(int T, int N, int k, long down_items)
 {
     return T >= 8 && T <= kTokBlock && down_items >= 2 * kCus && (long)N * ((T * k + kTokBlock - 1) / kTokBlock) <= kPlanMaxBlocks;
@@ -1744,6 +1742,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     }
     s.tok_block = s.big == 3 ? kWideTokens : staged_tokens(s.big, format);
     s.max_blocks = plan_max_blocks(T, N, k, s.tok_block);
+    s.plan.max_blocks = s.max_blocks;
     s.plan.shared_pairs = n_shared * (T > kDirectMaxTokens ? (T + s.tok_block - 1) / s.tok_block : 1);
     const int rows_dn = s.big == 3 ? 256 : 16 * (kFfnWaves / s.kwd) * 2;
     const int rows_gu = s.big == 3 ? 128 : 64 * staged_row_tiles(true, 1, s.big);

@@ -36,6 +36,7 @@ struct PlanShape {
     int dn_cap;      // down items the grid is sized for: the device takes the fewest units per item that fit it
     int dn_m_max;    // most units per down item
     int shared_pairs;   // (shared expert, token block) pairs: completion counters to clear
+    int max_blocks;     // (expert, token block) pairs that the FFN's grid has workgroups for, at most kPlanMaxBlocks
 };
 
 constexpr int kPlanB = 0, kPlanM = 1, kPlanNa = 2;   // words of the header
@@ -92,6 +93,9 @@ __device__ __forceinline__ void plan_write_header(const PlanShape &ps, int block
 // Builds the header and the block records from a caller's ranges.  Every thread of the workgroup calls it (one wave does the
 // work); count[e] / offs[e] (pairs of expert e and where they start in the permutation) are in LDS and complete (barrier
 // before).  blk0[e] (LDS) receives the first block of expert e, for the caller to file the pair ids under (barrier after).
+// Ranges that overlap can make more blocks than the grid has workgroups for.  An expert is in the plan with all of its blocks
+// or not at all (then none behind it is either): a down workgroup waits for the reports of every gate/up workgroup of
+// its expert, and those of a block past the grid never come.
 // ws = the routing part of the workspace.
 __device__ __forceinline__ void build_plan(const PlanShape &ps, int N, const int *count, const int *offs, int *blk0,
                                            int32_t *__restrict__ ws)
@@ -99,23 +103,21 @@ __device__ __forceinline__ void build_plan(const PlanShape &ps, int N, const int
     if (ps.units_gu <= 0) return;
     const int tid = threadIdx.x;
     if (tid >= kWave) return;
-    // exclusive prefixes over the experts in one packed scan: rank among the invoked experts (low half) and token
-    // blocks before (high half; at most kPlanMaxBlocks < 2^15)
-    int carry_r = 0, carry_b = 0;
+    int invoked = 0, blocks = 0, carry_b = 0;   // blocks: of the experts in the plan; carry_b: of all experts before these
     for (int base = 0; base < N; base += kWave) {
         const int e = base + tid;
         const int c = e < N ? count[e] : 0;
-        const int a = c > 0 ? 1 : 0;
         const int nb = c > 0 ? plan_token_blocks(c, ps.tok_block) : 0;
-        const int s = wave_prefix_sum_i32(a | (nb << 16));
-        const int q0 = carry_b + (s >> 16) - nb;
-        if (e < N) blk0[e] = q0;
-        if (a) plan_write_records(e, c, offs[e], q0, nb, ws);
-        const int total = __builtin_amdgcn_readlane(s, kWave - 1);
-        carry_r += total & 0xffff;
-        carry_b += total >> 16;
+        const int s = wave_prefix_sum_i32(nb);
+        const int q0 = carry_b + s - nb;
+        const bool in = c > 0 && q0 + nb <= ps.max_blocks;
+        if (e < N) blk0[e] = in ? q0 : kPlanMaxBlocks;
+        if (in) plan_write_records(e, c, offs[e], q0, nb, ws);
+        invoked += __popcll(__ballot(in));
+        blocks = max(blocks, wave_max_i32(in ? q0 + nb : 0));
+        carry_b += __builtin_amdgcn_readlane(s, kWave - 1);
     }
-    if (tid == 0) plan_write_header(ps, carry_b, carry_r, ws);
+    if (tid == 0) plan_write_header(ps, blocks, invoked, ws);
 }
 
 // Files pair id p, the i-th of expert e's te pairs, under the expert's block (experts on the direct path only).
@@ -123,7 +125,7 @@ __device__ __forceinline__ void plan_file_pair(const PlanShape &ps, const int *b
                                                int32_t *__restrict__ ws)
 {
     if (ps.units_gu <= 0 || te > kDirectMaxTokens) return;
-    if (blk0[e] >= kPlanMaxBlocks) return;   // (ranges of a caller that overlap: build_plan has no record for the block either)
+    if (blk0[e] >= kPlanMaxBlocks) return;   // (not in the plan)
     reinterpret_cast<uint16_t *>(ws + kWsPlanPairs)[blk0[e] * kDirectMaxTokens + i] = (uint16_t)p;
 }
 

@@ -283,6 +283,38 @@ def test_overlapping_expert_ranges_stay_inside_the_plan(L):
     assert np.all(host(ws.view(torch.int32))[20032:22080] == -1)
 
 
+@pytest.mark.parametrize("fmt,H,F", [("bf16", 64, 128), ("fp8", 2048, 4160), ("fp4", 2048, 4224)])
+def test_overlapping_expert_ranges_leave_nothing_to_wait_for(L, fmt, H, F):
+    """Overlapping ranges with more token blocks (15 + 16 + 16) than the grid has workgroups for (32), where both projections
+    are one launch: the third expert is left out whole, and no down workgroup waits for reports of blocks that do not exist.  All
+    experts have the same weights and the second one holds every pair, so y is that of any valid assignment."""
+    T = 64
+    k = N = 16
+    P = T * k
+    print(f"ffn overlapping ranges, one launch: {fmt} T={T} k={k} N={N} H={H} F={F}", flush=True)
+    rng = np.random.default_rng([H, F])
+    mk = lambda *shape: to_bf16_dev(wl.f32_to_bf16_bits((rng.standard_normal(shape) * 0.05).astype(np.float32))).expand(N, -1, -1).contiguous()
+    pack, ffn = {"bf16": (L.lynx_pack_weights, L.lynx_moe_ffn), "fp8": (L.lynx_quantize_weights_fp8, L.lynx_moe_ffn_fp8),
+                 "fp4": (L.lynx_quantize_weights_fp4, L.lynx_moe_ffn_fp4)}[fmt]
+    W = pack(mk(1, F, H), mk(1, F, H), mk(1, H, F))
+    W = tuple(W) if fmt == "bf16" else (W,)
+    x = to_bf16_dev(wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32)))
+    idx = dev(np.tile(np.arange(N, dtype=np.int32), (T, 1)))
+    gate = dev(rng.uniform(0.1, 1.0, (T, k)).astype(np.float32))
+    want = host(ffn(x, *W, idx, gate, L.lynx_permute(idx, N), N, F))
+    offsets = np.array([0, 960] + [0, P] * 7 + [0], np.int32)      # experts 0, 2, 4, ...: [0, 960), then all pairs
+    p = dict(offsets=dev(offsets), perm=dev(np.arange(P, dtype=np.int32)), active=dev(np.arange(N, dtype=np.int32)),
+             num_active=dev(np.array([N], np.int32)))
+    ws = L.new_workspace(T, H, F, N, k)
+    ws.fill_(0xFF)
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    y = host(ffn(x, *W, idx, gate, p, N, F, workspace=ws, status=status))
+    assert host(status)[0] == 0
+    words = host(ws.view(torch.int32))
+    assert list(words[9760:9763]) == [31, 1, 2]      # the plan's header: blocks, units per item, experts
+    assert np.all(np.isfinite(y)) and row_rel_err(y, want).max() <= Y_TOL
+
+
 @pytest.mark.parametrize("fmt", ["bf16", "fp8", "fp4"])
 @pytest.mark.parametrize("T,counts,S", [(40, (40, 33, 9, 1), 1), (130, (130, 100, 20), 0), (7, (7, 3), 1)])
 def test_token_rows_at_odd_places(L, fmt, T, counts, S):
