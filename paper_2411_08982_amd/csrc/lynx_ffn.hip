@@ -1741,7 +1741,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
         s.kwd = 1;
     }
     s.tok_block = s.big == 3 ? kWideTokens : staged_tokens(s.big, format);
-    s.max_blocks = plan_max_blocks(T, N, k, s.tok_block);
+    s.max_blocks = plan_max_blocks(T, N, k, s.tok_block, false);
     s.plan.max_blocks = s.max_blocks;
     s.plan.shared_pairs = n_shared * (T > kDirectMaxTokens ? (T + s.tok_block - 1) / s.tok_block : 1);
     const int rows_dn = s.big == 3 ? 256 : 16 * (kFfnWaves / s.kwd) * 2;
@@ -1970,6 +1970,7 @@ int moe_ffn_impl(const uint16_t *x_bf16, const uint16_t *Wgu_packed, const uint1
     int32_t *rws = reinterpret_cast<int32_t *>(workspace);
     hipStream_t st = (hipStream_t)stream;
     FfnShape shape = ffn_shape(T, H, F, N, k, n_shared, q8 ? q8->format : 0);
+    if (!plan_ready) shape.max_blocks = shape.plan.max_blocks = plan_max_blocks(T, N, k, shape.tok_block, true);
     if (reinterpret_cast<uintptr_t>(x_bf16) % 16 != 0) {
         // Token rows of a tensor that starts at an odd place of its storage.  The loads into LDS take 16 bytes per lane and
         // are not known to take them from everywhere, so the rows are copied first: to the place of the per-pair outputs,

@@ -46,13 +46,15 @@ __host__ __device__ __forceinline__ int plan_token_blocks(int te, int tok_block)
     return te <= kDirectMaxTokens ? 1 : (te + tok_block - 1) / tok_block;
 }
 
-// Most (expert, token block) pairs a batch of T tokens with k picks each can have.
-inline int plan_max_blocks(int T, int N, int k, int tok_block)
+// Most (expert, token block) pairs a batch of T tokens with k picks each can have.  repeats: an assignment may send a token to one
+// expert more than once (a caller's can; lynx_permute and the layer's routing make none such), so that an expert can
+// have more rows than there are tokens.
+inline int plan_max_blocks(int T, int N, int k, int tok_block, bool repeats)
 {
     const long P = (long)T * k;
     const long experts = P < N ? P : N;
-    if (T <= kDirectMaxTokens) return (int)experts;
-    return (int)(experts + P / tok_block);   // an expert with te tokens has at most 1 + te / tok_block blocks
+    if (T <= kDirectMaxTokens && !repeats) return (int)experts;
+    return (int)(experts + P / tok_block);   // an expert with te rows has at most 1 + te / tok_block blocks
 }
 
 // Units per down item the device will choose for B blocks (same rule on the host, for the grid size).

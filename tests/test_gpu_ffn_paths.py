@@ -172,7 +172,8 @@ def test_infinity_past_a_ragged_contraction(L, fmt, H, F, T, counts, where):
 # tokens, in kernels that are chosen by the number of tokens.  F is long enough for four K slices in the down projection.
 # (H = 160: the last 64-row unit of the staged path is shared by two down workgroups of which only one exists.)
 @pytest.mark.parametrize("fmt,H,F", [("bf16", 256, 2048), ("bf16", 160, 2048), ("fp8", 256, 4096), ("fp4", 256, 8192)])
-@pytest.mark.parametrize("T,per_expert", [(8, (4, 20, 0)), (8, (16, 0)), (7, (12, 2)), (8, (9, 7)), (5, (1, 9)), (8, (13, 11, 0))])
+@pytest.mark.parametrize("T,per_expert", [(8, (4, 20, 0)), (8, (16, 0)), (7, (12, 2)), (8, (9, 7)), (5, (1, 9)), (8, (13, 11, 0)),
+                                          (16, (121, 1, 1, 1, 1, 1, 1, 1))])   # (one token block more than experts)
 def test_more_rows_than_tokens(L, fmt, H, F, T, per_expert):
     print(f"ffn rows {fmt} T={T} rows={per_expert} H={H} F={F}", flush=True)
     N, P = len(per_expert), sum(per_expert)
