@@ -13,10 +13,12 @@ extern "C" {
 #endif
 
 /*
- * How many launches of the weight-streaming kernel lynx_moe_ffn issues for this batch size and expert width:
+ * How many launches of the weight-streaming kernel lynx_moe_ffn issues for this batch size and expert width, bf16 weights:
  * 1 (gate/up and down workgroups in one grid) or 2 (one grid each; always for an x that does not start on 16 bytes,
  * whose rows are copied first).  For measurement: per-launch figures of
  * a profile are whole-FFN figures divided by this.
+ * It does not answer for FP8 and MXFP4 weights where it says 2 and the batch has 8 to 64 tokens: there may be one launch
+ * then, or two of which the first runs the down workgroups as well if the batch invokes enough experts.
  */
 int lynx_moe_ffn_launches(int T, int F);
 

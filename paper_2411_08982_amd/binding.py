@@ -386,7 +386,7 @@ def lynx_debug_set(what: int, value: int):
 
 
 def lynx_moe_ffn_launches(T, F) -> int:
-    """Launches of the weight-streaming kernel per lynx_moe_ffn call (1 or 2) for this batch size and expert width."""
+    """Launches of the weight-streaming kernel per lynx_moe_ffn call (1 or 2) for this batch size and expert width, bf16 weights."""
     return int(lib().lynx_moe_ffn_launches(int(T), int(F)))
 
 

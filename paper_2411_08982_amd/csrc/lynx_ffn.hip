@@ -935,6 +935,7 @@ struct FfnParams {
     int block0;       // index of this launch's first workgroup in the (gate/up, down) order
     int gu_split;     // 1: the last, partial round of gate/up workgroups is cut into single row tiles (see ffn_kernel)
     int wait;         // 0: the down workgroups of this launch follow a finished gate/up launch and do not wait
+    int fill;         // > 0: down workgroups are in both of two launches and run in the first if at least so many are live
     int spin_limit;   // polls of a completion counter before a down workgroup gives up
     int target_bias;  // added to the count a down workgroup waits for (0; tests of the give-up path set it)
     int32_t *done;    // completion counters (kWsDone), zero before the launch
@@ -1149,6 +1150,10 @@ __global__ __launch_bounds__(kFfnThreads, kWgPerCu) void ffn_kernel(FfnParams fp
         else if constexpr (WF == 0)
             expert_work<true, kFfnWaves, BIG, WF>(fp.gu, bb, fp, stage0, stage1, rowoff, outrow, sub);
     } else {
+        if (WF != 0 && fp.fill > 0) {   // (the same answer in every workgroup of both launches: see launch_shape)
+            const int live = fp.dn.shared_blocks + max(fp.dn.plan[kWsPlanHdr + kPlanB], 0) * fp.dn.tiles_r;
+            if ((live >= fp.fill) != (fp.wait != 0)) return;
+        }
         expert_work<false, KWD, BIG, WF>(fp.dn, b - fp.gu_blocks, fp, stage0, stage1, rowoff, outrow);
     }
 }
@@ -1686,6 +1691,7 @@ struct FfnShape {
     int kwd;            // K slices of a down workgroup's waves
     int big;            // 0 = at most 64 tokens; 1, 2 = larger batches, gate/up units of 64 or of 128 rows; 3 = the wide kernel
     bool single;        // one launch for both projections
+    int fill;           // > 0: two launches, and the device decides which of them runs the down workgroups (launch_shape)
     int tok_block;
     int rows_gu, rows_dn;   // rows of a gate/up unit, of a down workgroup
     int max_blocks;     // most (expert, token block) pairs of a batch
@@ -1694,16 +1700,29 @@ struct FfnShape {
 
 static bool single_launch(int T, int F) { return T >= 1 && (F + 63) / 64 <= 64; }   // (any batch size: see below)
 
-// Quantised weights, huge experts: one launch all the same where the batch is between 8 and 64 tokens and can fill every slot
-// of the chip with down workgroups (two per CU).  They start in the slots that the last, partial round of gate/up workgroups
-// leaves empty.  us per FFN call, two launches against one: 8 experts of 4096 x 14336, FP8, 8 tokens 205 -> 195, 16 tokens
-// 230 -> 224, 48 tokens 246 -> 242; MXFP4 118 -> 109, 127 -> 122, 143 -> 141; 16 experts of 4096 x 8192, 20 tokens, FP8
-// 231 -> 220, MXFP4 128 -> 121.  Fewer down workgroups than slots lose: they go two to a CU as its slots come free, where a
-// launch of their own spreads them, one to a CU (4 experts of 2048 x 8192, FP8, 8 tokens 45 against 49; the first shapes, 2
-// tokens, 107 against 116, 100 tokens and 128-row workgroups, 277 against 309).  bf16 weights gain 0 to 1.5 % and keep two.
-static bool fill_tail(int T, int N, int k, long down_items)
+// Quantised weights, huge experts, batches of 8 to 64 tokens: one launch all the same where the live down workgroups fill the
+// chip.  They start in the slots that the last, partial round of gate/up workgroups leaves empty.  Too few of them lose: they go
+// two to a CU as its slots come free, where a launch of their own spreads them, one to a CU.  us per layer, two launches
+// against one, 8 experts of 4096 x 14336 of which so many are invoked:
+//   FP8,   16 tokens, 64-row workgroups, 64 per expert:   2: 95 / 124   4: 143 / 154   5: 176 / 169   6: 194 / 185   8: 239 / 237
+//   FP8,    8 tokens, 32-row workgroups, 128 per expert:  2: 82 / 98    3: 110 / 118   4: 133 / 130   6: 174 / 165   8: 221 / 216
+//   MXFP4, 32 tokens, 64-row workgroups:                  2: 79 / 112   4: 101 / 118   5: 125 / 130   6: 129 / 127   8: 147 / 143
+// and of 16 experts of 4096 x 8192, FP8, 64 tokens: 4: 107 / 123, 6: 138 / 133, 12: 234 / 225.  So the line lies at 384 live
+// workgroups of 64 rows, 512 of 32.  How many are live, only the device knows: one launch where the fewest experts a
+// batch can invoke (k) are enough, two where all of them are not, and otherwise down workgroups in both launches,
+// of which those of one leave at once.  That costs 1 to 2.5 us of the one launch's gain, and up to 1.5 us beside two (the
+// first line: 95.2, 143.4, 178.1, 187.8, 238.7).  bf16 weights gain 0 to 1.5 % with all eight experts and keep two.
+static void launch_shape(FfnShape &s, int T, int F, int k, int max_experts, int format)
 {
-    return T >= 8 && T <= kTokBlock && down_items >= 2 * kCus && (long)N * ((T * k + kTokBlock - 1) / kTokBlock) <= kPlanMaxBlocks;
+    s.single = single_launch(T, F);
+    s.fill = 0;
+    if (s.single || format == 0 || T < 8 || T > kTokBlock) return;
+    const int enough = s.kwd == 4 ? 2 * kCus : 2 * kCus * 3 / 4;
+    if ((long)s.plan.units_dn * max_experts < enough) return;
+    if ((long)s.plan.units_dn * k >= enough)
+        s.single = true;
+    else
+        s.fill = enough;
 }
 
 // The wide kernel pays with more than 128 tokens per expert on average, where its workgroups are long (a quarter of a wave's time
@@ -1750,7 +1769,7 @@ static FfnShape ffn_shape(int T, int H, int F, int N, int k, int n_shared, int f
     s.rows_dn = rows_dn;
     s.plan.units_gu = (F + rows_gu - 1) / rows_gu;
     s.plan.units_dn = (H + rows_dn - 1) / rows_dn;
-    s.single = single_launch(T, F) || (format != 0 && fill_tail(T, N, k, (long)s.plan.units_dn * max_experts));
+    launch_shape(s, T, F, k, max_experts, format);
     s.plan.tok_block = s.tok_block;
     // Longer down items only where the staged unit and the direct workgroup are the same 64 rows (two K slices).
     // (not in the large-batch kernels, whose items are single passes)
@@ -1793,7 +1812,8 @@ static void launch_kernel(const FfnParams &fp, unsigned blocks, hipStream_t st)
 // (DeepSeek-V2-Lite shapes, 16 tokens: 87.6 -> 84.7 us per layer, remap off 150.0 -> 146.5; Qwen1.5-MoE shapes, 8
 // tokens: 81.7 -> 81.7, remap off 92.3 -> 87.5); with huge experts it is
 // equal or slower with bf16 weights (Mixtral shapes, 1 token 129 -> 140 us, 64 tokens equal, 200 tokens 505 -> 555: down
-// workgroups that are few come to lie two to a CU) and faster with quantised ones between 8 and 64 tokens (fill_tail).
+// workgroups that are few come to lie two to a CU) and faster with quantised ones between 8 and 64 tokens, if enough experts
+// are invoked (launch_shape).
 
 // Gate/up and down over all invoked and shared experts.  Batches of more than 64 tokens take the large-batch kernels, whose
 // staged path makes passes of up to 128 tokens with bf16 weights, 64 with quantised ones.
@@ -1811,11 +1831,15 @@ static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
     fp.gu_split = (WF == 0 && d.T <= kSplitMaxTokens && fp.gu.shared_blocks < kSplitRound) ? 1 : 0;
     fp.gu_blocks = (int)grid_blocks(fp.gu) + (fp.gu_split ? kSplitMaxRem * (kFfnWaves - 1) : 0);
     const unsigned dn_blocks = grid_blocks(fp.dn);
+    // (live items are the first ones: the second of two launches that share them runs them only where they are fewer than fill)
+    const unsigned dn_last = sh.fill > 0 ? min(dn_blocks, (unsigned)sh.fill) : dn_blocks;
     int rc = LYNX_OK;
+    fp.fill = sh.fill;
     for (int part = 0; part < (sh.single ? 1 : 2) && rc == LYNX_OK; ++part) {
-        fp.wait = sh.single ? 1 : 0;
+        const bool both = part == 0 && (sh.single || sh.fill > 0);
+        fp.wait = both ? 1 : 0;
         fp.block0 = part == 0 ? 0 : fp.gu_blocks;
-        const unsigned blocks = sh.single ? (unsigned)fp.gu_blocks + dn_blocks : part == 0 ? (unsigned)fp.gu_blocks : dn_blocks;
+        const unsigned blocks = both ? (unsigned)fp.gu_blocks + dn_blocks : part == 0 ? (unsigned)fp.gu_blocks : dn_last;
         if (WF == 0 && sh.big == 3)
             hipLaunchKernelGGL(ffn_wide_kernel, dim3(blocks), dim3(kFfnThreads), 0, st, fp);
         else if (sh.big == 2 && sh.kwd == 1)
@@ -1980,6 +2004,7 @@ int moe_ffn_impl(const uint16_t *x_bf16, const uint16_t *Wgu_packed, const uint1
         if (rc != LYNX_OK) return rc;
         x_bf16 = reinterpret_cast<const uint16_t *>(obuf);
         shape.single = false;
+        shape.fill = 0;
     }
     if (!plan_ready) {
         hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(256), 0, st, expert_offsets, perm, N, T * k, shape.plan, rws);

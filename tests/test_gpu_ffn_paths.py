@@ -259,6 +259,51 @@ def test_huge_quantised_experts_in_one_launch(L, fmt, T, H, F):
     run_case(L, fmt, T, tuple(min(T, c) for c in (64, 20, 8, 7, 5, 3, 2, 1)), H, F, 0, 0)
 
 
+# Which launch the down workgroups of huge quantised experts run in.  A poll limit of zero and a count that is never reached make
+# every wait give up at once: status 1 where they are in the launch of the gate/up workgroups and wait for them, 0 where they
+# follow it.  64-row workgroups (H / 64 per expert) fill the chip from 384 on, 32-row ones (8 tokens, FP8) from 512; the live count
+# decides where k experts are too few and N are enough.
+@pytest.mark.parametrize("fmt,T,H,F,N,k,live,waits", [
+    ("fp8", 16, 4096, 4160, 8, 2, 6, 1), ("fp8", 16, 4096, 4160, 8, 2, 5, 0), ("fp4", 64, 4096, 4224, 8, 2, 6, 1),
+    ("fp4", 64, 4096, 4224, 8, 2, 5, 0), ("fp8", 8, 4096, 4160, 8, 2, 4, 1), ("fp8", 8, 4096, 4160, 8, 2, 3, 0),
+    ("fp8", 7, 4096, 4160, 8, 2, 8, 0), ("fp8", 65, 4096, 4160, 8, 2, 8, 0),      # outside the batch sizes of the rule
+    ("fp8", 16, 4096, 4160, 6, 2, 6, 1), ("fp8", 16, 4032, 4160, 6, 2, 6, 0),     # N experts are just enough, and not (63 rows of 64)
+    ("fp8", 16, 4096, 4160, 8, 6, 6, 1),                                          # k experts are enough: always one launch
+    ("bf16", 16, 4096, 4128, 8, 2, 8, 0),
+])
+def test_launches_of_huge_quantised_experts(L, fmt, T, H, F, N, k, live, waits):
+    from paper_2411_08982_amd import binding as B
+    print(f"ffn launches {fmt} T={T} H={H} F={F} N={N} k={k} live={live}", flush=True)
+    rng = np.random.default_rng([T, H, F, live])
+    names = rng.permutation(N)[:live]
+    idx = dev(np.stack([np.roll(names, t)[:k] for t in range(T)]).astype(np.int32))     # every one of them is picked
+    gate = dev(rng.uniform(0.1, 1.0, (T, k)).astype(np.float32))
+    gen = torch.Generator(device="cuda").manual_seed(T * live)
+    mk = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.05, generator=gen)
+    pack, ffn = {"bf16": (L.lynx_pack_weights, L.lynx_moe_ffn), "fp8": (L.lynx_quantize_weights_fp8, L.lynx_moe_ffn_fp8),
+                 "fp4": (L.lynx_quantize_weights_fp4, L.lynx_moe_ffn_fp4)}[fmt]
+    W = pack(mk(N, F, H), mk(N, F, H), mk(N, H, F))
+    W = tuple(W) if fmt == "bf16" else (W,)
+    x = mk(T, H)
+    p = L.lynx_permute(idx, N)
+    ws = L.new_workspace(T, H, F, N, k)
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    call = lambda x: host(ffn(x, *W, idx, gate, p, N, F, workspace=ws.fill_(0xFF), status=status))
+    y = call(x)
+    assert host(status)[0] == 0 and np.all(np.isfinite(y)) and np.any(y)
+    odd = torch.empty(T * H + 8, dtype=torch.bfloat16, device="cuda")[1:1 + T * H].view(T, H)   # always two launches
+    odd.copy_(x)
+    assert np.array_equal(call(odd), y)
+    try:
+        L.lynx_debug_set(B.DEBUG_SPIN_LIMIT, 0)
+        L.lynx_debug_set(B.DEBUG_TARGET_BIAS, 1 << 20)
+        call(x)
+    finally:
+        L.lynx_debug_set(B.DEBUG_SPIN_LIMIT, -1)
+        L.lynx_debug_set(B.DEBUG_TARGET_BIAS, 0)
+    assert host(status)[0] == waits
+
+
 def test_overlapping_expert_ranges_stay_inside_the_plan(L):
     """expert_offsets that lynx_permute cannot have written: every second expert claims all pairs, which makes more token
     blocks than the work plan has records, and the last expert, behind them, a few (its pair ids would be filed).  What
