@@ -146,6 +146,15 @@ __device__ __forceinline__ void wave_topk(const float (&v)[NS], unsigned cand, i
     }
 }
 
+// Between LDS writes and reads of lanes of ONE wave: the reads behind it see the writes before it.  LDS serves a wave in order, so
+// it costs no instruction; it keeps the compiler from moving an access of one side past those of the other.
+__device__ __forceinline__ void wave_lds_handover()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- data handed from one workgroup to another inside a launch ---------------------------------------------
 // Every XCD has its own L2, and a device-wide fence (write back / invalidate that L2) costs microseconds per
 // workgroup.  Instead, the few words that another workgroup of the same launch will read are written with

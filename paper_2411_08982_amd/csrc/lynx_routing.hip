@@ -218,6 +218,7 @@ __global__ __launch_bounds__(kLogitsWaves * kWave) void logits_mfma_kernel(const
         for (int i = 0; i < 4; ++i) wt[wave][((lane >> 4) + 4 * i) * 16 + (wp ^ ((lane >> 4) + 4 * i))] = wr[i];
         load(min(c + 1, chunks - 1));   // (the last chunk again at the end, from the cache)
         __builtin_amdgcn_sched_barrier(0);
+        wave_lds_handover();
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const logits_u32x4 xv = xt[wave][row * 8 + ((q * 4 + g) ^ (row & 7))];
@@ -229,6 +230,7 @@ __global__ __launch_bounds__(kLogitsWaves * kWave) void logits_mfma_kernel(const
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
         }
+        wave_lds_handover();
         __builtin_amdgcn_sched_barrier(0);
     }
     if (wave > 0) part[wave - 1][lane] = acc;
@@ -467,7 +469,7 @@ __device__ __forceinline__ void wave_fill_active(int N, int k, const int *order,
         if (u[i] && __popcll(b & ((1ull << lane) - 1ull)) < need) filled[er[i]] = 1;
         need -= __popcll(b);
     }
-    __builtin_amdgcn_wave_barrier();   // (the wave reads its own writes behind this; LDS serves a wave in order)
+    wave_lds_handover();   // (a lane's entries are read by others of its wave behind this)
 }
 
 // Selection of one token inside the active set (Secs. 3.4, 4): lane j < k holds its j-th expert in mye (-1 = none) and that
