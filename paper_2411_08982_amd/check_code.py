@@ -10,9 +10,10 @@ until at most as many loads are outstanding as it has issued behind them, a numb
 the compiler neither drops nor merges loads.  They are counted again in the machine code, ahead of every barrier behind a
 direct-to-LDS load, in the order of the listing (the kernel's loops around them are laid out straight).
 
-Operands: the wide kernel's matrix instructions are written out, so the compiler does not keep the two wait states between a VALU
-instruction that writes an operand of theirs and its use.  Their operands come from loads; that no VALU instruction writes one
-so late is checked in the machine code.
+Products: the wide kernel's matrix instructions are written out, so the compiler does not keep the wait states that they need: two
+between a VALU instruction that writes an operand of theirs and its use, and up to 19 (for the longest of them) between a product and
+any other instruction on its sums.  Their operands come from loads and their sums stay in place; that no instruction comes too
+close is checked in the machine code, in the order of the listing and across every branch.
 """
 from __future__ import annotations
 
@@ -87,40 +88,98 @@ def check_waits(listing: str) -> int:
     return barriers
 
 
-def _vector_registers(operand: str) -> set:
-    m = re.fullmatch(r"v(?:\[(\d+):(\d+)\]|(\d+))", operand)
+SUM_STATES = 19       # most wait states between a product and another instruction on its sums
+OPERAND_STATES = 2    # between a VALU instruction and a product that takes what it writes
+
+
+def _registers(operand: str) -> set:
+    m = re.fullmatch(r"-?\|?([va])(?:\[(\d+):(\d+)\]|(\d+))\|?", operand)
     if not m:
         return set()
-    lo = int(m.group(1) or m.group(3))
-    return set(range(lo, int(m.group(2) or lo) + 1))
+    lo = int(m.group(2) or m.group(4))
+    return {(m.group(1), i) for i in range(lo, int(m.group(3) or lo) + 1)}
+
+
+class _Instruction:
+    """What the products' wait states depend on, from a line of the listing."""
+
+    def __init__(self, line: str):
+        words = line.split("//")[0].replace(",", " ").split()
+        self.text, op = line.strip(), words[0]
+        self.product = op.startswith("v_mfma")
+        self.states = int(words[1], 0) + 1 if op == "s_nop" else 1
+        self.regs = set().union(*map(_registers, words[1:]))
+        self.sums = _registers(words[1]) if self.product else set()
+        self.writes = set()
+        if op.startswith("v_") and not self.product and not op.startswith("v_cmp"):
+            self.writes = _registers(words[1])
+            if "swap" in op:      # (writes both operands)
+                self.writes |= _registers(words[2])
+        self.ends = op in ("s_branch", "s_endpgm", "s_setpc_b64")
+        m = re.search(r"//\s*([0-9A-Fa-f]+):", line)
+        self.address = int(m.group(1), 16) if m else None
+        m = re.search(r"<\S+?(?:\+0x([0-9a-f]+))?>\s*$", line) if op.startswith(("s_branch", "s_cbranch")) else None
+        self.jump = int(m.group(1) or "0", 16) if m else None     # from the start of the function
+
+
+def _check_distances(ins: _Instruction, recent: list):
+    states = 0
+    for before in reversed(recent):
+        if states >= SUM_STATES:
+            return
+        if ins.product and states < OPERAND_STATES and before.writes & ins.regs:
+            raise RuntimeError(f"{ins.text} uses a register that was written {states} states before")
+        if not ins.product and before.sums & ins.regs:
+            raise RuntimeError(f"{ins.text} uses a sum of a product {states} states before")
+        states += before.states
+
+
+def _check_function(name: str, start: int, code: list):
+    at = {ins.address: i for i, ins in enumerate(code) if ins.address is not None}
+    paths = [(0, [], None)]       # where a path begins, what ran before it, how many states it is followed for (None: to the end)
+    while paths:
+        i, recent, left = paths.pop()
+        while i < len(code) and (left is None or left > 0):
+            ins = code[i]
+            try:
+                _check_distances(ins, recent)
+            except RuntimeError as e:
+                raise RuntimeError(f"{name}: {e}") from None
+            recent = recent[-SUM_STATES:] + [ins]
+            if left is not None:
+                left -= ins.states
+            if ins.jump is not None:
+                if start + ins.jump not in at:
+                    raise RuntimeError(f"{name}: {ins.text}: no instruction at its target")
+                if left is None or left > 0:
+                    paths.append((at[start + ins.jump], recent, SUM_STATES if left is None else left))
+            if ins.ends:
+                if left is not None:
+                    break
+                recent = []
+            i += 1
 
 
 def check_operands(listing: str) -> int:
-    """Raises if a VALU instruction of the wide kernel writes an operand of a matrix instruction within two wait states of its
-    use; the number of matrix instructions."""
+    """Raises if an instruction of the wide kernel comes too close to a matrix instruction (see above); the number of matrix
+    instructions."""
     products = 0
-    name = ""
-    recent = []           # (wait states it stands for, vector registers that a VALU instruction writes)
+    name, start, code = "", 0, []
+
+    def finish():
+        nonlocal products
+        if WIDE in name:
+            _check_function(name, start, code)
+            products += sum(ins.product for ins in code)
+
     for line in listing.splitlines():
-        head = re.match(r"[0-9a-f]+ <(\S+)>:", line)
+        head = re.match(r"([0-9a-f]+) <(\S+)>:", line)
         if head:
-            name, recent = head.group(1), []
-            continue
-        words = line.split("//")[0].replace(",", " ").split()
-        if not words or WIDE not in name:
-            continue
-        op = words[0]
-        if op.startswith("v_mfma"):
-            products += 1
-            states = 0
-            for n, written in reversed(recent):
-                if states >= 2:
-                    break
-                if written & (_vector_registers(words[2]) | _vector_registers(words[3])):
-                    raise RuntimeError(f"{name}: {line.strip()} uses a register that was written {states} states before")
-                states += n
-        valu = op.startswith("v_") and not op.startswith(("v_mfma", "v_cmp", "v_readlane", "v_readfirstlane"))
-        recent = recent[-3:] + [(int(words[1]) + 1 if op == "s_nop" else 1, _vector_registers(words[1]) if valu else set())]
+            finish()
+            name, start, code = head.group(2), int(head.group(1), 16), []
+        elif WIDE in name and line.split("//")[0].strip():
+            code.append(_Instruction(line))
+    finish()
     return products
 
 

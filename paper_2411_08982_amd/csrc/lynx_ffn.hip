@@ -1182,9 +1182,10 @@ constexpr int kWideBuffer = kWideTokens * kWideCols * 2;
 
 // One product.  Written out, because the compiler (left alone it keeps the sums in the other half of the registers, where they do
 // not fit beside the operands, and spills hundreds) has to be told that they live in accumulator registers.  It does not know what
-// is inside and inserts no waits between this and VALU instructions: settle_sums() stands between the sums and ordinary code, no
-// sum is used again for 4 * NT products, and the operands come from loads (the build checks that no VALU instruction writes one
-// in the two states before its use).
+// is inside and inserts no waits between this and other instructions: settle_sums() stands between the sums and ordinary code, no
+// sum is used again for 4 * NT products, and the operands come from loads.  The build checks in the machine code that no VALU
+// instruction writes an operand in the two states before its use, and that nothing else reads or writes a sum (a copy or a spill that
+// the compiler puts in) less than 19 states behind its product, in both cases across branches too.
 __device__ __forceinline__ void mfma_acc(f32x4 &c, bf16x8 a, bf16x8 b)
 {
     asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));

@@ -71,3 +71,43 @@ def test_a_late_write_of_an_operand_is_refused(before, ok):
     else:
         with pytest.raises(RuntimeError, match="written"):
             check_code.check_operands(listing)
+
+
+PRODUCT = "v_mfma_f32_16x16x32_bf16 a[0:3], v[8:11], v[20:23], a[0:3]"
+
+
+def wide_listing(body, symbol="_ZN4lynx15ffn_wide_kernelENS_9FfnParamsE"):
+    """body, four bytes an instruction from 0x6700; "-> n": the target of a branch is the n-th instruction."""
+    out = [f"0000000000006700 <{symbol}>:"]
+    for i, text in enumerate(body):
+        op, _, target = text.partition(" -> ")
+        mark = f" <{symbol}+0x{4 * int(target):x}>" if target and int(target) else f" <{symbol}>" if target else ""
+        out.append(f"\t{op}{' 0' if target else ''}    // {0x6700 + 4 * i:012X}: BF800000{mark}")
+    return "\n".join(out) + "\n"
+
+
+# A sum of a product is touched too soon (moved, read, stored, loaded over), or written too late; the instructions that exchange two
+# registers write both; a write at the end of a loop meets the product at its top, also behind a second branch.
+@pytest.mark.parametrize("body,ok", [
+    ([PRODUCT, "v_accvgpr_read_b32 v1, a2"], False),
+    ([PRODUCT, "v_accvgpr_read_b32 v1, a4"], True),
+    ([PRODUCT, "s_nop 15", "s_nop 1", "v_accvgpr_mov_b32 a9, a3"], False),
+    ([PRODUCT, "s_nop 15", "s_nop 2", "v_accvgpr_mov_b32 a9, a3"], True),
+    ([PRODUCT, "global_store_dwordx4 v[30:31], a[0:3], off"], False),
+    ([PRODUCT, "ds_read_b128 a[0:3], v40"], False),
+    (["v_accvgpr_write_b32 a3, v1", "s_nop 0", PRODUCT], False),
+    (["v_accvgpr_write_b32 a3, v1", "s_nop 1", PRODUCT], True),
+    (["v_swap_b32 v1, v9", PRODUCT], False),
+    (["v_permlane32_swap_b32_e32 v1, v23", "s_nop 0", PRODUCT], False),
+    ([PRODUCT, "v_mov_b32_e32 v9, v1", "s_cbranch_scc1 -> 0", "s_endpgm"], False),
+    ([PRODUCT, "v_mov_b32_e32 v9, v1", "s_nop 0", "s_cbranch_scc1 -> 0", "s_endpgm"], True),
+    (["s_nop 0", PRODUCT, "s_cbranch_scc0 -> 5", "s_nop 15", "s_nop 15", "s_branch -> 7", "s_endpgm", "v_accvgpr_read_b32 v1, a0"], False),
+    ([PRODUCT, "s_branch -> 3", "v_accvgpr_read_b32 v1, a0", "s_endpgm"], True),
+])
+def test_what_comes_too_close_to_a_product_is_refused(body, ok):
+    if ok:
+        assert check_code.check_operands(wide_listing(body)) == 1
+    else:
+        with pytest.raises(RuntimeError, match="states before"):
+            check_code.check_operands(wide_listing(body))
+    assert check_code.check_operands(wide_listing(body, "_ZN4lynx10ffn_kernelILi1EEEvNS_9FfnParamsE")) == 0
