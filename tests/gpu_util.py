@@ -63,3 +63,13 @@ def tile_covering_tokens(offsets, perm, k):
             pos = offsets[e] + min(16 * tile + (5 * tile + 3) % 16, int(te[e]) - 1)   # a different lane in every tile
             picked.append(int(perm[pos]) // k)
     return picked
+
+
+def planned_blocks(workspace):
+    """Token blocks in the FFN's work plan of the last call on this workspace (word 0 of the plan's header)."""
+    return int(workspace.view(torch.int32)[9760])
+
+
+def token_blocks(counts, tok_block):
+    """The same from the tokens per expert: up to 16 tokens are one block, more are cut into blocks of tok_block."""
+    return sum(1 if c <= 16 else -(-c // tok_block) for c in map(int, counts) if c)

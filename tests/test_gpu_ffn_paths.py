@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 
 import oracle
 import workloads as wl
-from gpu_util import dev, host, row_rel_err, to_bf16_dev
+from gpu_util import dev, host, planned_blocks, row_rel_err, to_bf16_dev, token_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -23,7 +23,7 @@ def L():
     return L
 
 
-def run_case(L, fmt, T, counts, H, F, S, Fs, spare=0):
+def run_case(L, fmt, T, counts, H, F, S, Fs, spare=0, tok_block=None):
     print(f"ffn paths {fmt} T={T} counts={counts} spare={spare} H={H} F={F} shared={S}x{Fs}", flush=True)
     k = len(counts)
     N = k + spare      # experts that no token picks
@@ -65,6 +65,7 @@ def run_case(L, fmt, T, counts, H, F, S, Fs, spare=0):
     torch.cuda.synchronize()
     got = host(y)
     assert host(status)[0] == 0
+    assert tok_block is None or planned_blocks(ws) == token_blocks(counts, tok_block)
     assert np.all(np.isfinite(got))
     err = row_rel_err(got, ref).max()
     assert err <= Y_TOL, f"max row error {err:.3e}"
@@ -246,9 +247,11 @@ def test_wide_kernel(L, case):
     from paper_2411_08982_amd import binding as B
     L.lynx_debug_set(B.DEBUG_WIDE_KERNEL, 1)
     try:
-        run_case(L, "bf16", *case)
+        run_case(L, "bf16", *case, tok_block=256)
     finally:
         L.lynx_debug_set(B.DEBUG_WIDE_KERNEL, 0)
+    T, counts, *_ = case
+    assert max(counts) <= 128 or token_blocks(counts, 256) < token_blocks(counts, 128)   # (the plan tells the kernels apart)
 
 
 # One launch for quantised experts past 4096 columns from 8 to 64 tokens, where 512 down workgroups exist: both edges of the

@@ -16,7 +16,7 @@ import torch
 
 import oracle
 import workloads as wl
-from gpu_util import bf16_bits, dev, host, row_rel_err, tile_covering_tokens, to_bf16_dev
+from gpu_util import bf16_bits, dev, host, planned_blocks, row_rel_err, tile_covering_tokens, to_bf16_dev, token_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -195,6 +195,45 @@ def test_single_launch_reads_no_stale_intermediates(L, name, T):
 def test_release_large_layers():
     _layers.clear()
     torch.cuda.empty_cache()
+
+
+# Large bf16 batches through the fused layer, whose routing writes the plan: the kernel for token blocks of 256 where the library's
+# rule takes it (in one launch and, past 4096 columns, in two) and blocks of 128 just short of each of its lines: F * T * k, H, tokens
+# per expert.  Sampled tokens sit in every column tile of the fullest expert's blocks.
+@pytest.mark.parametrize("T,H,F,N,preset,tok_block", [(1023, 4096, 3872, 4, "off", 256), (1000, 4096, 4128, 4, "moderate", 256),
+                                                      (1023, 4096, 3840, 4, "off", 128), (1023, 4064, 3904, 4, "off", 128),
+                                                      (512, 4096, 7712, 8, "off", 128)])
+def test_wide_kernel_by_the_rule(L, T, H, F, N, preset, tok_block):
+    print(f"large layer T={T} H={H} F={F} N={N} remap={preset}", flush=True)
+    cfg = dataclasses.replace(wl.CONFIGS["mixtral"], name="wide", H=H, F=F, N=N, seed=F)
+    (alpha, beta), enable = ((2.0, 2), 0) if preset == "off" else (wl.PRESETS[preset], 1)
+    lay = DeviceLayer(L, cfg, T)
+    _check_layer(L, lay, T, alpha, beta, enable, n_sample=2)
+    b = L.lynx_moe_layer(to_bf16_dev(lay.tokens(T)), lay.d["Wr"], lay.d["bias"], lay.Wgu, lay.Wdp, F, cfg.k, alpha, beta, enable)
+    counts = host(b.cnt_after)
+    assert planned_blocks(b.workspace) == token_blocks(counts, tok_block)
+    assert token_blocks(counts, 256) < token_blocks(counts, 128) < token_blocks(counts, 64)
+
+
+@pytest.mark.parametrize("T,H,F,N,k,S,Fs,preset", [(600, 256, 512, 6, 2, 0, 0, "off"), (300, 160, 352, 40, 3, 1, 1024, "moderate"),
+                                                   (1024, 96, 4384, 5, 2, 2, 320, "aggressive")])
+def test_wide_kernel_in_small_layers(L, T, H, F, N, k, S, Fs, preset):
+    """The same path with the kernel's knob set: small sizes, shared experts, experts on few tokens beside full blocks."""
+    from paper_2411_08982_amd import binding as B
+    print(f"small layer on the wide kernel T={T} H={H} F={F} N={N} remap={preset}", flush=True)
+    cfg = dataclasses.replace(wl.CONFIGS["tiny"], name="wide", H=H, F=F, N=N, k=k, n_shared=S, F_shared=Fs, seed=F)
+    (alpha, beta), enable = ((2.0, 2), 0) if preset == "off" else (wl.PRESETS[preset], 1)
+    lay = DeviceLayer(L, cfg, T)
+    try:
+        L.lynx_debug_set(B.DEBUG_WIDE_KERNEL, 1)
+        _check_layer(L, lay, T, alpha, beta, enable, n_sample=40)
+        b = L.lynx_moe_layer(to_bf16_dev(lay.tokens(T)), lay.d["Wr"], lay.d["bias"], lay.Wgu, lay.Wdp, F, k, alpha, beta, enable,
+                             lay.Sgu, lay.Sdp, S, Fs)
+        torch.cuda.synchronize()
+    finally:
+        L.lynx_debug_set(B.DEBUG_WIDE_KERNEL, 0)
+    counts = host(b.cnt_after)
+    assert planned_blocks(b.workspace) == token_blocks(counts, 256) < token_blocks(counts, 128)
 
 
 # ---- limits and ragged sizes through the fused entry point, small H / F so that the oracle does the whole batch ----
