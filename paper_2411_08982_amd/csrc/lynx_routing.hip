@@ -159,6 +159,9 @@ __global__ __launch_bounds__(256) void logits_kernel(const uint16_t *__restrict_
 // expert l%16, k group l/16), D: lane l holds expert l%16 for tokens 4*(l/16) .. +3.  A k-step is 32 columns: a lane holds the
 // 8 consecutive columns of its k group, and the j-th of its 8 values goes into the j-th of 8 MFMAs (any assignment of columns
 // to MFMAs is right as long as A and B agree).
+// The eight MFMAs have a sum each: with eight waves a chain of fp32 additions is then H / 64 terms long, as in logits_kernel, and the
+// rounding error is the same (2-norm of the difference from the 64-bit logits over theirs, H = 2048: 1.2e-7, H = 7168: 2.0e-7; with
+// one sum per wave 2.9e-7 and 5.4e-7).  It costs 0.1 us per launch at H = 512, nothing that shows from H = 2048 on.
 // Loads in operand order gather 16 bytes of sixteen rows side by side, 47 cycles of the load path each, and bound the kernel
 // (neither more waves nor a deeper ring, nor leaving the products out, made it faster).  So a wave loads chunks of 64 columns in
 // whole rows (128 bytes of x, 256 of Wr per row), one chunk ahead, and turns them over in an LDS region of its own: no barrier.
@@ -204,7 +207,7 @@ __global__ __launch_bounds__(kLogitsWaves * kWave) void logits_mfma_kernel(const
     };
     const int xs = (lane >> 3) * 8 + (xp ^ (lane >> 3));     // (rows 8 apart share row % 8)
     const int row = lane & 15, g = lane >> 4;
-    logits_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    logits_f32x4 acc[8] = {};   // one per MFMA of a k-step (see above)
     load(0);
     zero_slices(z, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid, kLogitsWaves * kWave);
     for (int c = 0; c < chunks; ++c) {
@@ -228,23 +231,24 @@ __global__ __launch_bounds__(kLogitsWaves * kWave) void logits_mfma_kernel(const
                                 bf16_lo(xv.z), bf16_hi(xv.z), bf16_lo(xv.w), bf16_hi(xv.w)};
             const float b[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+            for (int j = 0; j < 8; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc[j], 0, 0, 0);
         }
         wave_lds_handover();
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (wave > 0) part[wave - 1][lane] = acc;
+    logits_f32x4 sum = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    if (wave > 0) part[wave - 1][lane] = sum;
     __syncthreads();
     if (wave != 0) return;
-#pragma unroll
-    for (int w = 0; w < kLogitsWaves - 1; ++w) acc += part[w][lane];   // fixed order
+    static_assert(kLogitsWaves == 8, "the tree below");
+    sum = ((sum + part[0][lane]) + (part[1][lane] + part[2][lane])) + ((part[3][lane] + part[4][lane]) + (part[5][lane] + part[6][lane]));
     const int e = e0 + (lane & 15);
     if (e >= N) return;
     const float bv = bias ? bias[e] : 0.f;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int t = t0 + 4 * (lane >> 4) + v;
-        if (t < T) logits[(size_t)t * N + e] = acc[v] + bv;
+        if (t < T) logits[(size_t)t * N + e] = sum[v] + bv;
     }
 }
 

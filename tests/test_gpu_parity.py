@@ -662,3 +662,20 @@ def test_layer_zero_tokens(L):
     torch.cuda.synchronize()
     assert host(b.num_active).tolist() == [0, 0] and host(b.num_active_perm).tolist() == [0]
     assert np.all(host(b.offsets) == 0) and np.all(host(b.active) == -1)
+
+
+# The logits of small and large batches come from different kernels; both add chains of H / 64 fp32 terms (64 of them per logit, then six
+# levels of a tree).  With rounding errors of at most u = 2^-24 of the partial sum, uniform and independent, the i-th step of a chain of
+# terms of variance s^2 adds i s^2 u^2 / 3: n^2 / 6 for a chain of n = H / 64, 64 times that over the H s^2 of a logit is H / 384;
+# every level of the tree adds u^2 / 3.
+@pytest.mark.parametrize("T,H,N", [(64, 512, 128), (130, 2048, 64), (64, 2048, 128), (48, 7168, 256), (129, 4096, 128), (200, 1056, 60),
+                                   (64, 4096, 64)])
+def test_rounding_error_of_the_logits(L, T, H, N):
+    _say(f"logits against 64 bits T={T} H={H} N={N}")
+    g = torch.Generator(device="cuda").manual_seed(H + N)
+    x = torch.randn(T, H, device="cuda", generator=g).to(torch.bfloat16)
+    Wr = torch.randn(N, H, device="cuda", generator=g)
+    z = L.lynx_route(x, Wr, None, 1)["logits"]
+    exact = x.double() @ Wr.double().T
+    err = float((z.double() - exact).norm() / exact.norm())
+    assert err <= 2.0 ** -24 * (H / 384 + 2) ** 0.5, f"{err:.3e}"
