@@ -1154,15 +1154,26 @@ static void add_zero(ZeroList &z, int32_t *p, int count)
     ++z.n;
 }
 
-// Larger batches on the matrix cores.  Below 129 tokens it depends on the experts too (us, logits_kernel against the matrix cores,
-// H = 2048: 32 tokens x 128 experts 5.8 and 6.4, 61 x 64 5.7 and 6.5, 100 x 128 8.6 and 6.6; H = 7168: 32 x 256 17.6 and 14.7;
-// H = 4096: 128 x 8 5.9 and 9.9).
-static bool logits_on_matrix_cores(int T, int N) { return T > 128 || (long)T * N >= 8192; }
+// Larger batches on the matrix cores, whose time hardly grows with the batch (a workgroup for 16 tokens and 16 experts streams both and is
+// bound by the latency of that): where the line lies depends on the products of tokens and experts, on H, which is what a
+// workgroup streams, and on whether the router fits an XCD's L2 (4 MiB), since logits_kernel reads it again for every four tokens.
+// us per lynx_route call, logits_kernel against the matrix cores, the router's rows not in a cache:
+//   H = 1024:   129 x 8   7.1, 6.9   128 x 32  7.1, 7.1   512 x 8   7.1, 7.1
+//   H = 2048:   128 x 64  8.3, 8.8   129 x 64  9.5, 8.8   512 x 16  8.1, 8.8   720 x 16  9.5, 8.9   1024 x 8  8.1, 8.9
+//   H = 4096:   129 x 8   8.2, 12.1  64 x 128 11.6, 12.7  256 x 64 11.8, 12.2  100 x 128 13.5, 12.7  360 x 64 15.0, 12.3
+//   H = 7168:   64 x 128 15.4, 17.9  180 x 64 17.9, 17.9  512 x 32 18.1, 17.5  100 x 128 19.5, 18.0  1024 x 8 12.6, 17.5
+//   a router of 4 MiB and more, 32 x 256:  H = 4096 14.7, 13.0   H = 7168 20.1, 18.2;  16 x 256: 10.6, 12.9 and 15.4, 18.1
+static bool logits_on_matrix_cores(int T, int H, int N)
+{
+    const long work = (long)T * N;
+    if (H <= 1024) return T > 128 || work >= 8192;
+    return work >= ((long)N * H >= 1 << 20 ? 8192 : min(4L * H, 12288L));
+}
 
 static void launch_logits(const uint16_t *x, const float *Wr, const float *bias, int T, int H, int N, float *logits,
                           const ZeroList &z, hipStream_t st)
 {
-    if (logits_on_matrix_cores(T, N))
+    if (logits_on_matrix_cores(T, H, N))
         hipLaunchKernelGGL(logits_mfma_kernel, dim3((N + 15) / 16, (T + 15) / 16), dim3(kLogitsWaves * kWave), 0, st, x, Wr, bias, T, H, N,
                            logits, z);
     else

@@ -669,7 +669,8 @@ def test_layer_zero_tokens(L):
 # terms of variance s^2 adds i s^2 u^2 / 3: n^2 / 6 for a chain of n = H / 64, 64 times that over the H s^2 of a logit is H / 384;
 # every level of the tree adds u^2 / 3.
 @pytest.mark.parametrize("T,H,N", [(64, 512, 128), (130, 2048, 64), (64, 2048, 128), (48, 7168, 256), (129, 4096, 128), (200, 1056, 60),
-                                   (64, 4096, 64)])
+                                   (64, 4096, 64),
+                                   (129, 2048, 8), (1024, 2048, 9), (1024, 4096, 11), (1024, 4096, 12), (63, 4128, 128)])   # either side of the line
 def test_rounding_error_of_the_logits(L, T, H, N):
     _say(f"logits against 64 bits T={T} H={H} N={N}")
     g = torch.Generator(device="cuda").manual_seed(H + N)
