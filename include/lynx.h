@@ -140,7 +140,7 @@ int lynx_pack_weights(const uint16_t *Wg, const uint16_t *Wu, const uint16_t *Wd
  *                                                                      Sec. 3.3.1 last paragraph)
  * bf16 operands, fp32 accumulation; the intermediate vector is rounded to bf16 between the two
  * projections.  Each invoked expert's weights are read once per call (an expert with more tokens than one pass of
- * the kernel holds, 64 or 128, once per pass); experts with no pair are not touched.  Weights in the packed layout of
+ * the kernel holds, 64, 128 or 256, once per pass); experts with no pair are not touched.  Weights in the packed layout of
  * lynx_pack_weights (Sgu/Sd: packed with E = n_shared, F = F_shared; NULL when n_shared = 0).  expert_offsets / perm as
  * written by lynx_permute for the same idx: the invoked experts are those with a non-empty range in expert_offsets
  * (active_experts / num_active are accepted for symmetry with lynx_permute and not read).  y [T,H] fp32 out, overwritten.

@@ -50,7 +50,7 @@ int moe_ffn_impl(const uint16_t *x_bf16, const uint16_t *Wgu_packed, const uint1
 }
 
 // The fused path issues the routing side in two launches up to 16 tokens (logits; everything else in one
-// workgroup) and in four beyond (logits; top-k + bins; nominations; remap + token assignment) instead of the
+// workgroup, which computes the logits of small routers as well: one launch) and in four beyond (logits; top-k + bins; nominations; remap + token assignment) instead of the
 // launches of the separate calls; results are identical.
 namespace lynx {
 static int moe_layer_impl(const uint16_t *x_bf16, const float *Wr, const float *bias, const uint16_t *Wgu_packed,

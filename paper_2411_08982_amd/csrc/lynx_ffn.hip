@@ -915,7 +915,7 @@ __device__ __forceinline__ void staged_pass(const WorkItem &w, int nb, const int
 // with at most kDirectMaxTokens tokens takes the direct path with the workgroup's four waves as RW row tiles x KW
 // slices of K.  A larger expert takes the staged path, in which a workgroup covers 64 rows (128 in the large-batch kernels:
 // see staged_row_tiles): where a direct workgroup covers fewer, one of those that share the rows does the work, one pass of
-// up to 64 (128) tokens per item, and the others leave.  A down
+// up to 64 (128) tokens per item, and the others leave.  (The wide kernel has the same grid with units and blocks of its own.)  A down
 // item covers m consecutive row units, m chosen on the device from the number of (expert, token block) pairs: few
 // invoked experts get short items that fill the chip, many get fewer, longer ones, whose start-up (tables, first
 // tiles) weighs less.  The gate/up part of the grid ends with spare workgroups: when the last round of live gate/up
@@ -1171,10 +1171,10 @@ __global__ __launch_bounds__(kFfnThreads, kWgPerCu) void ffn_kernel(FfnParams fp
 //     weights: loads return in order, so whatever is waited for earlier shortens the way of everything behind it;
 //   * three LDS buffers and one barrier per chunk, in the middle of its products: a wave that is past it may write the
 //     buffer after next while another still reads the last one.
-// Mixtral shapes, 1000 tokens, us per layer 1107 -> 880 (gate/up 670 -> 510, down 417 -> 330): matrix cores busy half of the
+// Mixtral shapes, 1000 tokens, us per layer 1106 -> 898 (gate/up 670 -> 510, down 417 -> 330): matrix cores busy half of the
 // time a wave is there (8 of 10 states with the weights in the caches), gate/up 5.2 rounds of workgroups, down 208 of them, one
-// to a CU.  On the way: products in fours with the rest behind them 1008, dealt out between them 957; a turn of two chunks without
-// a way out in the middle 915; loads further apart, 866 to 881.
+// to a CU.  On the way (where it ended at 875): products in fours with the rest behind them 1008, dealt out between them 957; a
+// turn of two chunks without a way out in the middle 915; loads further apart 866 to 881.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kWideTokens = 256;             // tokens per block
 constexpr int kWideCols = 64;                // columns of a chunk: whole 128-byte lines of a token row
@@ -1727,10 +1727,12 @@ static void launch_shape(FfnShape &s, int T, int F, int k, int max_experts, int 
 }
 
 // The wide kernel pays with more than 128 tokens per expert on average, where its workgroups are long (a quarter of a wave's time
-// is start and end at H = 2048) and several per CU.  us, ffn_kernel against the wide one: Mixtral shapes, 400 tokens 674 against
-// 685, 520 tokens 744 -> 724, 700 tokens 823 -> 759, 1000 tokens 1085 -> 870; 12 experts of 4096 x 4096, 400 tokens 256 against
-// 281, 1000 tokens 363 -> 328; 16 experts of 2048 x 2048 (four picks), 1000 tokens 191 against 193; 8 of them (two picks) 107
-// against 114; 8 experts of 2048 x 4096, 600 tokens 192 against 204.
+// is start and end at H = 2048) and several per CU.  us per FFN call, ffn_kernel against the wide one: Mixtral shapes, 300 tokens
+// 602 against 657, 400 tokens 672 against 700, 520 tokens 757 -> 721, 700 tokens 837 -> 789, 1000 tokens 1142 -> 907; 12 experts of
+// 4096 x 4096, 400 tokens 267 against 265, 1000 tokens 369 -> 319; 16 experts of 2048 x 2048 (four picks), 1000 tokens 169 against 169;
+// 8 of them (two picks) 110 against 114; 8 experts of 2048 x 4096, 600 tokens 155 against 157.  us per layer: 60 experts of
+// 4096 x 1536 (eight picks) 1024 tokens 639 -> 594, 32 of 4096 x 2048 and a shared one, 600 tokens 495 -> 437, 16 of 7168 x 2048
+// (four picks) and a shared one, 1024 tokens 647 -> 535.
 static bool wide_pays(int T, int H, int F, int N, int k, int format)
 {
     if (format != 0 || T <= kTokBlock) return false;
@@ -1817,7 +1819,8 @@ static void launch_kernel(const FfnParams &fp, unsigned blocks, hipStream_t st)
 // are invoked (launch_shape).
 
 // Gate/up and down over all invoked and shared experts.  Batches of more than 64 tokens take the large-batch kernels, whose
-// staged path makes passes of up to 128 tokens with bf16 weights, 64 with quantised ones.
+// staged path makes passes of up to 128 tokens with bf16 weights, 64 with quantised ones, or the wide kernel with passes of up
+// to 256 (wide_pays).
 template <int WF>
 static int launch_ffn(FfnParams fp, const FfnShape &sh, hipStream_t st)
 {

@@ -11,11 +11,14 @@
 //           block q < B, the invoked experts by ascending id, an expert's blocks in a row;
 //   pairs   [q][i], 16 bits each: the (token, slot) pair id of the i-th token of block q, for the blocks of experts
 //           with at most kDirectMaxTokens tokens (entries past the expert's tokens are not written).
-// An expert with at most kDirectMaxTokens tokens is one token block; a larger one is cut into blocks of tok_block tokens
-// (one pass of the staged path each), which go to workgroups of their own.  The work items of a projection are
+// An expert with at most kDirectMaxTokens tokens is one token block; a larger one is cut into blocks of tok_block tokens (64, 128, or
+// 256 in the wide kernel; one pass over the weights each), which go to workgroups of their own.  The work items of a projection are
 // numbered block-major, unit-minor: item = block * units + unit, so a workgroup knows from its index alone which
 // records to read, and one round trip to memory tells it its expert, its tokens and where their rows are: nothing
 // it needs for its first weight and token loads depends on a second load.
+// Three places write the tables, each from what it has at hand: routing_small_kernel (one block per expert, from the lanes),
+// permute_from_bitsets (the last workgroup of remap_kernel, from the token bit sets) and plan_kernel (build_plan, from ranges
+// that a caller passes in).
 #pragma once
 
 #include "lynx_common.h"
@@ -24,7 +27,7 @@ namespace lynx {
 
 constexpr int kDirectMaxTokens = 16;         // experts with more tokens take the staged path
 constexpr int kTokBlock = 64;                // tokens per pass of the staged path (batches of up to 64 tokens, quantised weights)
-constexpr int kTokBlockBig = 128;            // the same for larger batches with bf16 weights
+constexpr int kTokBlockBig = 128;            // the same for larger batches with bf16 weights (the wide kernel: kWideTokens, 256)
 
 static_assert(LYNX_MAX_N + LYNX_MAX_T * LYNX_MAX_K / kTokBlock <= kPlanMaxBlocks, "the plan must hold every block of a batch");
 
@@ -32,7 +35,7 @@ static_assert(LYNX_MAX_N + LYNX_MAX_T * LYNX_MAX_K / kTokBlock <= kPlanMaxBlocks
 struct PlanShape {
     int units_gu;    // gate/up work items per (expert, token block): units of 64 or 128 of the F rows; 0 = build no plan
     int units_dn;    // down-projection row units per (expert, token block)
-    int tok_block;   // tokens per block of an expert on the staged path
+    int tok_block;   // tokens per block of an expert with more than kDirectMaxTokens
     int dn_cap;      // down items the grid is sized for: the device takes the fewest units per item that fit it
     int dn_m_max;    // most units per down item
     int shared_pairs;   // (shared expert, token block) pairs: completion counters to clear
