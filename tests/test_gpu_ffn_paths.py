@@ -254,8 +254,8 @@ def test_wide_kernel(L, case):
     assert max(counts) <= 128 or token_blocks(counts, 256) < token_blocks(counts, 128)   # (the plan tells the kernels apart)
 
 
-# One launch for quantised experts past 4096 columns from 8 to 64 tokens, where 512 down workgroups exist: both edges of the
-# batch size, direct and staged experts, and just too few workgroups (H = 1920: 480), two launches, beside it.
+# The results for quantised experts past 4096 columns where one launch begins (8 to 64 tokens, 512 down workgroups of 32 rows) and
+# just short of it (7 tokens; H = 1920: 480): direct and staged experts.  How many launches there are shows in the next test.
 @pytest.mark.parametrize("fmt,T,H,F", [("fp8", 7, 2048, 4160), ("fp8", 8, 1920, 4160), ("fp8", 8, 2048, 4160), ("fp4", 8, 2048, 4224),
                                        ("fp8", 64, 4096, 4160)])
 def test_huge_quantised_experts_in_one_launch(L, fmt, T, H, F):
